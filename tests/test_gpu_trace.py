@@ -100,3 +100,20 @@ def test_workload1_full_view_sampled(gpu_lib):
     valid = leaf >= 0
     assert np.array_equal(valid.sum(axis=1), cnt)
     assert np.all(tin[valid] < tout[valid])
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 257])
+@pytest.mark.parametrize("depth,K", [(1, 1), (1, 3), (2, 2), (3, 4), (3, 7), (4, 16)])
+def test_hit_limit_inside_a_leaf_group(gpu_lib, n, depth, K):
+    """A full grid, so that the hit limit falls at every place inside the up
+    to four hits of one leaf parent; rays through lattice points (several
+    middle planes crossed at once) and axis-parallel ones among them, at ray
+    counts around the traversal's block size."""
+    cells = crafted_occupancy("full", depth, seed=0)
+    rng = np.random.default_rng(100 * depth + K + n)
+    o, d = random_rays(rng, n, inside_frac=0.3, axis_frac=0.2)
+    lattice = rng.random(n) < 0.4
+    o[lattice] = rng.integers(-3, 4, (int(lattice.sum()), 3)) * (2.0 / (1 << depth))
+    d[lattice] = rng.integers(-1, 2, (int(lattice.sum()), 3))
+    exp = oracle_trace(Octree(cells, depth), o, d, K)
+    _assert_identical(_gpu_trace(gpu_lib, cells, depth, o, d, K), exp, f"n{n} d{depth} K{K}")
