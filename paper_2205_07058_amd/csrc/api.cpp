@@ -145,12 +145,12 @@ int make_table(const svlf_scene* scenes, int n_scenes, const int64_t* offs, bool
     d.ray_begin = offs[s];
     d.ray_end = offs[s + 1];
     d.depth = sc.octree.depth;
-    d.block_begin = static_cast<int32_t>(blocks);
-    blocks += (offs[s + 1] - offs[s] + kRaysPerBlock - 1) / kRaysPerBlock;
+    d.trace_begin = static_cast<int32_t>(blocks);
+    blocks += (offs[s + 1] - offs[s] + kTraceThreads - 1) / kTraceThreads;
+    if (blocks > (int64_t(1) << 30))
+      return fail(SVLF_E_RANGE, who_str(who, "too many rays"));
   }
-  if (blocks > (int64_t(1) << 30))
-    return fail(SVLF_E_RANGE, who_str(who, "too many rays"));
-  tab->n_blocks = static_cast<int32_t>(blocks);
+  tab->n_trace = static_cast<int32_t>(blocks);
   return SVLF_OK;
 }
 
@@ -301,9 +301,12 @@ int run_shade(int mode, const svlf_scene* scenes, int32_t n_scenes, const int64_
   hipError_t e = hipSuccess;
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
-                              const_cast<int32_t*>(a.cnt), s);
-    if (e != hipSuccess) return hip_fail(e, who);
+                              const_cast<int32_t*>(a.cnt), a.item_counter,
+                              a.item_counter != nullptr ? 1 : 0, s);
+  } else if (a.item_counter != nullptr) {
+    e = launch_fill(reinterpret_cast<float*>(a.item_counter), 0.0f, 1, s);   // 0.0f has zero bits
   }
+  if (e != hipSuccess) return hip_fail(e, who);
   if (opts->flags & SVLF_FLAG_TRACE_ONLY) return SVLF_OK;
   const int64_t n_leaves = scenes[0].octree.n_leaves, n_vertices = scenes[0].octree.n_vertices;
   void* det_scratch = base + dx.scratch;
@@ -325,9 +328,7 @@ int run_shade(int mode, const svlf_scene* scenes, int32_t n_scenes, const int64_
     if (e != hipSuccess) return hip_fail(e, who);
   }
   int grid = 0;
-  if (a.item_counter != nullptr)
-    e = launch_fill(reinterpret_cast<float*>(a.item_counter), 0.0f, 1, s);   // 0.0f has zero bits
-  if (e == hipSuccess) e = launch_shade(a, mode, s, &grid);
+  e = launch_shade(a, mode, s, &grid);
   if (e == hipSuccess && mode != kForward)
     e = launch_reduce_partials(a.ws_partials, grid, sh.n_params, a.grad_params, a.ws_loss,
                                mode == kTrain ? a.loss_out : nullptr, s);
@@ -457,9 +458,11 @@ int run_lf_call(int mode, const svlf_scene* scenes, int32_t n_scenes, const int6
   hipError_t e = hipSuccess;
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
-                              const_cast<int32_t*>(a.cnt), s);
-    if (e != hipSuccess) return hip_fail(e, who);
+                              const_cast<int32_t*>(a.cnt), a.item_counters, 3, s);
+  } else {
+    e = launch_fill(reinterpret_cast<float*>(a.item_counters), 0.0f, 3, s);   // 0.0f has zero bits
   }
+  if (e != hipSuccess) return hip_fail(e, who);
   if (opts->flags & SVLF_FLAG_TRACE_ONLY) return SVLF_OK;
   e = launch_lf(a, mode, s);
   if (e != hipSuccess) return hip_fail(e, who);

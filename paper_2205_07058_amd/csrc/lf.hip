@@ -289,7 +289,7 @@ __device__ __forceinline__ ItemDeal item_deal(const LfArgs& a, int which) {
   d.G = gridDim.x;
   const int b = blockIdx.x;
   d.lb = (d.G % 8 == 0) ? (b % 8) * (d.G / 8) + b / 8 : b;
-  d.nb = a.tab.n_blocks;
+  d.nb = a.tab.n_items;
   d.counter = a.item_counters != nullptr ? a.item_counters + which : nullptr;
   const int n_tail = d.counter != nullptr ? (d.nb < 2 * d.G ? d.nb : 2 * d.G) : 0;
   d.n_static = d.nb - n_tail;
@@ -327,7 +327,7 @@ __device__ __forceinline__ int open_window_imap(int s0, int total, int off, int 
 
 __device__ __forceinline__ int scene_of(const SceneTable& tab, int item) {
   int si = 0;
-  while (si + 1 < tab.n && item >= tab.s[si + 1].block_begin) ++si;
+  while (si + 1 < tab.n && item >= tab.s[si + 1].item_begin) ++si;
   return si;
 }
 
@@ -522,9 +522,9 @@ __global__ __launch_bounds__(kThreads, 1) void k_density(LfArgs a) {
   ItemDeal deal = item_deal(a, CF::BWD ? 2 : 0);
   for (int item = deal.first(scr); item < deal.nb; item = deal.next(item, scr)) {
     const DevScene& sc = a.tab.s[scene_of(a.tab, item)];
-    const ItemRays ir = item_rays(sc, item);
+    const ItemRays ir = item_rays(a.tab, sc, item);
     const int64_t r = ir.ray(tid);
-    const int count = r < sc.ray_end ? a.cnt[r] : 0;
+    const int count = tid < ir.n && r < sc.ray_end ? a.cnt[r] : 0;
     const float h = __int_as_float((128 - sc.depth) << 23);
     const float inv_h = __int_as_float((126 + sc.depth) << 23);
     int total;
@@ -925,9 +925,9 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
     const float* featC32 = sc.feat32 + zc;
     const uint16_t* featC16 = sc.feat16 != nullptr ? sc.feat16 + zc : nullptr;
     float* gradC = sc.grad != nullptr ? sc.grad + zc : nullptr;
-    const ItemRays ir = item_rays(sc, item);
+    const ItemRays ir = item_rays(a.tab, sc, item);
     const int64_t r = ir.ray(tid);
-    const bool live = r < sc.ray_end;
+    const bool live = tid < ir.n && r < sc.ray_end;
     const int count = live ? a.cnt[r] : 0;
     const float h = __int_as_float((128 - sc.depth) << 23);
     const float inv_h = __int_as_float((126 + sc.depth) << 23);
@@ -1420,8 +1420,7 @@ int lf_num_cus() {
 // and LDS), at most `cap` (the backward kernels' partial sums are sized for
 // lf_grid_limit() blocks).
 template <class K>
-hipError_t launch_persistent(K kern, int lds, const LfArgs& a, hipStream_t s, int* grid_out,
-                             int cap) {
+hipError_t launch_persistent(K kern, int lds, LfArgs a, hipStream_t s, int* grid_out, int cap) {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
@@ -1431,7 +1430,8 @@ hipError_t launch_persistent(K kern, int lds, const LfArgs& a, hipStream_t s, in
     per_cu = 1;
   int grid = lf_num_cus() * per_cu;
   if (grid > cap) grid = cap;
-  if (grid > a.tab.n_blocks) grid = a.tab.n_blocks;
+  plan_items(&a.tab, grid);
+  if (grid > a.tab.n_items) grid = a.tab.n_items;
   if (grid < 1) grid = 1;
   *grid_out = grid;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, s, a);
@@ -1445,8 +1445,6 @@ hipError_t run_lf(const LfArgs& a, int mode, hipStream_t s) {
   hipLaunchKernelGGL((k_lf_pack<BF, VD>), dim3(64), dim3(kThreads), 0, s, a.params,
                      static_cast<char*>(a.packs));
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && a.item_counters != nullptr)
-    e = launch_fill(reinterpret_cast<float*>(a.item_counters), 0.0f, 3, s);   // 0.0f has zero bits
   if (e != hipSuccess) return e;
   int g1 = 0, g2 = 0, g3 = 0;
   const int fwd_cap = 4096, bwd_cap = lf_grid_limit();

@@ -108,6 +108,21 @@ __device__ __forceinline__ int kmap_x(int s, int g, int j) {
   return 4 * (2 * (s >> 2) + g) + (s & 3);
 }
 
+// Inverses of kmap_d / kmap_x: where K index k sits in its operand.
+struct KPos {
+  int s, g, j;
+};
+template <bool BF>
+__device__ __forceinline__ KPos kpos_d(int k) {
+  if (BF) return {k >> 4, (k >> 2) & 1, ((k >> 1) & 4) | (k & 3)};
+  return {4 * (k >> 3) + (k & 3), (k >> 2) & 1, 0};
+}
+template <bool BF>
+__device__ __forceinline__ KPos kpos_x(int k) {
+  if (BF) return {k >> 4, (k >> 3) & 1, k & 7};
+  return {4 * (k >> 3) + (k & 3), (k >> 2) & 1, 0};
+}
+
 constexpr int align16(int x) { return (x + 15) & ~15; }
 constexpr int align8(int x) { return (x + 7) & ~7; }
 constexpr int align32(int x) { return (x + 31) & ~31; }

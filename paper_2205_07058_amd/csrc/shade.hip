@@ -185,36 +185,56 @@ __device__ __forceinline__ typename CF::Elem to_elem(float v) {
 
 // ------------------------------------------------------------ weight packs
 
+// Every block builds its own packs, so a small call waits for this: all of the
+// parameters are read at once, in order (a read per pack entry, in loops, was
+// latency-bound), then scattered to their places in the forward and the
+// transposed pack.  Ends without a barrier.
 template <class CF>
 __device__ __forceinline__ void build_packs(const Smem<CF>& sm, const float* __restrict__ params) {
   constexpr int E = CF::BF ? 8 : 1;
-  static_for<CF::NL>([&](auto lc) {
-    constexpr int l = decltype(lc)::value;
-    constexpr int IW = in_w(l, CF::CI, CF::H), OW = out_w(l, CF::H, CF::NH);
-    constexpr int IR = in_real(l, CF::CIN, CF::H), OR = out_real(l, CF::H, CF::NH);
-    constexpr int STEPS = IW / CF::KS;
-    const float* W = params + par_w(l, CF::CIN, CF::H, CF::NH);
-    const float* b = params + par_b(l, CF::CIN, CF::H, CF::NH);
-    typename CF::Elem* fp = sm.fpack() + fwd_off(l, CF::CI, CF::H, CF::NH);
-    for (int e = threadIdx.x; e < OW * IW; e += kThreads) {
-      const int j = e % E, lane = (e / E) % 64, s = (e / (E * 64)) % STEPS, mt = e / (E * 64 * STEPS);
-      const int m = 32 * mt + (lane & 31), g = lane >> 5;
-      const int k = (l == 0) ? kmap_x<CF::BF>(s, g, j) : kmap_d<CF::BF>(s, g, j);
-      fp[e] = to_elem<CF>((m < OR && k < IR) ? W[m * IR + k] : 0.0f);
-    }
-    for (int r = threadIdx.x; r < OW; r += kThreads)
-      sm.bias()[bias_off(l, CF::H, CF::NH) + r] = r < OR ? b[r] : 0.0f;
-    if constexpr (CF::BWD) {
-      // transposed pack: M = layer input (padded), K = layer output (D layout)
-      constexpr int BM = bwd_m(l, CF::H), BSTEPS = OW / CF::KS;
-      typename CF::Elem* bp = sm.bpack() + bwd_off(l, CF::H, CF::NH);
-      for (int e = threadIdx.x; e < BM * OW; e += kThreads) {
-        const int j = e % E, lane = (e / E) % 64, s = (e / (E * 64)) % BSTEPS, mt = e / (E * 64 * BSTEPS);
-        const int m = 32 * mt + (lane & 31), g = lane >> 5;
-        const int k = kmap_d<CF::BF>(s, g, j);
-        bp[e] = to_elem<CF>((m < IR && k < OR) ? W[k * IR + m] : 0.0f);
+  constexpr int N = (CF::NPARAMS + kThreads - 1) / kThreads;
+  const int tid = threadIdx.x;
+  float v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = i * kThreads + tid < CF::NPARAMS ? params[i * kThreads + tid] : 0.0f;
+  // padding (input columns, output rows) stays zero
+  static_assert(CF::L_FP == 0 && (CF::L_BI + CF::BIAS_ELEMS * 4) % 16 == 0, "packs and biases lead the LDS");
+  uint4* z = reinterpret_cast<uint4*>(g_smem);
+  for (int e = tid; e < (CF::L_BI + CF::BIAS_ELEMS * 4) / 16; e += kThreads) z[e] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  static_for<N>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const int idx = i * kThreads + tid;
+    static_for<CF::NL>([&](auto lc) {
+      constexpr int l = decltype(lc)::value;
+      constexpr int IW = in_w(l, CF::CI, CF::H), OW = out_w(l, CF::H, CF::NH);
+      constexpr int IR = in_real(l, CF::CIN, CF::H), OR = out_real(l, CF::H, CF::NH);
+      constexpr int PW = par_w(l, CF::CIN, CF::H, CF::NH), PB = par_b(l, CF::CIN, CF::H, CF::NH);
+      if constexpr (PW < (i + 1) * kThreads && PB > i * kThreads) {
+        if (idx >= PW && idx < PB) {
+          const int m = (idx - PW) / IR, k = (idx - PW) % IR;
+          const typename CF::Elem w = to_elem<CF>(v[i]);
+          {
+            const KPos p = l == 0 ? kpos_x<CF::BF>(k) : kpos_d<CF::BF>(k);
+            const int lane = (m & 31) + 32 * p.g;
+            sm.fpack()[fwd_off(l, CF::CI, CF::H, CF::NH) +
+                       (((m >> 5) * (IW / CF::KS) + p.s) * 64 + lane) * E + p.j] = w;
+          }
+          if constexpr (CF::BWD) {
+            // transposed pack: M = layer input (features only), K = layer output
+            if (k < bwd_m(l, CF::H)) {
+              const KPos p = kpos_d<CF::BF>(m);
+              const int lane = (k & 31) + 32 * p.g;
+              sm.bpack()[bwd_off(l, CF::H, CF::NH) +
+                         (((k >> 5) * (OW / CF::KS) + p.s) * 64 + lane) * E + p.j] = w;
+            }
+          }
+        }
       }
-    }
+      if constexpr (PB < (i + 1) * kThreads && PB + OR > i * kThreads) {
+        if (idx >= PB && idx < PB + OR) sm.bias()[bias_off(l, CF::H, CF::NH) + idx - PB] = v[i];
+      }
+    });
   });
 }
 
@@ -412,7 +432,7 @@ __global__ __launch_bounds__(kThreads, CF::BWD ? 1 : 3) void k_shade(ShadeArgs a
   // neighbouring rays in every round and shares their features in its L2.
   const int G = gridDim.x, b = blockIdx.x;
   const int lb = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
-  const int NB = a.tab.n_blocks;
+  const int NB = a.tab.n_items;
   // The last two rounds of items are handed out in order by a counter to
   // whichever block is free, so that blocks whose items held fewer hits
   // take more of them and the launch does not wait on the slowest block.
@@ -464,11 +484,11 @@ __global__ __launch_bounds__(kThreads, CF::BWD ? 1 : 3) void k_shade(ShadeArgs a
   for (int item = lb < n_static ? lb : tail_item(); item < NB;
        item = item + G < n_static ? item + G : tail_item()) {
     int si = 0;
-    while (si + 1 < a.tab.n && item >= a.tab.s[si + 1].block_begin) ++si;
+    while (si + 1 < a.tab.n && item >= a.tab.s[si + 1].item_begin) ++si;
     const DevScene& sc = a.tab.s[si];
-    const ItemRays ir = item_rays(sc, item);
+    const ItemRays ir = item_rays(a.tab, sc, item);
     const int64_t r = ir.ray(tid);
-    const bool live = r < sc.ray_end;
+    const bool live = tid < ir.n && r < sc.ray_end;
     const int count = live ? a.cnt[r] : 0;
     // the ray's target (train) or upstream gradient (backward), read before
     // any window so that no load waits behind pending atomics
@@ -1053,7 +1073,7 @@ int num_cus() {
 }
 
 template <class CF>
-hipError_t run(const ShadeArgs& a, hipStream_t s, int* grid_used) {
+hipError_t run(ShadeArgs a, hipStream_t s, int* grid_used) {
   const auto kern = k_shade<CF>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, CF::LDS_BYTES);
@@ -1068,7 +1088,8 @@ hipError_t run(const ShadeArgs& a, hipStream_t s, int* grid_used) {
   if (occ > 0 && occ < per_cu) per_cu = occ;
   int grid = num_cus() * (per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu));
   if (grid > shade_grid_limit()) grid = shade_grid_limit();
-  if (grid > a.tab.n_blocks) grid = a.tab.n_blocks;
+  plan_items(&a.tab, grid);
+  if (grid > a.tab.n_items) grid = a.tab.n_items;
   if (grid < 1) grid = 1;
   *grid_used = grid;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), CF::LDS_BYTES, s, a);

@@ -27,13 +27,16 @@ struct DevScene {
   int64_t ray_begin;      // first ray of this scene
   int64_t ray_end;
   int32_t depth;
-  int32_t block_begin;    // first 256-ray block of this scene in the grid
+  int32_t item_begin;     // first work item of this scene (plan_items)
+  int32_t trace_begin;    // first traversal block of this scene
 };
 
 struct SceneTable {
   DevScene s[SVLF_MAX_SCENES];
   int32_t n;
-  int32_t n_blocks;       // total 256-ray blocks over all scenes
+  int32_t item_rays;      // rays per work item (plan_items)
+  int32_t n_items;        // work items over all scenes (plan_items)
+  int32_t n_trace;        // traversal blocks over all scenes
 };
 
 // Internal hit record, one per (ray, slot): leaf id, t_in, t_out and the
@@ -45,31 +48,61 @@ struct HitRec {
   uint32_t ijk;
 };
 
-constexpr int kRaysPerBlock = 256;
+constexpr int kRaysPerBlock = 256;   // most rays of a work item (one per thread)
+constexpr int kTraceThreads = 64;    // rays (threads) of a traversal block
 
-// Rays of one work item (kRaysPerBlock rays) of the shading kernels.  The
-// rays of kIlvItems consecutive full items of a scene are interleaved: item
-// j of such a group takes rays j, j + kIlvItems, j + 2 kIlvItems, ... of
-// the group, so that one item's rays lie far apart in the caller's order
-// while the group, whose items run at about the same time, covers one
-// contiguous range.  Other items take kRaysPerBlock consecutive rays.
-// Lane t of the item handles ray base + t * stride (it may be past the
-// scene's last ray only in a scene's last, partial item).
+// Work items of the shading kernels: up to kRaysPerBlock rays of one scene.
+// Where the rays fill a few rounds of the persistent grid at most, an item
+// takes the share of the rays that gives every block the same number of
+// items, in as few rounds as 256-ray items would need: 4,096 rays in 256-ray
+// items keep 16 of 256 blocks busy, and 100,003 rays give 391 items, two
+// rounds with the second half empty.  From kBalancedRounds rounds on, full
+// items are interleaved (below) and the last rounds are handed out on demand,
+// which balances as well.
+constexpr int kBalancedRounds = 3;
+constexpr int kMinItemRays = 16;
+
+inline void plan_items(SceneTable* tab, int blocks) {
+  const int64_t n = tab->s[tab->n - 1].ray_end - tab->s[0].ray_begin;
+  const int64_t round = static_cast<int64_t>(blocks) * kRaysPerBlock;
+  const int64_t rounds = (n + round - 1) / round;
+  int64_t rays = kRaysPerBlock;
+  if (rounds >= 1 && rounds <= kBalancedRounds) {
+    rays = (n + rounds * blocks - 1) / (rounds * blocks);
+    if (rays < kMinItemRays) rays = kMinItemRays;
+  }
+  tab->item_rays = static_cast<int32_t>(rays);
+  int64_t items = 0;
+  for (int s = 0; s < tab->n; ++s) {
+    tab->s[s].item_begin = static_cast<int32_t>(items);
+    items += (tab->s[s].ray_end - tab->s[s].ray_begin + rays - 1) / rays;
+  }
+  tab->n_items = static_cast<int32_t>(items);
+}
+
+// Rays of one work item.  The rays of kIlvItems consecutive full
+// kRaysPerBlock-ray items of a scene are interleaved: item j of such a group
+// takes rays j, j + kIlvItems, j + 2 kIlvItems, ... of the group, so that one
+// item's rays lie far apart in the caller's order while the group, whose
+// items run at about the same time, covers one contiguous range.  Other items
+// take consecutive rays.  Lane t < n of the item handles ray base + t * stride
+// (it may be past the scene's last ray only in a scene's last, partial item).
 constexpr int kIlvItems = 256;
 
 struct ItemRays {
   int64_t base;
-  int stride;
+  int stride, n;
   __device__ __forceinline__ int64_t ray(int lane) const {
     return base + static_cast<int64_t>(lane) * stride;
   }
 };
 
-__device__ __forceinline__ ItemRays item_rays(const DevScene& sc, int item) {
-  const int64_t li = item - sc.block_begin, g0 = li / kIlvItems * kIlvItems;
-  if ((g0 + kIlvItems) * kRaysPerBlock <= sc.ray_end - sc.ray_begin)
-    return {sc.ray_begin + g0 * kRaysPerBlock + (li - g0), kIlvItems};
-  return {sc.ray_begin + li * kRaysPerBlock, 1};
+__device__ __forceinline__ ItemRays item_rays(const SceneTable& tab, const DevScene& sc, int item) {
+  const int n = tab.item_rays;
+  const int64_t li = item - sc.item_begin, g0 = li / kIlvItems * kIlvItems;
+  if (n == kRaysPerBlock && (g0 + kIlvItems) * kRaysPerBlock <= sc.ray_end - sc.ray_begin)
+    return {sc.ray_begin + g0 * kRaysPerBlock + (li - g0), kIlvItems, n};
+  return {sc.ray_begin + li * n, 1, n};
 }
 
 // Launchers (defined in the .hip files).
@@ -77,7 +110,8 @@ hipError_t launch_trace_public(const svlf_octree& oct, const float* o, const flo
                                int64_t n, int K, int32_t* leaf, float* tin, float* tout,
                                int32_t* cnt, hipStream_t s);
 hipError_t launch_trace_internal(const SceneTable& tab, const float* o, const float* d,
-                                 int K, HitRec* hits, int32_t* cnt, hipStream_t s);
+                                 int K, HitRec* hits, int32_t* cnt, int32_t* zero, int n_zero,
+                                 hipStream_t s);
 
 struct ShadeArgs {
   SceneTable tab;

@@ -8,12 +8,9 @@
 namespace svlf {
 namespace {
 
-// One wave per block: a block's LDS and slots are free as soon as its own
-// longest ray is done, and few rays spread over more CUs (4,096 rays at depth
-// 8: 55 us with 256-thread blocks, 50 us with 64).
-constexpr int kTraceThreads = 64;
-static_assert(kRaysPerBlock % kTraceThreads == 0, "a ray block is whole traversal blocks");
-constexpr int kTracePerBlock = kRaysPerBlock / kTraceThreads;
+// One wave per block (kTraceThreads): a block's LDS and slots are free as soon
+// as its own longest ray is done, and few rays spread over more CUs (4,096
+// rays at depth 8: 55 us with 256-thread blocks, 50 us with 64).
 
 __device__ __forceinline__ Ray load_ray(const float* __restrict__ o, const float* __restrict__ d,
                                         int64_t r) {
@@ -59,18 +56,19 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace_public(
 }
 
 // Internal layout for the shading kernels: one 16-byte record per hit slot
-// (unused slots are left unwritten), rays grouped by scene.
+// (unused slots are left unwritten), rays grouped by scene.  The first block
+// also clears the shading kernels' work-item counters (a launch of its own
+// costs about 5 us, an eighth of a 4,096-ray render).
 __global__ __launch_bounds__(kTraceThreads) void k_trace_internal(
     SceneTable tab, const float* __restrict__ o, const float* __restrict__ d, int K,
-    HitRec* hits, int32_t* __restrict__ cnt_out) {
+    HitRec* hits, int32_t* __restrict__ cnt_out, int32_t* __restrict__ zero, int n_zero) {
   extern __shared__ uint2 stk[];
-  const int b = blockIdx.x / kTracePerBlock;
+  const int b = blockIdx.x;
+  if (b == 0 && static_cast<int>(threadIdx.x) < n_zero) zero[threadIdx.x] = 0;
   int s = 0;
-  while (s + 1 < tab.n && b >= tab.s[s + 1].block_begin) ++s;
+  while (s + 1 < tab.n && b >= tab.s[s + 1].trace_begin) ++s;
   const DevScene& sc = tab.s[s];
-  const int64_t r = sc.ray_begin +
-                    static_cast<int64_t>(static_cast<int>(blockIdx.x) - sc.block_begin * kTracePerBlock) *
-                        kTraceThreads +
+  const int64_t r = sc.ray_begin + static_cast<int64_t>(b - sc.trace_begin) * kTraceThreads +
                     threadIdx.x;
   if (r >= sc.ray_end) return;
   int count = 0;
@@ -118,12 +116,14 @@ hipError_t launch_trace_public(const svlf_octree& oct, const float* o, const flo
 }
 
 hipError_t launch_trace_internal(const SceneTable& tab, const float* o, const float* d, int K,
-                                 HitRec* hits, int32_t* cnt, hipStream_t s) {
-  if (tab.n_blocks == 0) return hipSuccess;
+                                 HitRec* hits, int32_t* cnt, int32_t* zero, int n_zero,
+                                 hipStream_t s) {
+  if (tab.n_trace == 0) return hipSuccess;
   int max_depth = 1;
   for (int i = 0; i < tab.n; ++i) max_depth = tab.s[i].depth > max_depth ? tab.s[i].depth : max_depth;
-  hipLaunchKernelGGL(k_trace_internal, dim3(static_cast<unsigned>(tab.n_blocks) * kTracePerBlock),
-                     dim3(kTraceThreads), stack_bytes(max_depth), s, tab, o, d, K, hits, cnt);
+  hipLaunchKernelGGL(k_trace_internal, dim3(static_cast<unsigned>(tab.n_trace)),
+                     dim3(kTraceThreads), stack_bytes(max_depth), s, tab, o, d, K, hits, cnt,
+                     zero, n_zero);
   return hipGetLastError();
 }
 
