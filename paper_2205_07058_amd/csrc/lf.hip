@@ -13,20 +13,40 @@
 // of them can be trained or frozen as one contiguous array).  Decoder
 // inputs are ordered [features | r | (d)].
 //
-// Three kernels, all persistent over 256-ray items with ray-aligned hit
-// windows (as the single-decoder kernels):
+// Three kernels, all persistent over work items with ray-aligned hit windows
+// (as the single-decoder kernels):
 //  * k_density: records, gather of the 8 corner rows of Z_T (one gather
 //    serves x1 and x2: both lie on the same voxel), r, F_T on MFMA, and per
 //    hit tau, eta and the surface point (written to the workspace); in
 //    backward mode it recomputes F_T, back-propagates dL/d(o_T0, o_T1) left
 //    by the colour kernel, accumulates F_T's weight gradients and scatters
 //    dL/dZ_T;
-//  * k_color: gather of Z_C at the surface point, F_C on MFMA (hidden
-//    activations kept transposed in LDS in backward mode), Eq. 3, and in
+//  * k_color: gather of Z_C at the surface point, F_C on MFMA, Eq. 3, and in
 //    backward / train mode the compositing backward, F_C's backward, the
 //    scatter of dL/dZ_C, and dL/deta through the interpolation at x_s;
 //  * k_lf_pack: MFMA operand packs of both decoders (forward and transposed)
-//    from the FP32 masters, read by the kernels from global memory (L2).
+//    from the FP32 masters.
+//
+// Decoder organisation.  A hidden layer is 128 x 128: its weights are far too
+// many for one wave, and reading them from L2 for every 32-hit tile left the
+// matrix cores idle behind the loads (and, in the backward, behind the
+// gradient atomics that the vector-memory counter orders before them).  So
+// the layer is split over the block's four waves by OUTPUT features: wave w
+// owns features [32 w, 32 w + 32) of every hidden layer, for all hits of the
+// window.
+//  * BF16: a wave's share of all layers, forward and transposed, is loaded
+//    into registers once per launch (36 to 148 VGPRs / AGPRs) and stays there;
+//  * FP32: a share is 64 VGPRs per layer, read once per 64-hit window (the
+//    next layer's while the current one multiplies);
+//  * activations pass through LDS, [hit][feature] in 16-byte chunks that are
+//    MFMA operands as they stand (Tile), written once and read by all waves;
+//  * weight gradients: wave w owns the rows of its features, accumulated in
+//    registers over the whole launch; the operands need the hits along K, so
+//    BF16 reads the same tiles through the LDS transpose read
+//    (ds_read_b64_tr_b16) and FP32 reads them as they are;
+//  * dL/dz of a layer overwrites that layer's activations in place (a wave
+//    masks and replaces its own features);
+//  * the narrow ends (decoder outputs, dL/dx) are split by hits instead.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -120,49 +140,47 @@ __device__ __forceinline__ typename Types<BF>::Elem to_el(float v) {
   else return v;
 }
 
-// operand (mt, s) of a packed matrix in global memory
+// Operands come in fragments of 16 bytes per lane: one K step of the BF16 MFMA
+// or four of the FP32 one.  K index of fragment i, lane group g, element j:
+// kfrag_d for operands made of result tiles (drow), kfrag_x for natural rows.
+typedef int frag_t __attribute__((ext_vector_type(4)));
 template <bool BF>
-__device__ __forceinline__ typename Types<BF>::Op gop(const typename Types<BF>::Elem* __restrict__ p,
-                                                      int mt, int s, int steps, int lane) {
-  if constexpr (BF)
-    return *reinterpret_cast<const s16x8*>(p + (static_cast<size_t>(mt * steps + s) * 64 + lane) * 8);
-  else
-    return p[(mt * steps + s) * 64 + lane];
+constexpr int kFragK = BF ? 16 : 8;
+template <bool BF>
+__device__ __forceinline__ int kfrag_d(int i, int g, int j) {
+  return BF ? 16 * i + 8 * (j >> 2) + 4 * g + (j & 3) : 8 * i + 4 * g + j;
+}
+template <bool BF>
+__device__ __forceinline__ int kfrag_x(int i, int g, int j) {
+  return BF ? 16 * i + 8 * g + j : 8 * i + 4 * g + j;
 }
 
-// Weight operands are read with buffer loads: the per-(tile, step) offset is
-// a scalar (SGPR) and only the lane offset lives in a VGPR, so a fully
-// unrolled layer needs no per-load address registers; loads past the end of
-// the pack return 0.
-typedef int v4i_t __attribute__((ext_vector_type(4)));
+template <bool BF>
+__device__ __forceinline__ f32x16 mma_frag(frag_t a, frag_t b, f32x16 c) {
+  if constexpr (BF) {
+    return mma(__builtin_bit_cast(s16x8, a), __builtin_bit_cast(s16x8, b), c);
+  } else {
+    const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c = mma(x[j], y[j], c);
+    return c;
+  }
+}
+
+// Weight fragments are read with buffer loads: the per-fragment offset is a
+// scalar (SGPR) and only the lane offset lives in a VGPR; loads past the end
+// of the pack return 0.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t pack_rsrc(const void* p, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
-template <bool BF>
-__device__ __forceinline__ typename Types<BF>::Op gopb(__amdgpu_buffer_rsrc_t rs, int byte_base,
-                                                       int mt, int s, int steps, int lane) {
-  if constexpr (BF) {
-    const v4i_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, byte_base + (mt * steps + s) * 1024, 0);
-    return __builtin_bit_cast(s16x8, v);
-  } else {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, byte_base + (mt * steps + s) * 256, 0));
-  }
-}
-
-// B operand of step s from D-layout tiles
-template <bool BF>
-__device__ __forceinline__ typename Types<BF>::Op dop(const f32x16* t, int s) {
-  if constexpr (BF) {
-    s16x8 b;
-    const f32x16& tt = t[s >> 1];
-    {
-      const int o = 8 * (s & 1);
-      b = bf16_rne8(tt[o], tt[o + 1], tt[o + 2], tt[o + 3], tt[o + 4], tt[o + 5], tt[o + 6], tt[o + 7]);
-    }
-    return b;
-  } else {
-    return t[s >> 4][s & 15];
-  }
+// fragments [0, N) of M tile mt of a packed matrix with NF fragments per tile
+template <int N>
+__device__ __forceinline__ void load_frags(frag_t (&w)[N], __amdgpu_buffer_rsrc_t rs, int byte_base,
+                                           int mt, int NF, int lane) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    w[i] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                          rs, lane * 16, byte_base + (mt * NF + i) * 1024, 0));
 }
 
 __device__ __forceinline__ f32x16 gbias(const float* __restrict__ b, int mt, int g) {
@@ -179,39 +197,6 @@ __device__ __forceinline__ f32x16 gbias(const float* __restrict__ b, int mt, int
   return t;
 }
 
-template <bool BF>
-struct ActT;
-template <>
-struct ActT<true> {
-  s16x8 lo, hi;
-  __device__ __forceinline__ void set(const f32x16& t) {
-    lo = bf16_rne8(t[0], t[1], t[2], t[3], t[4], t[5], t[6], t[7]);
-    hi = bf16_rne8(t[8], t[9], t[10], t[11], t[12], t[13], t[14], t[15]);
-  }
-  __device__ __forceinline__ bool positive(int i) const { return (i < 8 ? lo[i] : hi[i - 8]) > 0; }
-  __device__ __forceinline__ uint16_t elem(int i) const {
-    return static_cast<uint16_t>(i < 8 ? lo[i] : hi[i - 8]);
-  }
-};
-template <>
-struct ActT<false> {
-  f32x16 v;
-  __device__ __forceinline__ void set(const f32x16& t) { v = t; }
-  __device__ __forceinline__ bool positive(int i) const { return v[i] > 0.0f; }
-  __device__ __forceinline__ float elem(int i) const { return v[i]; }
-};
-
-// Keeps the compiler from hoisting the weight loads of a whole layer ahead
-// of its MFMAs (they come from global memory; hoisting them all would need a
-// register per operand): no instruction moves across the fence, which is
-// placed every CH K-steps of a fully unrolled loop.
-template <int CH>
-__device__ __forceinline__ void chunk_fence(int s) {
-  if ((s + 1) % CH == 0) __builtin_amdgcn_sched_barrier(0);
-}
-template <bool BF>
-constexpr int kChunk = BF ? 4 : 16;
-
 // ------------------------------------------------------------ packing
 
 // Packs one decoder from its FP32 layers (params) into [fwd][bwd] operand
@@ -219,7 +204,7 @@ constexpr int kChunk = BF ? 4 : 16;
 template <bool BF, class M>
 __device__ void pack_decoder(const float* __restrict__ params, char* __restrict__ out) {
   using El = typename Types<BF>::Elem;
-  constexpr int E = BF ? 8 : 1;
+  constexpr int E = BF ? 8 : 4;
   El* fp = reinterpret_cast<El*>(out);
   El* bp = fp + M::FWD;
   float* bias = reinterpret_cast<float*>(out + M::pack_bytes(Types<BF>::EB) - M::BIAS * 4);
@@ -228,23 +213,23 @@ __device__ void pack_decoder(const float* __restrict__ params, char* __restrict_
   static_for<M::NL>([&](auto lc) {
     constexpr int l = decltype(lc)::value;
     constexpr int IW = M::in_p(l), OW = M::out_p(l), IR = M::in_r(l), OR = M::out_r(l);
-    constexpr int STEPS = IW / M::KS;
+    constexpr int STEPS = IW / kFragK<BF>;
     const float* W = params + M::par_w(l);
     const float* b = params + M::par_b(l);
     El* f = fp + M::fwd_off(l);
     for (int e = t0; e < OW * IW; e += stride) {
       const int j = e % E, lane = (e / E) % 64, s = (e / (E * 64)) % STEPS, mt = e / (E * 64 * STEPS);
       const int m = 32 * mt + (lane & 31), g = lane >> 5;
-      const int k = (l == 0) ? kmap_x<BF>(s, g, j) : kmap_d<BF>(s, g, j);
+      const int k = (l == 0) ? kfrag_x<BF>(s, g, j) : kfrag_d<BF>(s, g, j);
       f[e] = to_el<BF>((m < OR && k < IR) ? W[m * IR + k] : 0.0f);
     }
     // transposed: M = layer input (the first bm(l) only), K = layer output
-    constexpr int BM = M::bm(l), BSTEPS = OW / M::KS;
+    constexpr int BM = M::bm(l), BSTEPS = OW / kFragK<BF>;
     El* bb = bp + M::bwd_off(l);
     for (int e = t0; e < BM * OW; e += stride) {
       const int j = e % E, lane = (e / E) % 64, s = (e / (E * 64)) % BSTEPS, mt = e / (E * 64 * BSTEPS);
       const int m = 32 * mt + (lane & 31), g = lane >> 5;
-      const int k = kmap_d<BF>(s, g, j);
+      const int k = kfrag_d<BF>(s, g, j);
       bb[e] = to_el<BF>((m < IR && k < OR) ? W[k * IR + m] : 0.0f);
     }
     for (int r = t0; r < OW; r += stride) bias[M::bias_off(l) + r] = r < OR ? b[r] : 0.0f;
@@ -264,8 +249,6 @@ __global__ __launch_bounds__(kThreads) void k_lf_pack(const float* __restrict__ 
 
 extern __shared__ __attribute__((aligned(16))) char g_lds[];
 
-// Hit window: the rays of the item whose hits all fit in [s0, s0 + WIN);
-// returns s1 (end of the window) and publishes hit -> (ray lane | slot << 16).
 // Work items of a persistent light-field kernel: dealt round-robin over the
 // grid (the logical block index groups the blocks of one XCD), except the
 // last two rounds, which `counter` hands out in order to whichever block
@@ -296,31 +279,15 @@ __device__ __forceinline__ ItemDeal item_deal(const LfArgs& a, int which) {
   return d;
 }
 
+// Hit window [s0, s1): the rays whose hits all fit in [s0, s0 + WIN), from the
+// map of the item's hits (hit -> lane | slot << 8, written once per item): the
+// window ends at the start of the ray that holds hit s0 + WIN (no ray is longer
+// than a window).  No barrier.
 template <int WIN>
-__device__ __forceinline__ int open_window(int s0, int total, int off, int count, int* scr,
-                                           int* hmap, bool& in_win) {
-  const int tid = threadIdx.x;
-  if (tid == 0) scr[8] = total;
-  __syncthreads();
-  const bool started = count > 0 && off >= s0;
-  in_win = started && off + count <= s0 + WIN;
-  if (started && !in_win) atomicMin(&scr[8], off);
-  __syncthreads();
-  const int s1 = scr[8];
-  if (in_win)
-    for (int q = 0; q < count; ++q) hmap[off - s0 + q] = tid | (q << 16);
-  __syncthreads();
-  return s1;
-}
-
-// The same window from a map of all of the item's hits (hit -> lane |
-// slot << 16, written once per item): the window ends at the start of the
-// ray that holds hit s0 + WIN (no ray is longer than a window).  No barrier.
-template <int WIN>
-__device__ __forceinline__ int open_window_imap(int s0, int total, int off, int count,
-                                                const int* imap, bool& in_win) {
+__device__ __forceinline__ int open_window(int s0, int total, int off, int count,
+                                           const uint16_t* imap, bool& in_win) {
   const int p = s0 + WIN;
-  const int s1 = p < total ? p - (imap[p] >> 16) : total;
+  const int s1 = p < total ? p - (imap[p] >> 8) : total;
   in_win = count > 0 && off >= s0 && off + count <= s1;
   return s1;
 }
@@ -361,50 +328,285 @@ __device__ __forceinline__ void sphere_r(float y0, float y1, float y2, float dx,
   }
 }
 
-// dW tiles of layer l for one window (K = the window's hits, read
-// transposed from LDS: GZ rows = layer outputs, AT rows = layer inputs),
-// added into this block's partial sums (FP32, parameter layout).  A tile is
-// owned by one wave, so the additions never collide; they are
-// workgroup-scope atomics only so that the wave does not wait for a load
-// of the old values (the block's partials are private to the block and are
-// read by the reduction kernel after this kernel ends).  Only one tile is
-// live in registers at a time.
-template <bool BF, class M, int l, int WIN, int TS>
-__device__ __forceinline__ void dw_window(const typename Types<BF>::El* GZ,
-                                          const typename Types<BF>::El* AT, float* __restrict__ part,
-                                          int wave, int lane) {
-  using El = typename Types<BF>::El;
-  constexpr int MT = M::dw_mt(l), NT = M::dw_nt(l), T0 = M::dw_off(l);
-  constexpr int KSTEPS = WIN / M::KS;
-  constexpr int IR = M::in_r(l), OR = M::out_r(l);
-  const int g = lane >> 5;
-#pragma unroll 1
-  for (int t = 0; t < MT * NT; ++t) {
-    if ((T0 + t) % kWaves != wave) continue;
-    const int mt = t / NT, nt = t % NT;
-    const El* ga_ = GZ + (32 * mt + (lane & 31)) * TS;
-    const El* gb_ = AT + (32 * nt + (lane & 31)) * TS;
-    f32x16 acc = zero16();
+// ------------------------------------------------------------ LDS tiles
+
+// The compiler would hoist every tile address (a register per chunk and tile)
+// out of the window loop; recomputing them where they are used costs a few
+// instructions instead of some two hundred registers.
+__device__ __forceinline__ int here(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// LDS tile [hit][column], ROWB bytes a row, addressed in 16-byte chunks.  The
+// chunk index is swizzled by the hit so that neither of the two access
+// patterns conflicts: 16 lanes reading the same chunk of 16 hits (operands
+// with the features along K), and the transpose read's 4 hits x 64 bytes
+// (operands with the hits along K).  A 256- or 512-byte row covers all banks,
+// so hit bits 0-1 choose the 64-byte quarter and bits 2-3 the chunk in it;
+// the other widths start neighbouring rows in different banks already and
+// need fewer bits.
+template <int ROWB>
+__device__ __forceinline__ int tile_swz(int hit) {
+  if constexpr (ROWB == 256 || ROWB == 512) return ((hit & 3) << 2) | ((hit >> 2) & 3);
+  else if constexpr (ROWB == 640) return (hit >> 1) & 7;
+  else if constexpr (ROWB == 320) return (hit >> 2) & 3;
+  else {
+    static_assert(ROWB == 128, "tile width");
+    return ((hit & 2) << 1) | ((hit >> 2) & 3);
+  }
+}
+template <int ROWB>
+__device__ __forceinline__ char* tile_at(int base, int hit, int chunk) {
+  return g_lds + base + hit * ROWB + ((chunk ^ tile_swz<ROWB>(hit)) << 4);
+}
+template <int ROWB>
+__device__ __forceinline__ frag_t frag_at(int base, int hit, int chunk) {
+  return *reinterpret_cast<const frag_t*>(tile_at<ROWB>(base, hit, chunk));
+}
+
+// Chunks of a 32-feature result tile: chunk q of tile t holds result registers
+// [16 / NCH q, 16 / NCH (q + 1)) of one lane, at chunk 2 (NCH t + q) + g of its
+// hit's row, which makes it fragment NCH t + q of the next layer's operand.
+template <bool BF>
+constexpr int kTileChunks = BF ? 2 : 4;
+
+template <bool BF>
+__device__ __forceinline__ frag_t pack_chunk(const f32x16& v, int q) {
+  if constexpr (BF)
+    return __builtin_bit_cast(frag_t, bf16_rne8(v[8 * q], v[8 * q + 1], v[8 * q + 2], v[8 * q + 3],
+                                                v[8 * q + 4], v[8 * q + 5], v[8 * q + 6], v[8 * q + 7]));
+  else
+    return __builtin_bit_cast(frag_t, f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]});
+}
+
+template <bool BF, int ROWB>
+__device__ __forceinline__ void store_tile(int base, int t, int hit, int g, const f32x16& v) {
+  hit = here(hit);
 #pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) {
-      if constexpr (BF) {
-        const s16x8 av = *reinterpret_cast<const s16x8*>(ga_ + 16 * s + 8 * g);
-        const s16x8 bv = *reinterpret_cast<const s16x8*>(gb_ + 16 * s + 8 * g);
-        acc = mma(av, bv, acc);
-      } else {
-        acc = mma(ga_[2 * s + g], gb_[2 * s + g], acc);
+  for (int q = 0; q < kTileChunks<BF>; ++q)
+    *reinterpret_cast<frag_t*>(tile_at<ROWB>(base, hit, 2 * (kTileChunks<BF> * t + q) + g)) = pack_chunk<BF>(v, q);
+}
+
+// dL/dz of a hidden layer's tile from dL/da (v): masked by the activations
+// that the tile holds, stored in their place, and added to the bias
+// gradient's per-lane sums bs (of the values as stored).
+template <bool BF, int ROWB>
+__device__ __forceinline__ void mask_store_tile(int base, int t, int hit, int g, const f32x16& v, f32x16& bs) {
+  hit = here(hit);
+#pragma unroll
+  for (int q = 0; q < kTileChunks<BF>; ++q) {
+    frag_t* at = reinterpret_cast<frag_t*>(tile_at<ROWB>(base, hit, 2 * (kTileChunks<BF> * t + q) + g));
+    if constexpr (BF) {
+      const s16x8 act = __builtin_bit_cast(s16x8, *at);
+      float z[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) z[j] = act[j] > 0 ? v[8 * q + j] : 0.0f;
+      const s16x8 r = bf16_rne8(z[0], z[1], z[2], z[3], z[4], z[5], z[6], z[7]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) bs[8 * q + j] += bf16_f32(static_cast<uint16_t>(r[j]));
+      *at = __builtin_bit_cast(frag_t, r);
+    } else {
+      const f32x4 act = __builtin_bit_cast(f32x4, *at);
+      f32x4 r;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        r[j] = act[j] > 0.0f ? v[4 * q + j] : 0.0f;
+        bs[4 * q + j] += r[j];
       }
-      chunk_fence<BF ? 2 : 8>(s);
-    }
-    const int col = 32 * nt + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int rowo = 32 * mt + drow(i, g);
-      if (rowo < OR && col < IR)
-        __hip_atomic_fetch_add(part + M::par_w(l) + rowo * IR + col, acc[i], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
+      *at = __builtin_bit_cast(frag_t, r);
     }
   }
+}
+
+// Feature (within its 32-tile) at column position p of a tile row: BF16 chunks
+// hold result registers in pairs of row quads (drow).
+template <bool BF>
+__device__ __forceinline__ int tile_feature(int p) {
+  return BF ? (p & 16) | ((p & 4) << 1) | ((p & 8) >> 1) | (p & 3) : p;
+}
+
+// One layer's share of this wave (fragments w) over the window's hits, 64 hits
+// (two independent accumulators) at a time: done(t, acc) gets each 32-hit
+// tile's result.
+template <bool BF, int ROWB, int NT, int NF, class Done>
+__device__ __forceinline__ void layer_mma(const f32x16& init, const frag_t (&w)[NF], int base, int tw, int lane,
+                                          Done&& done) {
+  lane = here(lane);
+  const int row = lane & 31, g = lane >> 5;
+  static_for<NT / 2>([&](auto pc) {
+    constexpr int p = decltype(pc)::value;
+    if (64 * p < tw) {
+      f32x16 acc[2] = {init, init};
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          acc[t] = mma_frag<BF>(w[i], frag_at<ROWB>(base, 64 * p + 32 * t + row, 2 * i + g), acc[t]);
+        if constexpr (!BF) __builtin_amdgcn_sched_barrier(0);
+      }
+      done(2 * p, acc[0]);
+      done(2 * p + 1, acc[1]);
+    }
+  });
+}
+
+// Operand with the hits along K: row / column p = lane & 31 of tile t, K = hits.
+// BF16: step k covers hits [16 k, 16 k + 16).  The transpose read gives lane i
+// of a 16-lane group column i of the 4 x 16 block whose row r lanes 4 r .. 4 r + 3
+// address, 4 columns each; two reads make the lane's 8 hits 16 k + 8 g + j.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+template <int ROWB>
+__device__ __forceinline__ s16x8 hits_operand_bf16(int base, int t, int k, int lane) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  const int i = lane & 15, g = lane >> 5;
+  const int col = (lane & 16) + 4 * (i & 3);
+  s16x8 r;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int hit = 16 * k + 8 * g + 4 * half + (i >> 2);
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (lds_s16x4*)(tile_at<ROWB>(base, hit, 4 * t + (col >> 3)) + (col & 7) * 2));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[4 * half + j] = v[j];
+  }
+  return r;
+}
+// FP32: step k covers hits 2 k and 2 k + 1.
+template <int ROWB>
+__device__ __forceinline__ float hits_operand_fp32(int base, int t, int k, int lane) {
+  const int col = lane & 31;
+  return *reinterpret_cast<const float*>(tile_at<ROWB>(base, 2 * k + (lane >> 5), 8 * t + (col >> 2)) + (col & 3) * 4);
+}
+
+// dw[nt] += (tile tA of A)^T x (tile nt of B) over the window's hits (hits from
+// tw to the next multiple of 16 are zero in one of the two and finite in the other).
+template <bool BF, int ROWA, int ROWB, int NT>
+__device__ __forceinline__ void dw_mma(f32x16 (&dw)[NT], int base_a, int ta, int base_b, int tw, int lane) {
+  lane = here(lane);
+#pragma unroll 1
+  for (int k = 0; k < (tw + 15) >> 4; ++k) {
+    if constexpr (BF) {
+      const s16x8 a = hits_operand_bf16<ROWA>(base_a, ta, k, lane);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) dw[nt] = mma(a, hits_operand_bf16<ROWB>(base_b, nt, k, lane), dw[nt]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float a = hits_operand_fp32<ROWA>(base_a, ta, 8 * k + j, lane);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) dw[nt] = mma(a, hits_operand_fp32<ROWB>(base_b, nt, 8 * k + j, lane), dw[nt]);
+      }
+    }
+  }
+}
+
+// The output layer's gradients are kept [output][hit] (row stride GOS bytes) as
+// well: dw += (tile ta of A)^T x go^T, column n = output n < OUT.
+template <bool BF, int ROWA, int OUT>
+__device__ __forceinline__ void dw_out_mma(f32x16& dw, int base_a, int ta, int base_go, int gos, int tw, int lane) {
+  lane = here(lane);
+  const int n = lane & 31, g = lane >> 5;
+#pragma unroll 1
+  for (int k = 0; k < (tw + 15) >> 4; ++k) {
+    if constexpr (BF) {
+      s16x8 b = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (n < OUT) b = *reinterpret_cast<const s16x8*>(g_lds + base_go + n * gos + (16 * k + 8 * g) * 2);
+      dw = mma(hits_operand_bf16<ROWA>(base_a, ta, k, lane), b, dw);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int st = 8 * k + j;
+        const float b = n < OUT ? *reinterpret_cast<const float*>(g_lds + base_go + n * gos + (2 * st + g) * 4) : 0.0f;
+        dw = mma(hits_operand_fp32<ROWA>(base_a, ta, st, lane), b, dw);
+      }
+    }
+  }
+}
+
+// Block partials: dW tiles of a layer whose inputs are a hidden layer's tiles
+// (HID) or the decoder's input columns, and the output layer's.
+template <bool BF, class M, int l, bool HID, int NT>
+__device__ __forceinline__ void write_dw(const f32x16 (&dw)[NT], float* __restrict__ part, int wave, int lane) {
+  const int g = lane >> 5, n = lane & 31;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int col = 32 * nt + (HID ? tile_feature<BF>(n) : n);
+    if (col < M::in_r(l)) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        part[M::par_w(l) + (32 * wave + tile_feature<BF>(drow(i, g))) * M::in_r(l) + col] = dw[nt][i];
+    }
+  }
+}
+template <bool BF, class M>
+__device__ __forceinline__ void write_dw_out(const f32x16& dw, float* __restrict__ part, int wave, int lane) {
+  const int g = lane >> 5, n = lane & 31;
+  if (n < M::OUT) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      part[M::par_w(M::NH) + n * kLfH + 32 * wave + tile_feature<BF>(drow(i, g))] = dw[i];
+  }
+}
+// Bias gradient of a hidden layer: sums the 32 lanes (hits) of each group.
+template <class M, int l>
+__device__ __forceinline__ void write_bias(f32x16 bs, float* __restrict__ part, int wave, int lane) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    float v = bs[i];
+#pragma unroll
+    for (int m = 16; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+    if ((lane & 31) == 0) part[M::par_b(l) + 32 * wave + drow(i, lane >> 5)] = v;
+  }
+}
+// Bias gradient of the output layer: per-lane sums of every wave, combined
+// through LDS (kWaves x OUT floats at `lds`) in wave order.  Called by all threads.
+template <class M>
+__device__ __forceinline__ void write_bias_out(const float (&bo)[M::OUT], float* lds, float* __restrict__ part,
+                                               int wave, int lane, int tid) {
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < M::OUT; ++c) {
+    float v = bo[c];
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+    if (lane == 0) lds[wave * M::OUT + c] = v;
+  }
+  __syncthreads();
+  if (tid < M::OUT) {
+    float v = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) v += lds[w * M::OUT + tid];
+    part[M::par_b(M::NH) + tid] = v;
+  }
+  __syncthreads();
+}
+
+// 16 bytes of a feature row as floats, and 16 bytes of a tile row from floats.
+template <bool BF>
+constexpr int kRowVals = BF ? 8 : 4;
+template <bool BF>
+__device__ __forceinline__ void unpack_row(uint4 raw, float (&f)[kRowVals<BF>]) {
+  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (BF) {
+      f[2 * i] = bf16_f32(static_cast<uint16_t>(w[i] & 0xFFFFu));
+      f[2 * i + 1] = bf16_f32(static_cast<uint16_t>(w[i] >> 16));
+    } else {
+      f[i] = __uint_as_float(w[i]);
+    }
+  }
+}
+template <bool BF>
+__device__ __forceinline__ frag_t pack_row(const float* f) {
+  if constexpr (BF) return __builtin_bit_cast(frag_t, bf16_rne8(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7]));
+  else return __builtin_bit_cast(frag_t, f32x4{f[0], f[1], f[2], f[3]});
+}
+template <bool BF>
+__device__ __forceinline__ uint4 load_row(const DevScene& sc, int64_t block, int64_t elem) {
+  if constexpr (BF) return *reinterpret_cast<const uint4*>(sc.feat16 + block + elem);
+  else return *reinterpret_cast<const uint4*>(sc.feat32 + block + elem);
 }
 
 // ------------------------------------------------------------ density kernel
@@ -417,108 +619,101 @@ struct DCfg {
   using El = typename Types<BF>::Elem;
   static constexpr int EB = Types<BF>::EB;
   static constexpr int WIN = BF ? 128 : 64;
-  static constexpr int NTILE = WIN / 32;
-  static constexpr int XS = M::IN0P + (BF ? 8 : 4);
-  static constexpr int TS = WIN + (BF ? 8 : 1);
-  static constexpr int XT_ROWS = align32(M::IN0);        // rows of X^T read by the dW tiles
-  // LDS: records (64 B / hit), X, then (backward) GZ [128][TS] and AT [XT_ROWS][TS]
-  static constexpr int L_REC = 0;
-  static constexpr int L_X = L_REC + WIN * 64;
-  static constexpr int L_GZ = align16(L_X + WIN * XS * EB);
-  static constexpr int L_AT = align16(L_GZ + (BWD ? kLfH * TS * EB : 0));
-  static constexpr int L_MAP = align16(L_AT + (BWD ? XT_ROWS * TS * EB : 0));
-  // hit map: all of a work item's hits (IMAP: backward, where it fits) or the window's
-  static constexpr bool IMAP = BWD && align16(L_MAP + kThreads * SVLF_MAX_K * 4) + 64 <= 160 * 1024;
-  static constexpr int L_SCR = align16(L_MAP + (IMAP ? kThreads * SVLF_MAX_K : WIN) * 4);
+  static constexpr int NT = WIN / 32;
+  static constexpr int ROWH = kLfH * EB;                 // activations
+  static constexpr int ROWX = align32(M::IN0) * EB;      // decoder inputs (columns up to the dW tiles)
+  static constexpr int ROWG = 2 * kLfCT * 4;             // dL/dx, FP32
+  static constexpr int NF0 = M::IN0P / kFragK<BF>, NFH = kLfH / kFragK<BF>;
+  static constexpr int GOS = (WIN + 16 / EB) * EB;
+  // Forward: the activations take the inputs' place (two blocks per CU).
+  // Backward: dL/dx stays until the next window's inputs have been gathered,
+  // so it and the records have areas of their own.
+  static constexpr int L_X = 0;
+  static constexpr int L_ACT = BWD ? L_X + WIN * ROWX : L_X;
+  static constexpr int L_GX = L_X + WIN * ROWX + (BWD ? WIN * ROWH : 0);
+  static constexpr int REC = 56;                         // bytes of a record
+  static constexpr int L_REC = L_GX + (BWD ? WIN * ROWG : 0);
+  static constexpr int L_GO = L_REC + (BWD ? 2 : 1) * WIN * REC;
+  static constexpr int L_WO = align16(L_GO + (BWD ? 2 * GOS : 0));
+  static constexpr int L_MAP = L_WO + ((BF && !BWD) ? NFH * 1024 : 0);
+  static constexpr int L_SCR = L_MAP + kThreads * SVLF_MAX_K * 2;
   static constexpr int LDS = L_SCR + 64;
-  static_assert(LDS <= 160 * 1024, "LDS");
-  static_assert(!BWD || WIN * 2 * kLfCT * 4 <= L_MAP - L_GZ, "dL/dz staging fits in GZ + AT");
-  static_assert(M::NBIAS <= kThreads, "one thread per bias entry writes its combined gradient");
+  static_assert(LDS <= (BWD ? 160 : 80) * 1024, "LDS");
+  static_assert(BWD || WIN * ROWH <= WIN * ROWX, "activations fit in the inputs' place");
 };
 
-// Bias gradients of layer l (ROWS real rows of width RW in GZ, one column
-// per hit of the window): thread (row = tid % RW, part = tid / RW) adds its
-// slice of the window's hits to its own register; the parts are combined
-// once per block by bias_combine.
-template <bool BF, int RW, int ROWS, int WIN, int TS, class El>
-__device__ __forceinline__ void bias_part(const El* GZ, int tid, float& acc) {
-  constexpr int HP = WIN / (kThreads / RW);
-  static_assert(kThreads % RW == 0 && (!BF || HP % 8 == 0), "bias-gradient parts");
-  const int row = tid % RW, pt = tid / RW;
-  if (row >= ROWS) return;
-  const El* gr = GZ + row * TS + pt * HP;
-  float sum = 0.0f;
-  if constexpr (BF) {
-#pragma unroll
-    for (int hh = 0; hh < HP; hh += 8) {
-      const s16x8 v = *reinterpret_cast<const s16x8*>(gr + hh);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) sum += bf16_f32(static_cast<uint16_t>(v[j]));
-    }
-  } else {
-#pragma unroll
-    for (int hh = 0; hh < HP; ++hh) sum += gr[hh];
-  }
-  acc += sum;
-}
-
-// Sums every layer's parts (through `lds`, NL * kThreads floats) into the
-// block's partial gradient.  Called by all threads.
-template <class M>
-__device__ __forceinline__ void bias_combine(const float (&acc)[M::NL], float* lds, float* part,
-                                             int tid) {
-  __syncthreads();
-#pragma unroll
-  for (int l = 0; l < M::NL; ++l) lds[l * kThreads + tid] = acc[l];
-  __syncthreads();
-  static_for<M::NL>([&](auto lc) {
-    constexpr int l = decltype(lc)::value;
-    constexpr int RW = M::out_p(l);
-    if (tid < M::out_r(l)) {
-      float sum = 0.0f;
-#pragma unroll
-      for (int pt = 0; pt < kThreads / RW; ++pt) sum += lds[l * kThreads + pt * RW + tid];
-      part[M::par_b(l) + tid] = sum;
-    }
-  });
-}
-
-// Density record (64 B): unclamped cell coordinates of x1 and x2, t_in,
-// t_out and the 8 corner ids.
+// Density record: unclamped cell coordinates of x1 and x2 and the 8 corner
+// ids (the surface point needs them in the forward pass, the scatter in the
+// backward pass).
 struct DRec {
   float u1[3];
   float u2[3];
-  float tin, tout;
-  int4 v0, v1;
+  int v[8];
 };
 
-template <class CF>
-__device__ __forceinline__ typename CF::El* dX() { return reinterpret_cast<typename CF::El*>(g_lds + CF::L_X); }
-
 template <int P, int MODE>
-__global__ __launch_bounds__(kThreads, 1) void k_density(LfArgs a) {
+__global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(LfArgs a) {
   using CF = DCfg<P, MODE>;
   using M = typename CF::M;
-  using El = typename CF::El;
   constexpr bool BF = CF::BF;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
-  DRec* rec = reinterpret_cast<DRec*>(g_lds + CF::L_REC);
-  int* hmap = reinterpret_cast<int*>(g_lds + CF::L_MAP);
+  static_assert(sizeof(DRec) == CF::REC, "record size");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, row = lane & 31;
+  uint16_t* imap = reinterpret_cast<uint16_t*>(g_lds + CF::L_MAP);
   int* scr = reinterpret_cast<int*>(g_lds + CF::L_SCR);
   const auto rs = pack_rsrc(a.packs, static_cast<int>(M::pack_bytes(CF::EB)));
   constexpr int BWD_BASE = M::FWD * CF::EB;
   const float* bias = reinterpret_cast<const float*>(static_cast<const char*>(a.packs) +
                                                      M::pack_bytes(CF::EB) - M::BIAS * 4);
 
-  float* part = a.partT + static_cast<int64_t>(blockIdx.x) * M::NPARAMS;
-  if constexpr (CF::BWD) {
-    for (int i = tid; i < M::NPARAMS; i += kThreads) part[i] = 0.0f;
-    __syncthreads();
+  // this wave's weights
+  frag_t w0[CF::NF0], b0[CF::BWD ? CF::NFH : 1], b1[1];
+  if constexpr (BF) {
+    load_frags(w0, rs, 0, wave, CF::NF0, lane);
+    if constexpr (CF::BWD) {
+      load_frags(b0, rs, BWD_BASE + M::bwd_off(0) * CF::EB, wave, CF::NFH, lane);
+      load_frags(b1, rs, BWD_BASE + M::bwd_off(1) * CF::EB, wave, 32 / kFragK<BF>, lane);
+    } else {
+      for (int e = tid; e < CF::NFH * 64; e += kThreads)
+        *reinterpret_cast<frag_t*>(g_lds + CF::L_WO + e * 16) = __builtin_bit_cast(
+            frag_t, __builtin_amdgcn_raw_buffer_load_b128(rs, e * 16, M::fwd_off(1) * CF::EB, 0));
+    }
   }
-  float dbp[M::NL];
-#pragma unroll
-  for (int l = 0; l < M::NL; ++l) dbp[l] = 0.0f;
+  const f32x16 bias0 = gbias(bias, wave, g);
 
+  // gradients of this wave's rows, over the whole launch
+  constexpr int NX = align32(M::IN0) / 32;
+  f32x16 dw0[NX], dw1 = zero16(), bs0 = zero16();
+#pragma unroll
+  for (int i = 0; i < NX; ++i) dw0[i] = zero16();
+  float bo[2] = {0.0f, 0.0f};
+
+  // The feature-gradient atomics of a window are issued after the next
+  // window's gather, so that its loads do not queue behind them.
+  int rb = 0, pend_tw = 0;
+  float* pend_grad = nullptr;
+  auto records = [&](int b) { return reinterpret_cast<DRec*>(g_lds + CF::L_REC + b * CF::WIN * CF::REC); };
+  auto scatter = [&]() {
+    if constexpr (CF::BWD) {
+      const DRec* rec = records(rb ^ 1);
+      const int n0 = 32 * wave;
+      for (int k = 0; k < 32; ++k) {
+        const int hh = n0 + k;
+        if (wave >= CF::NT || hh >= pend_tw) break;
+        const DRec rc = rec[hh];
+        float w1[8], w2[8];
+        trilinear(clamp01(rc.u1[0]), clamp01(rc.u1[1]), clamp01(rc.u1[2]), w1);
+        trilinear(clamp01(rc.u2[0]), clamp01(rc.u2[1]), clamp01(rc.u2[2]), w2);
+        const float g1 = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, lane >> 2) + (lane & 3) * 4);
+        const float g2 = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, 16 + (lane >> 2)) + (lane & 3) * 4);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          unsafeAtomicAdd(pend_grad + static_cast<int64_t>(rc.v[j]) * kLfCT + lane, w1[j] * g1 + w2[j] * g2);
+      }
+      pend_tw = 0;
+    }
+  };
+
+  __syncthreads();
   ItemDeal deal = item_deal(a, CF::BWD ? 2 : 0);
   for (int item = deal.first(scr); item < deal.nb; item = deal.next(item, scr)) {
     const DevScene& sc = a.tab.s[scene_of(a.tab, item)];
@@ -529,300 +724,228 @@ __global__ __launch_bounds__(kThreads, 1) void k_density(LfArgs a) {
     const float inv_h = __int_as_float((126 + sc.depth) << 23);
     int total;
     const int off = block_excl_scan<kWaves>(count, scr, total, [&](int o) {
-      if constexpr (CF::IMAP)
-        for (int q = 0; q < count; ++q) hmap[o + q] = tid | (q << 16);
+      for (int q = 0; q < count; ++q) imap[o + q] = static_cast<uint16_t>(tid | (q << 8));
     });
     for (int s0 = 0; s0 < total;) {
       bool in_win;
-      const int s1 = CF::IMAP ? open_window_imap<CF::WIN>(s0, total, off, count, hmap, in_win)
-                              : open_window<CF::WIN>(s0, total, off, count, scr, hmap, in_win);
-      const int* wmap = CF::IMAP ? hmap + s0 : hmap;    // the window's map entries
-      const int tw = s1 - s0;
+      const int s1 = open_window<CF::WIN>(s0, total, off, count, imap, in_win);
       (void)in_win;
-      if (BF && CF::BWD && a.xsave != nullptr) {
-        // the forward pass saved this window's decoder inputs: one thread per
-        // hit rebuilds its record, the rows stream back 16 B per thread
-        for (int hh = tid; hh < CF::WIN; hh += kThreads) {
-          if (hh < tw) {
-            const int mp = wmap[hh];
-            const int64_t ray = ir.ray(mp & 0xFFFF);
-            const HitRec hr = a.hits[ray * a.K + (mp >> 16)];
-            const float ox = a.o[3 * ray], oy = a.o[3 * ray + 1], oz = a.o[3 * ray + 2];
-            const float dx = a.d[3 * ray], dy = a.d[3 * ray + 1], dz = a.d[3 * ray + 2];
-            const int4* lc = reinterpret_cast<const int4*>(sc.leaf_corners + 8 * static_cast<int64_t>(hr.leaf));
-            const float lx = -1.0f + static_cast<float>(hr.ijk & 1023u) * h;
-            const float ly = -1.0f + static_cast<float>((hr.ijk >> 10) & 1023u) * h;
-            const float lz = -1.0f + static_cast<float>(hr.ijk >> 20) * h;
-            DRec rc;
-            rc.u1[0] = cell_coord(ox, dx, hr.tin, 0.0f, lx, inv_h);
-            rc.u1[1] = cell_coord(oy, dy, hr.tin, 0.0f, ly, inv_h);
-            rc.u1[2] = cell_coord(oz, dz, hr.tin, 0.0f, lz, inv_h);
-            rc.u2[0] = cell_coord(ox, dx, hr.tout, 0.0f, lx, inv_h);
-            rc.u2[1] = cell_coord(oy, dy, hr.tout, 0.0f, ly, inv_h);
-            rc.u2[2] = cell_coord(oz, dz, hr.tout, 0.0f, lz, inv_h);
-            rc.tin = hr.tin;
-            rc.tout = hr.tout;
-            rc.v0 = lc[0];
-            rc.v1 = lc[1];
-            rec[hh] = rc;
+      const uint16_t* wmap = imap + s0;
+      const int tw = s1 - s0;
+      const int tp = (tw + 63) & ~63;              // rows that the layers touch
+      DRec* rec = records(rb);
+      auto slot_of = [&](int hh) {
+        const int mp = wmap[hh];
+        return ir.ray(mp & 0xFF) * a.K + (mp >> 8);
+      };
+      // records: one thread per hit; r into the input columns
+      const bool saved = BF && CF::BWD && a.xsave != nullptr;
+      if (tid < tp) {
+        float rr[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (tid < tw) {
+          const int mp = wmap[tid];
+          const int64_t ray = ir.ray(mp & 0xFF);
+          const HitRec hr = a.hits[ray * a.K + (mp >> 8)];
+          const float ox = a.o[3 * ray], oy = a.o[3 * ray + 1], oz = a.o[3 * ray + 2];
+          const float dx = a.d[3 * ray], dy = a.d[3 * ray + 1], dz = a.d[3 * ray + 2];
+          const int4* lc = reinterpret_cast<const int4*>(sc.leaf_corners + 8 * static_cast<int64_t>(hr.leaf));
+          const int4 c0 = lc[0], c1 = lc[1];
+          const float lx = -1.0f + static_cast<float>(hr.ijk & 1023u) * h;
+          const float ly = -1.0f + static_cast<float>((hr.ijk >> 10) & 1023u) * h;
+          const float lz = -1.0f + static_cast<float>(hr.ijk >> 20) * h;
+          DRec rc;
+          rc.u1[0] = cell_coord(ox, dx, hr.tin, 0.0f, lx, inv_h);
+          rc.u1[1] = cell_coord(oy, dy, hr.tin, 0.0f, ly, inv_h);
+          rc.u1[2] = cell_coord(oz, dz, hr.tin, 0.0f, lz, inv_h);
+          rc.u2[0] = cell_coord(ox, dx, hr.tout, 0.0f, lx, inv_h);
+          rc.u2[1] = cell_coord(oy, dy, hr.tout, 0.0f, ly, inv_h);
+          rc.u2[2] = cell_coord(oz, dz, hr.tout, 0.0f, lz, inv_h);
+          rc.v[0] = c0.x; rc.v[1] = c0.y; rc.v[2] = c0.z; rc.v[3] = c0.w;
+          rc.v[4] = c1.x; rc.v[5] = c1.y; rc.v[6] = c1.z; rc.v[7] = c1.w;
+          rec[tid] = rc;
+          if (!saved) {
+            const float hc = 0.5f * h;
+            float r6[6];
+            sphere_r(cell_coord(ox, dx, hr.tin, 0.0f, lx + hc, 1.0f),
+                     cell_coord(oy, dy, hr.tin, 0.0f, ly + hc, 1.0f),
+                     cell_coord(oz, dz, hr.tin, 0.0f, lz + hc, 1.0f), dx, dy, dz, h, r6);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) rr[i] = r6[i];
           }
         }
-        constexpr int CPR = M::IN0P * 2 / 16;   // 16-byte chunks per row
-        for (int e = tid; e < CF::WIN * CPR; e += kThreads) {
+        if (!saved) {
+          constexpr int C0 = 2 * kLfCT / kRowVals<BF>;
+          const float zero[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+          *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, tid, C0)) = pack_row<BF>(rr);
+          *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, tid, C0 + 1)) = pack_row<BF>(BF ? zero : rr + 4);
+        }
+      }
+      if (saved) {
+        // the forward pass kept this window's decoder inputs
+        constexpr int CPR = M::IN0P * 2 / 16;      // 16-byte chunks per row
+        for (int e = tid; e < tp * CPR; e += kThreads) {
           const int hh = e / CPR, c = e % CPR;
           uint4 v = make_uint4(0u, 0u, 0u, 0u);
-          if (hh < tw) {
-            const int mp = wmap[hh];
-            const int64_t slot = ir.ray(mp & 0xFFFF) * a.K + (mp >> 16);
-            v = *reinterpret_cast<const uint4*>(a.xsave + slot * M::IN0P + 8 * c);
-          }
-          *reinterpret_cast<uint4*>(dX<CF>() + hh * CF::XS + 8 * c) = v;
+          if (hh < tw) v = *reinterpret_cast<const uint4*>(a.xsave + slot_of(hh) * M::IN0P + 8 * c);
+          *reinterpret_cast<uint4*>(tile_at<CF::ROWX>(CF::L_X, hh, c)) = v;
         }
       } else {
-      // gather: thread q of a hit owns VPT channels of psi(x1) and psi(x2)
-      {
-        constexpr int TPH = kLfCT * CF::EB / 16;
-        constexpr int VPT = 16 / CF::EB;
-        constexpr int HPP = kThreads / TPH;
+        __syncthreads();
+        // thread q of a hit owns VPT channels of psi(x1) and psi(x2)
+        constexpr int VPT = kRowVals<BF>, TPH = kLfCT / VPT, HPP = kThreads / TPH;
         const int q = tid % TPH;
-#pragma unroll 1
-        for (int hh = tid / TPH; hh < CF::WIN; hh += HPP) {
+#pragma unroll 2
+        for (int hh = tid / TPH; hh < tp; hh += HPP) {
           float v1[VPT], v2[VPT];
 #pragma unroll
           for (int i = 0; i < VPT; ++i) v1[i] = v2[i] = 0.0f;
-          float rr[6] = {0, 0, 0, 0, 0, 0};
           if (hh < tw) {
-            const int mp = wmap[hh];
-            const int64_t ray = ir.ray(mp & 0xFFFF);
-            const HitRec hr = a.hits[ray * a.K + (mp >> 16)];
-            const float ox = a.o[3 * ray], oy = a.o[3 * ray + 1], oz = a.o[3 * ray + 2];
-            const float dx = a.d[3 * ray], dy = a.d[3 * ray + 1], dz = a.d[3 * ray + 2];
-            const int4* lc = reinterpret_cast<const int4*>(sc.leaf_corners + 8 * static_cast<int64_t>(hr.leaf));
-            const int4 c0 = lc[0], c1 = lc[1];
-            const float lx = -1.0f + static_cast<float>(hr.ijk & 1023u) * h;
-            const float ly = -1.0f + static_cast<float>((hr.ijk >> 10) & 1023u) * h;
-            const float lz = -1.0f + static_cast<float>(hr.ijk >> 20) * h;
-            const float u1[3] = {cell_coord(ox, dx, hr.tin, 0.0f, lx, inv_h),
-                                 cell_coord(oy, dy, hr.tin, 0.0f, ly, inv_h),
-                                 cell_coord(oz, dz, hr.tin, 0.0f, lz, inv_h)};
-            const float u2[3] = {cell_coord(ox, dx, hr.tout, 0.0f, lx, inv_h),
-                                 cell_coord(oy, dy, hr.tout, 0.0f, ly, inv_h),
-                                 cell_coord(oz, dz, hr.tout, 0.0f, lz, inv_h)};
-            if (q == 0) {
-              DRec rc;
-              rc.u1[0] = u1[0]; rc.u1[1] = u1[1]; rc.u1[2] = u1[2];
-              rc.u2[0] = u2[0]; rc.u2[1] = u2[1]; rc.u2[2] = u2[2];
-              rc.tin = hr.tin;
-              rc.tout = hr.tout;
-              rc.v0 = c0;
-              rc.v1 = c1;
-              rec[hh] = rc;
-              const float hc = 0.5f * h;
-              sphere_r(cell_coord(ox, dx, hr.tin, 0.0f, lx + hc, 1.0f),
-                       cell_coord(oy, dy, hr.tin, 0.0f, ly + hc, 1.0f),
-                       cell_coord(oz, dz, hr.tin, 0.0f, lz + hc, 1.0f), dx, dy, dz, h, rr);
-            }
+            const DRec rc = rec[hh];
+            uint4 raw[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) raw[j] = load_row<BF>(sc, 0, static_cast<int64_t>(rc.v[j]) * kLfCT + VPT * q);
             float w1[8], w2[8];
-            trilinear(clamp01(u1[0]), clamp01(u1[1]), clamp01(u1[2]), w1);
-            trilinear(clamp01(u2[0]), clamp01(u2[1]), clamp01(u2[2]), w2);
-            const int vid[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+            trilinear(clamp01(rc.u1[0]), clamp01(rc.u1[1]), clamp01(rc.u1[2]), w1);
+            trilinear(clamp01(rc.u2[0]), clamp01(rc.u2[1]), clamp01(rc.u2[2]), w2);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-              if constexpr (BF) {
-                const uint4 raw = *reinterpret_cast<const uint4*>(sc.feat16 + static_cast<int64_t>(vid[j]) * kLfCT + 8 * q);
-                const uint32_t w4[4] = {raw.x, raw.y, raw.z, raw.w};
+              float f[VPT];
+              unpack_row<BF>(raw[j], f);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                  const float f0 = bf16_f32(static_cast<uint16_t>(w4[i] & 0xFFFFu));
-                  const float f1 = bf16_f32(static_cast<uint16_t>(w4[i] >> 16));
-                  v1[2 * i] += w1[j] * f0;
-                  v1[2 * i + 1] += w1[j] * f1;
-                  v2[2 * i] += w2[j] * f0;
-                  v2[2 * i + 1] += w2[j] * f1;
-                }
-              } else {
-                const float4 f = *reinterpret_cast<const float4*>(sc.feat32 + static_cast<int64_t>(vid[j]) * kLfCT + 4 * q);
-                v1[0] += w1[j] * f.x; v1[1] += w1[j] * f.y; v1[2] += w1[j] * f.z; v1[3] += w1[j] * f.w;
-                v2[0] += w2[j] * f.x; v2[1] += w2[j] * f.y; v2[2] += w2[j] * f.z; v2[3] += w2[j] * f.w;
+              for (int i = 0; i < VPT; ++i) {
+                v1[i] += w1[j] * f[i];
+                v2[i] += w2[j] * f[i];
               }
             }
           }
-          El* xr = dX<CF>() + hh * CF::XS;
-#pragma unroll
-          for (int i = 0; i < VPT; ++i) {
-            xr[VPT * q + i] = to_el<BF>(v1[i]);
-            xr[kLfCT + VPT * q + i] = to_el<BF>(v2[i]);
-          }
-          if (q == 0) {
-#pragma unroll
-            for (int i = 2 * kLfCT; i < M::IN0P; ++i) xr[i] = to_el<BF>(i < 2 * kLfCT + 6 ? rr[i - 2 * kLfCT] : 0.0f);
-          }
+          *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, hh, q)) = pack_row<BF>(v1);
+          *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, hh, TPH + q)) = pack_row<BF>(v2);
         }
       }
-      }
+      if constexpr (!BF) load_frags(w0, rs, 0, wave, CF::NF0, lane);
       __syncthreads();
+      if (pend_tw > 0) scatter();
       if (BF && !CF::BWD && a.xsave != nullptr) {
-        // save the window's decoder inputs for the backward pass
+        // keep the window's decoder inputs for the backward pass
         constexpr int CPR = M::IN0P * 2 / 16;
         for (int e = tid; e < tw * CPR; e += kThreads) {
           const int hh = e / CPR, c = e % CPR;
-          const int mp = wmap[hh];
-          const int64_t slot = ir.ray(mp & 0xFFFF) * a.K + (mp >> 16);
-          *reinterpret_cast<uint4*>(a.xsave + slot * M::IN0P + 8 * c) =
-              *reinterpret_cast<const uint4*>(dX<CF>() + hh * CF::XS + 8 * c);
+          *reinterpret_cast<uint4*>(a.xsave + slot_of(hh) * M::IN0P + 8 * c) =
+              *reinterpret_cast<const uint4*>(tile_at<CF::ROWX>(CF::L_X, hh, c));
         }
       }
 
-      const int n0 = 32 * wave;
-      const bool has_tile = wave < CF::NTILE && n0 < tw;
-      ActT<BF> act[M::MTH];
-      f32x16 o;
-      if (has_tile) {
-        const int row = n0 + (lane & 31);
-        f32x16 hdn[M::MTH];
-        constexpr int S0 = M::IN0P / M::KS;
+      // hidden layer
+      {
+        auto store = [&](int t, f32x16& acc) {
+          relu16(acc);
+          store_tile<BF, CF::ROWH>(CF::L_ACT, wave, 32 * t + row, g, acc);
+        };
+        if constexpr (CF::BWD) {
+          layer_mma<BF, CF::ROWX, CF::NT>(bias0, w0, CF::L_X, tw, lane, store);
+        } else {
+          f32x16 acc[CF::NT];
+          layer_mma<BF, CF::ROWX, CF::NT>(bias0, w0, CF::L_X, tw, lane, [&](int t, f32x16& v) { acc[t] = v; });
+          __syncthreads();                         // the inputs are overwritten
 #pragma unroll
-        for (int mt = 0; mt < M::MTH; ++mt) hdn[mt] = gbias(bias, mt, g);
-#pragma unroll
-        for (int s = 0; s < S0; ++s) {
-          typename Types<BF>::Op b;
-          if constexpr (BF) b = *reinterpret_cast<const s16x8*>(dX<CF>() + row * CF::XS + 16 * s + 8 * g);
-          else b = dX<CF>()[row * CF::XS + 4 * (2 * (s >> 2) + g) + (s & 3)];
-#pragma unroll
-          for (int mt = 0; mt < M::MTH; ++mt) hdn[mt] = mma(gopb<BF>(rs, 0, mt, s, S0, lane), b, hdn[mt]);
-          chunk_fence<kChunk<BF>>(s);
-        }
-#pragma unroll
-        for (int mt = 0; mt < M::MTH; ++mt) {
-          relu16(hdn[mt]);
-          act[mt].set(hdn[mt]);
-        }
-        constexpr int S1 = kLfH / M::KS;
-        o = gbias(bias + M::bias_off(1), 0, g);
-#pragma unroll
-        for (int s = 0; s < S1; ++s) {
-          o = mma(gopb<BF>(rs, M::fwd_off(1) * CF::EB, 0, s, S1, lane), dop<BF>(hdn, s), o);
-          chunk_fence<kChunk<BF>>(s);
+          for (int t = 0; t < CF::NT; ++t)
+            if (32 * t < tp) store(t, acc[t]);
         }
       }
 
       if constexpr (!CF::BWD) {
-        // per hit: tau, eta, the surface point (section 4.2) -> workspace
-        if (has_tile && g == 0 && n0 + lane < tw) {
-          const int hh = n0 + lane;
-          const DRec rc = rec[hh];
-          const int mp = wmap[hh];
-          const int64_t slot = ir.ray(mp & 0xFFFF) * a.K + (mp >> 16);
-          const float dt = rc.tout - rc.tin;
-          const float ft = a.tau_mode == SVLF_TAU_VOXEL ? dt * inv_h
-                           : a.tau_mode == SVLF_TAU_WORLD ? dt : 1.0f;
-          const float tau = fmaxf(o[0], 0.0f) * ft;
-          const float eta = sigmoidf_(o[1]);
-          LfHit st;
-          st.us[0] = eta * rc.u1[0] + (1.0f - eta) * rc.u2[0];
-          st.us[1] = eta * rc.u1[1] + (1.0f - eta) * rc.u2[1];
-          st.us[2] = eta * rc.u1[2] + (1.0f - eta) * rc.u2[2];
-          st.ts = eta * rc.tin + (1.0f - eta) * rc.tout;
-          st.alpha = -expm1f(-tau);
-          st.e = expf(-tau);
-          st.dtau = o[0] > 0.0f ? ft : 0.0f;
-          st.eta = eta;
-          a.st[slot] = st;
+        __syncthreads();
+        // output layer, split by hits; per hit tau, eta and the surface point
+        // (section 4.2) -> workspace
+        const int n0 = 32 * wave;
+        if (wave < CF::NT && n0 < tw) {
+          f32x16 o = gbias(bias + M::bias_off(1), 0, g);
+#pragma unroll
+          for (int i = 0; i < CF::NFH; ++i) {
+            frag_t wf;
+            if constexpr (BF) wf = *reinterpret_cast<const frag_t*>(g_lds + CF::L_WO + (i * 64 + lane) * 16);
+            else
+              wf = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  rs, lane * 16, M::fwd_off(1) * CF::EB + i * 1024, 0));
+            o = mma_frag<BF>(wf, frag_at<CF::ROWH>(CF::L_ACT, n0 + row, 2 * i + g), o);
+          }
+          if (g == 0 && n0 + lane < tw) {
+            const int hh = n0 + lane;
+            const DRec rc = rec[hh];
+            const int64_t slot = slot_of(hh);
+            const float tin = a.hits[slot].tin, tout = a.hits[slot].tout;
+            const float dt = tout - tin;
+            const float ft = a.tau_mode == SVLF_TAU_VOXEL ? dt * inv_h
+                             : a.tau_mode == SVLF_TAU_WORLD ? dt : 1.0f;
+            const float tau = fmaxf(o[0], 0.0f) * ft;
+            const float eta = sigmoidf_(o[1]);
+            LfHit st;
+            st.us[0] = eta * rc.u1[0] + (1.0f - eta) * rc.u2[0];
+            st.us[1] = eta * rc.u1[1] + (1.0f - eta) * rc.u2[1];
+            st.us[2] = eta * rc.u1[2] + (1.0f - eta) * rc.u2[2];
+            st.ts = eta * tin + (1.0f - eta) * tout;
+            st.alpha = -expm1f(-tau);
+            st.e = expf(-tau);
+            st.dtau = o[0] > 0.0f ? ft : 0.0f;
+            st.eta = eta;
+            a.st[slot] = st;
+          }
         }
       } else {
         // backward of F_T from dL/d(o_0, o_1) left by the colour kernel
-        El* GZ = reinterpret_cast<El*>(g_lds + CF::L_GZ);
-        El* AT = reinterpret_cast<El*>(g_lds + CF::L_AT);
-        f32x16 gz[M::MTH];
-#pragma unroll
-        for (int mt = 0; mt < M::MTH; ++mt) gz[mt] = zero16();
-        if (has_tile && g == 0 && n0 + lane < tw) {
-          const int mp = wmap[n0 + lane];
-          const int64_t slot = ir.ray(mp & 0xFFFF) * a.K + (mp >> 16);
-          const float2 gv = *reinterpret_cast<const float2*>(a.gT + 2 * slot);
-          gz[0][0] = gv.x;
-          gz[0][1] = gv.y;
+        if constexpr (!BF) {
+          load_frags(b1, rs, BWD_BASE + M::bwd_off(1) * CF::EB, wave, 32 / kFragK<BF>, lane);
+          load_frags(b0, rs, BWD_BASE + M::bwd_off(0) * CF::EB, wave, CF::NFH, lane);
         }
-        f32x16 gx[2 * kLfCT / 32];
-        static_for<M::NL>([&](auto lc) {
-          constexpr int l = M::NH - decltype(lc)::value;
-          constexpr int OT = M::out_p(l) / 32;
-          const int col = n0 + (lane & 31);
-          if (wave < CF::NTILE) {
-            if (has_tile) {
-#pragma unroll
-              for (int mt = 0; mt < OT; ++mt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) GZ[(32 * mt + drow(i, g)) * CF::TS + col] = to_el<BF>(gz[mt][i]);
-              if constexpr (l > 0) {
-#pragma unroll
-                for (int mt = 0; mt < M::MTH; ++mt)
-#pragma unroll
-                  for (int i = 0; i < 16; ++i) AT[(32 * mt + drow(i, g)) * CF::TS + col] = act[mt].elem(i);
-              }
-            } else {
-              for (int rr = g; rr < 32 * OT; rr += 2) GZ[rr * CF::TS + col] = to_el<BF>(0.0f);
-              if constexpr (l > 0)
-                for (int rr = g; rr < kLfH; rr += 2) AT[rr * CF::TS + col] = to_el<BF>(0.0f);
-            }
+        using El = typename CF::El;
+        float go0 = 0.0f, go1 = 0.0f;
+        if (tid < tp) {
+          if (tid < tw) {
+            const float2 gv = *reinterpret_cast<const float2*>(a.gT + 2 * slot_of(tid));
+            go0 = gv.x;
+            go1 = gv.y;
           }
-          if constexpr (l == 0)
-            transpose_tile<BF, CF::WIN, CF::XS, CF::TS, M::IN0P, CF::XT_ROWS, kThreads>(dX<CF>(), AT, tid);
-          __syncthreads();
-          dw_window<BF, M, l, CF::WIN, CF::TS>(GZ, AT, part, wave, lane);
-          bias_part<BF, M::out_p(l), M::out_r(l), CF::WIN, CF::TS>(GZ, tid, dbp[l]);
-          if (has_tile) {
-            constexpr int BMT = M::bm(l) / 32;
-            constexpr int S = M::out_p(l) / M::KS;
-            constexpr int BB = BWD_BASE + M::bwd_off(l) * CF::EB;
-            f32x16 rr_[BMT];
-#pragma unroll
-            for (int mt = 0; mt < BMT; ++mt) rr_[mt] = zero16();
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-              const typename Types<BF>::Op bo = dop<BF>(gz, s);
-#pragma unroll
-              for (int mt = 0; mt < BMT; ++mt) rr_[mt] = mma(gopb<BF>(rs, BB, mt, s, S, lane), bo, rr_[mt]);
-              chunk_fence<kChunk<BF>>(s);
-            }
-            if constexpr (l > 0) {
-#pragma unroll
-              for (int mt = 0; mt < M::MTH; ++mt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) gz[mt][i] = act[mt].positive(i) ? rr_[mt][i] : 0.0f;
-            } else {
-#pragma unroll
-              for (int mt = 0; mt < BMT; ++mt) gx[mt] = rr_[mt];
-            }
+          const El e0 = to_el<BF>(go0), e1 = to_el<BF>(go1);
+          *reinterpret_cast<El*>(g_lds + CF::L_GO + tid * CF::EB) = e0;
+          *reinterpret_cast<El*>(g_lds + CF::L_GO + CF::GOS + tid * CF::EB) = e1;
+          if constexpr (BF) {
+            bo[0] += bf16_f32(e0);
+            bo[1] += bf16_f32(e1);
+          } else {
+            bo[0] += e0;
+            bo[1] += e1;
           }
-          __syncthreads();
-        });
-        // scatter dL/dZ_T: dL/dpsi(x1) and dL/dpsi(x2) share the voxel's corners
-        float* gxs = reinterpret_cast<float*>(g_lds + CF::L_GZ);      // [WIN][128]
-        if (has_tile) {
-          const int row = n0 + (lane & 31);
-#pragma unroll
-          for (int mt = 0; mt < 2 * kLfCT / 32; ++mt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) gxs[row * 2 * kLfCT + 32 * mt + drow(i, g)] = gx[mt][i];
         }
         __syncthreads();
-        if (has_tile) {
-          for (int k = 0; k < 32; ++k) {
-            const int hh = n0 + k;
-            if (hh >= tw) break;
-            const DRec rc = rec[hh];
-            float w1[8], w2[8];
-            trilinear(clamp01(rc.u1[0]), clamp01(rc.u1[1]), clamp01(rc.u1[2]), w1);
-            trilinear(clamp01(rc.u2[0]), clamp01(rc.u2[1]), clamp01(rc.u2[2]), w2);
-            const int vid[8] = {rc.v0.x, rc.v0.y, rc.v0.z, rc.v0.w, rc.v1.x, rc.v1.y, rc.v1.z, rc.v1.w};
-            const float g1 = gxs[hh * 2 * kLfCT + lane];
-            const float g2 = gxs[hh * 2 * kLfCT + kLfCT + lane];
+        // output layer: its weight gradient (this wave's features), and dL/dz_0
+        dw_out_mma<BF, CF::ROWH, 2>(dw1, CF::L_ACT, wave, CF::L_GO, CF::GOS, tw, lane);
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-              unsafeAtomicAdd(sc.grad + static_cast<int64_t>(vid[j]) * kLfCT + lane, w1[j] * g1 + w2[j] * g2);
+        for (int t = 0; t < CF::NT; ++t) {
+          if (32 * t < tp) {
+            const int hit = 32 * t + row;
+            frag_t gb = {0, 0, 0, 0};
+            if (g == 0) {
+              const El e0 = *reinterpret_cast<const El*>(g_lds + CF::L_GO + hit * CF::EB);
+              const El e1 = *reinterpret_cast<const El*>(g_lds + CF::L_GO + CF::GOS + hit * CF::EB);
+              if constexpr (BF) gb[0] = static_cast<int>(e0 | (static_cast<uint32_t>(e1) << 16));
+              else {
+                gb[0] = __float_as_int(e0);
+                gb[1] = __float_as_int(e1);
+              }
+            }
+            const f32x16 ga = mma_frag<BF>(b1[0], gb, zero16());
+            mask_store_tile<BF, CF::ROWH>(CF::L_ACT, wave, hit, g, ga, bs0);
           }
         }
+        __syncthreads();
+        // input layer: weight gradient, dL/dx (wave w: input features [32 w, 32 w + 32))
+        dw_mma<BF, CF::ROWH, CF::ROWX>(dw0, CF::L_ACT, wave, CF::L_X, tw, lane);
+        layer_mma<BF, CF::ROWH, CF::NT>(zero16(), b0, CF::L_ACT, tw, lane, [&](int t, f32x16& gx) {
+          store_tile<false, CF::ROWG>(CF::L_GX, wave, 32 * t + row, g, gx);
+        });
+        pend_tw = tw;
+        pend_grad = sc.grad;
+        rb ^= 1;
       }
       __syncthreads();
       s0 = s1;
@@ -830,8 +953,12 @@ __global__ __launch_bounds__(kThreads, 1) void k_density(LfArgs a) {
   }
 
   if constexpr (CF::BWD) {
-    static_assert(M::NL * kThreads * 4 <= kLfH * CF::TS * CF::EB, "bias parts fit in GZ");
-    bias_combine<M>(dbp, reinterpret_cast<float*>(g_lds + CF::L_GZ), part, tid);
+    if (pend_tw > 0) scatter();
+    float* part = a.partT + static_cast<int64_t>(blockIdx.x) * M::NPARAMS;
+    write_dw<BF, M, 0, false>(dw0, part, wave, lane);
+    write_dw_out<BF, M>(dw1, part, wave, lane);
+    write_bias<M, 0>(bs0, part, wave, lane);
+    write_bias_out<M>(bo, reinterpret_cast<float*>(scr), part, wave, lane, tid);
   }
 }
 
@@ -844,63 +971,61 @@ struct CCfg {
   using M = typename Dec<BF, VD>::C;
   using El = typename Types<BF>::Elem;
   static constexpr int EB = Types<BF>::EB;
-  // BF16 backward keeps the activations of hidden layers 1 and 2 in
-  // registers (packed) and those of layer 0 transposed in LDS, staging one
-  // register layer at a time for the weight gradients; this allows 128-hit
-  // windows (all four waves own a tile).  FP32 keeps all three layers
-  // transposed in LDS at 32-hit windows.
-  static constexpr bool ACT_REG = BF;
-  static constexpr int L0_ROW = ACT_REG ? kLfH : 0;     // LDS row of layer 0's activations
-  static constexpr int WIN = BWD ? (BF ? 128 : 32) : (BF ? 128 : 64);
-  static constexpr int NTILE = WIN / 32;
-  static constexpr int XS = M::IN0P + (BF ? 8 : 4);
-  static constexpr int TS = WIN + (BF ? 8 : 1);
-  static constexpr int XT_ROWS = align32(M::IN0);
-  // LDS: records, X, per-hit out (8 floats), then (backward) the hidden
-  // activations [NH][H][TS] (or, with ACT_REG, one staged layer [H][TS] that
-  // also takes X^T), X^T [XT_ROWS][TS] and GZ [H][TS]
-  static constexpr int ACT_ROWS = ACT_REG ? 2 * kLfH : kLfNHC * kLfH;
-  static constexpr int L_REC = 0;
-  static constexpr int L_X = L_REC + WIN * 64;
-  static constexpr int L_OUT = align16(L_X + WIN * XS * EB);
-  static constexpr int L_ACT = align16(L_OUT + WIN * 32);
-  static constexpr int L_XT = align16(L_ACT + (BWD ? ACT_ROWS * TS * EB : 0));
-  static constexpr int L_GZ = align16(L_XT + ((BWD && !ACT_REG) ? XT_ROWS * TS * EB : 0));
-  static constexpr int L_MAP = align16(L_GZ + (BWD ? kLfH * TS * EB : 0));
-  // hit map: all of a work item's hits (IMAP: backward, where it fits) or the window's
-  static constexpr bool IMAP = BWD && align16(L_MAP + kThreads * SVLF_MAX_K * 4) + 64 <= 160 * 1024;
-  static constexpr int L_SCR = align16(L_MAP + (IMAP ? kThreads * SVLF_MAX_K : WIN) * 4);
+  static constexpr int WIN = BF ? 128 : 64;
+  static constexpr int NT = WIN / 32;
+  static constexpr int ROWH = kLfH * EB;
+  static constexpr int ROWX = 64 * EB;                   // decoder inputs (columns up to the dW tiles)
+  static constexpr int ROWG = kLfCC * 4;                 // dL/dx, FP32
+  static constexpr int NF0 = M::IN0P / kFragK<BF>, NFH = kLfH / kFragK<BF>;
+  static constexpr int GOS = (WIN + 16 / EB) * EB;
+  static constexpr int ACT = WIN * ROWH;                 // bytes of one layer's activations
+  // Forward: one layer's activations (each layer takes the previous one's
+  // place; two blocks per CU).  Backward: all three; dL/dx takes the place of
+  // the last layer's, which the next window does not write before the
+  // pending scatter has read it.
+  static constexpr int L_X = 0;
+  static constexpr int L_ACT = L_X + WIN * ROWX;
+  static constexpr int L_GX = L_ACT + 2 * ACT;
+  static constexpr int L_REC = L_ACT + (BWD ? 3 : 1) * ACT;
+  static constexpr int L_DIR = L_REC + (BWD ? 2 : 1) * WIN * 64;
+  static constexpr int L_OUT = L_DIR + (BWD ? WIN * 16 : 0);
+  static constexpr int L_GO = L_OUT + WIN * 32;
+  static constexpr int L_WO = align16(L_GO + (BWD ? 3 * GOS : 0));       // BF16: output layer
+  static constexpr int L_B0 = L_WO + (BF ? NFH * 1024 : 0);              // BF16: transposed input layer
+  static constexpr int L_MAP = L_B0 + ((BF && BWD) ? NFH * 1024 : 0);
+  static constexpr int L_SCR = L_MAP + kThreads * SVLF_MAX_K * 2;
   static constexpr int LDS = L_SCR + 64;
-  static_assert(LDS <= 160 * 1024, "LDS");
-  static_assert(!BWD || WIN * kLfCC * 4 <= kLfH * TS * EB, "dL/dz_C staging fits in GZ");
-  static_assert(XT_ROWS <= kLfH, "X^T fits in the staged-activation area");
+  static_assert(LDS <= (BWD ? 160 : 80) * 1024, "LDS");
+  static_assert(WIN * ROWG <= ACT && align32(M::IN0) * EB <= ROWX, "dL/dx and inputs fit");
 };
 
 // Colour record (64 B): unclamped surface point in cell units, t_in, t_out,
-// eta, the slot's ray index within the item, and the 8 corner ids.
+// eta, the hit slot and the 8 corner ids.
 struct CRec {
   float us[3];
   float tin, tout, eta;
-  int ray_lane;
-  int pad;
-  int4 v0, v1;
+  int64_t slot;
+  int v[8];
 };
+static_assert(sizeof(CRec) == 64, "colour record");
 
-template <class CF>
-__device__ __forceinline__ typename CF::El* cX() { return reinterpret_cast<typename CF::El*>(g_lds + CF::L_X); }
-template <class CF>
-__device__ __forceinline__ typename CF::El* cACT() { return reinterpret_cast<typename CF::El*>(g_lds + CF::L_ACT); }
+__device__ __forceinline__ float quad_xor1(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float quad_xor2(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, true));
+}
 
 template <int P, int MODE, int VD>
-__global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
+__global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(LfArgs a) {
   using CF = CCfg<P, MODE, VD>;
   using M = typename CF::M;
   using El = typename CF::El;
   constexpr bool BF = CF::BF;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
-  CRec* rec = reinterpret_cast<CRec*>(g_lds + CF::L_REC);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, row = lane & 31;
   float* out = reinterpret_cast<float*>(g_lds + CF::L_OUT);
-  int* hmap = reinterpret_cast<int*>(g_lds + CF::L_MAP);
+  float4* dirs = reinterpret_cast<float4*>(g_lds + CF::L_DIR);
+  uint16_t* imap = reinterpret_cast<uint16_t*>(g_lds + CF::L_MAP);
   int* scr = reinterpret_cast<int*>(g_lds + CF::L_SCR);
   using MT_ = typename Dec<BF, VD>::T;
   const char* cpack = static_cast<const char*>(a.packs) + MT_::pack_bytes(CF::EB);
@@ -908,196 +1033,232 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
   constexpr int BWD_BASE = M::FWD * CF::EB;
   const float* bias = reinterpret_cast<const float*>(cpack + M::pack_bytes(CF::EB) - M::BIAS * 4);
 
-  float* part = a.partC + static_cast<int64_t>(blockIdx.x) * M::NPARAMS;
-  if constexpr (CF::BWD) {
-    for (int i = tid; i < M::NPARAMS; i += kThreads) part[i] = 0.0f;
-    __syncthreads();
+  // this wave's weights (BF16: for the whole launch; FP32: loaded per window)
+  constexpr int NFB = CF::BWD ? CF::NFH : 1;
+  frag_t w0[CF::NF0], w1[CF::NFH], w2[CF::NFH], b1[NFB], b2[NFB], b3[1];
+  auto load_w0 = [&]() { load_frags(w0, rs, M::fwd_off(0) * CF::EB, wave, CF::NF0, lane); };
+  auto load_w1 = [&]() { load_frags(w1, rs, M::fwd_off(1) * CF::EB, wave, CF::NFH, lane); };
+  auto load_w2 = [&]() { load_frags(w2, rs, M::fwd_off(2) * CF::EB, wave, CF::NFH, lane); };
+  auto load_b1 = [&]() { load_frags(b1, rs, BWD_BASE + M::bwd_off(1) * CF::EB, wave, CF::NFH, lane); };
+  auto load_b2 = [&]() { load_frags(b2, rs, BWD_BASE + M::bwd_off(2) * CF::EB, wave, CF::NFH, lane); };
+  auto load_b3 = [&]() { load_frags(b3, rs, BWD_BASE + M::bwd_off(3) * CF::EB, wave, 32 / kFragK<BF>, lane); };
+  if constexpr (BF) {
+    load_w0();
+    load_w1();
+    load_w2();
+    if constexpr (CF::BWD) {
+      load_b1();
+      load_b2();
+      load_b3();
+    }
+    for (int e = tid; e < CF::NFH * 64; e += kThreads) {
+      *reinterpret_cast<frag_t*>(g_lds + CF::L_WO + e * 16) = __builtin_bit_cast(
+          frag_t, __builtin_amdgcn_raw_buffer_load_b128(rs, e * 16, M::fwd_off(3) * CF::EB, 0));
+      if constexpr (CF::BWD)
+        *reinterpret_cast<frag_t*>(g_lds + CF::L_B0 + e * 16) = __builtin_bit_cast(
+            frag_t, __builtin_amdgcn_raw_buffer_load_b128(rs, e * 16, BWD_BASE + M::bwd_off(0) * CF::EB, 0));
+    }
   }
-  float dbp[M::NL];
+  // fragment i of a narrow (one M tile) matrix: BF16 from LDS, FP32 from L2
+  auto narrow = [&](int lds, int bytes, int i) -> frag_t {
+    if constexpr (BF) return *reinterpret_cast<const frag_t*>(g_lds + lds + (i * 64 + lane) * 16);
+    else
+      return __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, bytes + i * 1024, 0));
+  };
+
+  f32x16 dw0[2], dw1[4], dw2[4], dw3 = zero16();
+  f32x16 bs0 = zero16(), bs1 = zero16(), bs2 = zero16();
 #pragma unroll
-  for (int l = 0; l < M::NL; ++l) dbp[l] = 0.0f;
+  for (int i = 0; i < 4; ++i) {
+    dw1[i] = dw2[i] = zero16();
+    if (i < 2) dw0[i] = zero16();
+  }
+  float bo[3] = {0.0f, 0.0f, 0.0f};
   float loss_acc = 0.0f;
 
+  int rb = 0, pend_tw = 0;
+  float* pend_grad = nullptr;
+  auto records = [&](int b) { return reinterpret_cast<CRec*>(g_lds + CF::L_REC + b * CF::WIN * 64); };
+  auto scatter = [&]() {
+    if constexpr (CF::BWD) {
+      const CRec* rec = records(rb ^ 1);
+      const int n0 = 32 * wave, c = lane & 31, hs = lane >> 5;
+      if (wave < CF::NT && n0 < pend_tw) {
+        for (int k = 0; k < 32; k += 2) {
+          const int hh = n0 + k + hs;
+          if (hh < pend_tw) {
+            const CRec rc = rec[hh];
+            float w[8];
+            trilinear(clamp01(rc.us[0]), clamp01(rc.us[1]), clamp01(rc.us[2]), w);
+            const float gv = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, c >> 2) + (c & 3) * 4);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              unsafeAtomicAdd(pend_grad + static_cast<int64_t>(rc.v[j]) * kLfCC + c, w[j] * gv);
+          }
+        }
+      }
+      pend_tw = 0;
+    }
+  };
+
+  __syncthreads();
   ItemDeal deal = item_deal(a, 1);
   for (int item = deal.first(scr); item < deal.nb; item = deal.next(item, scr)) {
     const DevScene& sc = a.tab.s[scene_of(a.tab, item)];
     const int64_t zc = sc.n_vertices * kLfCT;       // Z_C follows Z_T
-    const float* featC32 = sc.feat32 + zc;
-    const uint16_t* featC16 = sc.feat16 != nullptr ? sc.feat16 + zc : nullptr;
-    float* gradC = sc.grad != nullptr ? sc.grad + zc : nullptr;
     const ItemRays ir = item_rays(a.tab, sc, item);
     const int64_t r = ir.ray(tid);
     const bool live = tid < ir.n && r < sc.ray_end;
     const int count = live ? a.cnt[r] : 0;
+    // the ray's target (train) or upstream gradient (backward)
+    float tg0 = 0.0f, tg1 = 0.0f, tg2 = 0.0f, tg3 = 0.0f, tg4 = 0.0f;
+    if (MODE == kTrain && live) {
+      tg0 = a.t_rgb[3 * r]; tg1 = a.t_rgb[3 * r + 1]; tg2 = a.t_rgb[3 * r + 2]; tg3 = a.t_depth[r];
+    } else if (MODE == kBackward && live) {
+      tg0 = a.g_rgb[3 * r]; tg1 = a.g_rgb[3 * r + 1]; tg2 = a.g_rgb[3 * r + 2]; tg3 = a.g_depth[r];
+      tg4 = a.g_acc ? a.g_acc[r] : 0.0f;
+    }
     const float h = __int_as_float((128 - sc.depth) << 23);
     const float inv_h = __int_as_float((126 + sc.depth) << 23);
     int total;
     const int off = block_excl_scan<kWaves>(count, scr, total, [&](int o) {
-      if constexpr (CF::IMAP)
-        for (int q = 0; q < count; ++q) hmap[o + q] = tid | (q << 16);
+      for (int q = 0; q < count; ++q) imap[o + q] = static_cast<uint16_t>(tid | (q << 8));
     });
-    float cr = 0.0f, cg = 0.0f, cb = 0.0f, dep = 0.0f, acc = 0.0f;
+    float cr = 0.0f, cg = 0.0f, cb = 0.0f, dep = 0.0f, acc_w = 0.0f;
     for (int s0 = 0; s0 < total;) {
       bool in_win;
-      const int s1 = CF::IMAP ? open_window_imap<CF::WIN>(s0, total, off, count, hmap, in_win)
-                              : open_window<CF::WIN>(s0, total, off, count, scr, hmap, in_win);
-      const int* wmap = CF::IMAP ? hmap + s0 : hmap;    // the window's map entries
+      const int s1 = open_window<CF::WIN>(s0, total, off, count, imap, in_win);
+      const uint16_t* wmap = imap + s0;
       const int tw = s1 - s0;
+      const int tp = (tw + 63) & ~63;              // rows that the layers touch
+      CRec* rec = records(rb);
+      if constexpr (!BF) {
+        load_w0();
+        load_w1();
+      }
+      // records: one thread per hit; r and the direction into the input columns
+      if (tid < tp) {
+        float rr[16] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        if (tid < tw) {
+          const int mp = wmap[tid];
+          const int64_t ray = ir.ray(mp & 0xFF);
+          const int64_t slot = ray * a.K + (mp >> 8);
+          const HitRec hr = a.hits[slot];
+          const LfHit st = a.st[slot];
+          const float ox = a.o[3 * ray], oy = a.o[3 * ray + 1], oz = a.o[3 * ray + 2];
+          const float dx = a.d[3 * ray], dy = a.d[3 * ray + 1], dz = a.d[3 * ray + 2];
+          const int4* lc = reinterpret_cast<const int4*>(sc.leaf_corners + 8 * static_cast<int64_t>(hr.leaf));
+          const int4 c0 = lc[0], c1 = lc[1];
+          CRec rc;
+          rc.us[0] = st.us[0];
+          rc.us[1] = st.us[1];
+          rc.us[2] = st.us[2];
+          rc.tin = hr.tin;
+          rc.tout = hr.tout;
+          rc.eta = st.eta;
+          rc.slot = slot;
+          rc.v[0] = c0.x; rc.v[1] = c0.y; rc.v[2] = c0.z; rc.v[3] = c0.w;
+          rc.v[4] = c1.x; rc.v[5] = c1.y; rc.v[6] = c1.z; rc.v[7] = c1.w;
+          rec[tid] = rc;
+          // per-hit compositing inputs: {e^-tau, dtau/do_0, t_s, alpha}
+          *reinterpret_cast<f32x4*>(out + 8 * tid + 4) = f32x4{st.e, st.dtau, st.ts, st.alpha};
+          if constexpr (CF::BWD) dirs[tid] = make_float4(dx, dy, dz, 0.0f);
+          const float lx = -1.0f + static_cast<float>(hr.ijk & 1023u) * h;
+          const float ly = -1.0f + static_cast<float>((hr.ijk >> 10) & 1023u) * h;
+          const float lz = -1.0f + static_cast<float>(hr.ijk >> 20) * h;
+          const float hc = 0.5f * h;
+          float r6[6];
+          sphere_r(cell_coord(ox, dx, hr.tin, 0.0f, lx + hc, 1.0f),
+                   cell_coord(oy, dy, hr.tin, 0.0f, ly + hc, 1.0f),
+                   cell_coord(oz, dz, hr.tin, 0.0f, lz + hc, 1.0f), dx, dy, dz, h, r6);
+#pragma unroll
+          for (int i = 0; i < 6; ++i) rr[i] = r6[i];
+          if (VD) {
+            rr[6] = dx;
+            rr[7] = dy;
+            rr[8] = dz;
+          }
+        }
+        constexpr int C0 = kLfCC / kRowVals<BF>, NC = (M::IN0P - kLfCC) / kRowVals<BF>;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, tid, C0 + c)) = pack_row<BF>(rr + kRowVals<BF> * c);
+      }
+      __syncthreads();
       {
-        constexpr int TPH = kLfCC * CF::EB / 16;
-        constexpr int VPT = 16 / CF::EB;
-        constexpr int HPP = kThreads / TPH;
+        // thread q of a hit owns VPT channels of psi(x_s)
+        constexpr int VPT = kRowVals<BF>, TPH = kLfCC / VPT, HPP = kThreads / TPH;
         const int q = tid % TPH;
-#pragma unroll 1
-        for (int hh = tid / TPH; hh < CF::WIN; hh += HPP) {
+#pragma unroll 2
+        for (int hh = tid / TPH; hh < tp; hh += HPP) {
           float v[VPT];
 #pragma unroll
           for (int i = 0; i < VPT; ++i) v[i] = 0.0f;
-          float rr[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
           if (hh < tw) {
-            const int mp = wmap[hh];
-            const int64_t ray = ir.ray(mp & 0xFFFF);
-            const int64_t slot = ray * a.K + (mp >> 16);
-            const HitRec hr = a.hits[slot];
-            const LfHit st = a.st[slot];
-            const int4* lc = reinterpret_cast<const int4*>(sc.leaf_corners + 8 * static_cast<int64_t>(hr.leaf));
-            const int4 c0 = lc[0], c1 = lc[1];
-            if (q == 0) {
-              CRec rc;
-              rc.us[0] = st.us[0];
-              rc.us[1] = st.us[1];
-              rc.us[2] = st.us[2];
-              rc.tin = hr.tin;
-              rc.tout = hr.tout;
-              rc.eta = st.eta;
-              rc.ray_lane = mp & 0xFFFF;
-              rc.pad = 0;
-              rc.v0 = c0;
-              rc.v1 = c1;
-              rec[hh] = rc;
-              // per-hit compositing inputs: {e^-tau, dtau/do_0, t_s, alpha}
-              *reinterpret_cast<f32x4*>(out + 8 * hh + 4) = f32x4{st.e, st.dtau, st.ts, st.alpha};
-              const float ox = a.o[3 * ray], oy = a.o[3 * ray + 1], oz = a.o[3 * ray + 2];
-              const float dx = a.d[3 * ray], dy = a.d[3 * ray + 1], dz = a.d[3 * ray + 2];
-              const float lx = -1.0f + static_cast<float>(hr.ijk & 1023u) * h;
-              const float ly = -1.0f + static_cast<float>((hr.ijk >> 10) & 1023u) * h;
-              const float lz = -1.0f + static_cast<float>(hr.ijk >> 20) * h;
-              const float hc = 0.5f * h;
-              float r6[6];
-              sphere_r(cell_coord(ox, dx, hr.tin, 0.0f, lx + hc, 1.0f),
-                       cell_coord(oy, dy, hr.tin, 0.0f, ly + hc, 1.0f),
-                       cell_coord(oz, dz, hr.tin, 0.0f, lz + hc, 1.0f), dx, dy, dz, h, r6);
+            const CRec rc = rec[hh];
+            uint4 raw[8];
 #pragma unroll
-              for (int i = 0; i < 6; ++i) rr[i] = r6[i];
-              rr[6] = dx;
-              rr[7] = dy;
-              rr[8] = dz;
-            }
+            for (int j = 0; j < 8; ++j) raw[j] = load_row<BF>(sc, zc, static_cast<int64_t>(rc.v[j]) * kLfCC + VPT * q);
             float w[8];
-            trilinear(clamp01(st.us[0]), clamp01(st.us[1]), clamp01(st.us[2]), w);
-            const int vid[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+            trilinear(clamp01(rc.us[0]), clamp01(rc.us[1]), clamp01(rc.us[2]), w);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-              if constexpr (BF) {
-                const uint4 raw = *reinterpret_cast<const uint4*>(featC16 + static_cast<int64_t>(vid[j]) * kLfCC + 8 * q);
-                const uint32_t w4[4] = {raw.x, raw.y, raw.z, raw.w};
+              float f[VPT];
+              unpack_row<BF>(raw[j], f);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                  v[2 * i] += w[j] * bf16_f32(static_cast<uint16_t>(w4[i] & 0xFFFFu));
-                  v[2 * i + 1] += w[j] * bf16_f32(static_cast<uint16_t>(w4[i] >> 16));
-                }
-              } else {
-                const float4 f = *reinterpret_cast<const float4*>(featC32 + static_cast<int64_t>(vid[j]) * kLfCC + 4 * q);
-                v[0] += w[j] * f.x; v[1] += w[j] * f.y; v[2] += w[j] * f.z; v[3] += w[j] * f.w;
-              }
+              for (int i = 0; i < VPT; ++i) v[i] += w[j] * f[i];
             }
           }
-          El* xr = cX<CF>() + hh * CF::XS;
-#pragma unroll
-          for (int i = 0; i < VPT; ++i) xr[VPT * q + i] = to_el<BF>(v[i]);
-          if (q == 0) {
-#pragma unroll
-            for (int i = kLfCC; i < M::IN0P; ++i)
-              xr[i] = to_el<BF>(i < kLfCC + 6 + 3 * VD ? rr[i - kLfCC] : 0.0f);
-          }
+          *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, hh, q)) = pack_row<BF>(v);
         }
       }
       __syncthreads();
+      if (pend_tw > 0) scatter();
 
-      // colour decoder: one 32-hit tile per wave
-      const int n0 = 32 * wave;
-      const bool has_tile = wave < CF::NTILE && n0 < tw;
-      const int col = n0 + (lane & 31);
-      ActT<BF> act[CF::ACT_REG && CF::BWD ? M::NH - 1 : 1][M::MTH];   // layers 1 .. NH-1
-      if (has_tile) {
-        const int row = col;
-        f32x16 cur[M::MTH];
-        {
-          constexpr int S0 = M::IN0P / M::KS;
+      // hidden layers
+      static_for<M::NH>([&](auto lc) {
+        constexpr int l = decltype(lc)::value;
+        const f32x16 bt = gbias(bias + M::bias_off(l), wave, g);
+        constexpr int SRC = CF::L_ACT + (CF::BWD && l > 0 ? (l - 1) * CF::ACT : 0);
+        constexpr int DST = CF::L_ACT + (CF::BWD ? l * CF::ACT : 0);
+        if constexpr (!BF && l == 0) load_w2();
+        auto store = [&](int t, f32x16& acc) {
+          relu16(acc);
+          store_tile<BF, CF::ROWH>(DST, wave, 32 * t + row, g, acc);
+        };
+        auto run = [&](auto&& done) {
+          if constexpr (l == 0) layer_mma<BF, CF::ROWX, CF::NT>(bt, w0, CF::L_X, tw, lane, done);
+          else if constexpr (l == 1) layer_mma<BF, CF::ROWH, CF::NT>(bt, w1, SRC, tw, lane, done);
+          else layer_mma<BF, CF::ROWH, CF::NT>(bt, w2, SRC, tw, lane, done);
+        };
+        if constexpr (CF::BWD || l == 0) {
+          run(store);
+        } else {
+          f32x16 acc[CF::NT];
+          run([&](int t, f32x16& v) { acc[t] = v; });
+          __syncthreads();                         // in place
 #pragma unroll
-          for (int mt = 0; mt < M::MTH; ++mt) cur[mt] = gbias(bias, mt, g);
-#pragma unroll
-          for (int s = 0; s < S0; ++s) {
-            typename Types<BF>::Op b;
-            if constexpr (BF) b = *reinterpret_cast<const s16x8*>(cX<CF>() + row * CF::XS + 16 * s + 8 * g);
-            else b = cX<CF>()[row * CF::XS + 4 * (2 * (s >> 2) + g) + (s & 3)];
-#pragma unroll
-            for (int mt = 0; mt < M::MTH; ++mt) cur[mt] = mma(gopb<BF>(rs, 0, mt, s, S0, lane), b, cur[mt]);
-            chunk_fence<kChunk<BF>>(s);
-          }
-#pragma unroll
-          for (int mt = 0; mt < M::MTH; ++mt) relu16(cur[mt]);
-          if constexpr (CF::BWD) {
-#pragma unroll
-            for (int mt = 0; mt < M::MTH; ++mt)
-#pragma unroll
-              for (int i = 0; i < 16; ++i)
-                cACT<CF>()[(CF::L0_ROW + 32 * mt + drow(i, g)) * CF::TS + col] = to_el<BF>(cur[mt][i]);
-          }
+          for (int t = 0; t < CF::NT; ++t)
+            if (32 * t < tp) store(t, acc[t]);
         }
-        static_for<M::NH - 1>([&](auto lc) {
-          constexpr int l = decltype(lc)::value + 1;
-          constexpr int S = kLfH / M::KS;
-          f32x16 nxt[M::MTH];
-#pragma unroll
-          for (int mt = 0; mt < M::MTH; ++mt) nxt[mt] = gbias(bias + M::bias_off(l), mt, g);
-#pragma unroll
-          for (int s = 0; s < S; ++s) {
-            const typename Types<BF>::Op b = dop<BF>(cur, s);
-#pragma unroll
-            for (int mt = 0; mt < M::MTH; ++mt) nxt[mt] = mma(gopb<BF>(rs, M::fwd_off(l) * CF::EB, mt, s, S, lane), b, nxt[mt]);
-            chunk_fence<kChunk<BF>>(s);
-          }
-#pragma unroll
-          for (int mt = 0; mt < M::MTH; ++mt) {
-            relu16(nxt[mt]);
-            cur[mt] = nxt[mt];
-          }
-          if constexpr (CF::BWD && CF::ACT_REG) {
-#pragma unroll
-            for (int mt = 0; mt < M::MTH; ++mt) act[l - 1][mt].set(cur[mt]);
-          } else if constexpr (CF::BWD) {
-#pragma unroll
-            for (int mt = 0; mt < M::MTH; ++mt)
-#pragma unroll
-              for (int i = 0; i < 16; ++i)
-                cACT<CF>()[(l * kLfH + 32 * mt + drow(i, g)) * CF::TS + col] = to_el<BF>(cur[mt][i]);
-          }
-        });
-        constexpr int S = kLfH / M::KS;
+        __syncthreads();
+      });
+      // output layer, split by hits
+      constexpr int L_LAST = CF::L_ACT + (CF::BWD ? 2 * CF::ACT : 0);
+      const int n0 = 32 * wave;
+      const bool has_tile = wave < CF::NT && n0 < tw;
+      if (has_tile) {
         f32x16 o = gbias(bias + M::bias_off(M::NH), 0, g);
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-          o = mma(gopb<BF>(rs, M::fwd_off(M::NH) * CF::EB, 0, s, S, lane), dop<BF>(cur, s), o);
-          chunk_fence<kChunk<BF>>(s);
-        }
-        if (g == 0 && col < tw)
-          *reinterpret_cast<f32x4*>(out + 8 * col) = f32x4{sigmoidf_(o[0]), sigmoidf_(o[1]), sigmoidf_(o[2]), 0.0f};
-      } else if (CF::BWD && wave < CF::NTILE) {
-        // no hits for this tile: its activation columns must not hold stale data
-        constexpr int R0 = CF::ACT_REG ? CF::L0_ROW : 0;
-        constexpr int R1 = CF::ACT_REG ? CF::L0_ROW + kLfH : kLfNHC * kLfH;
-        for (int rr = R0 + g; rr < R1; rr += 2) cACT<CF>()[rr * CF::TS + col] = to_el<BF>(0.0f);
+        for (int i = 0; i < CF::NFH; ++i)
+          o = mma_frag<BF>(narrow(CF::L_WO, M::fwd_off(M::NH) * CF::EB, i),
+                           frag_at<CF::ROWH>(L_LAST, n0 + row, 2 * i + g), o);
+        if (g == 0 && n0 + row < tw)
+          *reinterpret_cast<f32x4*>(out + 8 * (n0 + row)) = f32x4{sigmoidf_(o[0]), sigmoidf_(o[1]), sigmoidf_(o[2]), 0.0f};
+      }
+      if constexpr (!BF && CF::BWD) {
+        load_b3();
+        load_b2();
       }
       __syncthreads();
 
@@ -1114,7 +1275,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
           cg += w * va[1];
           cb += w * va[2];
           dep += w * vb[2];
-          acc += w;
+          acc_w += w;
           if constexpr (CF::BWD) hp[3] = T;
           T *= vb[0];
         }
@@ -1122,30 +1283,23 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
           float gr, gg, gb, gd, ga;
           // the hit holding the target surface point (staged losses)
           int surf = -1;
-          float tgt_r = 0.0f, tgt_g = 0.0f, tgt_b = 0.0f;
-          if (MODE == kTrain) {
-            tgt_r = a.t_rgb[3 * r];
-            tgt_g = a.t_rgb[3 * r + 1];
-            tgt_b = a.t_rgb[3 * r + 2];
-          }
           if (MODE == kTrain && a.loss_kind != kLfLossDefault) {
-            const float ts_ = a.t_depth[r];
             for (int k = 0; k < count; ++k) {
               const CRec& rc = rec[p0 + k];
-              if (rc.tin <= ts_ && ts_ < rc.tout) surf = k;
+              if (rc.tin <= tg3 && tg3 < rc.tout) surf = k;
             }
           }
           if (MODE == kTrain && a.loss_kind == kLfLossSurface) {
             gr = gg = gb = gd = ga = 0.0f;
           } else if (MODE == kTrain && a.loss_kind == kLfLossVolume) {
             const float k2 = 2.0f * a.loss_scale;
-            gr = k2 * (cr - tgt_r);
-            gg = k2 * (cg - tgt_g);
-            gb = k2 * (cb - tgt_b);
+            gr = k2 * (cr - tg0);
+            gg = k2 * (cg - tg1);
+            gb = k2 * (cb - tg2);
             gd = 0.0f;
             ga = 0.0f;
           } else if (MODE == kTrain) {
-            const float er = cr - tgt_r, eg = cg - tgt_g, eb = cb - tgt_b, ed = dep - a.t_depth[r];
+            const float er = cr - tg0, eg = cg - tg1, eb = cb - tg2, ed = dep - tg3;
             const float k2 = a.loss_scale * (2.0f / 3.0f);
             gr = k2 * er;
             gg = k2 * eg;
@@ -1153,11 +1307,11 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
             gd = a.loss_scale * a.lambda_depth * (ed > 0.0f ? 1.0f : (ed < 0.0f ? -1.0f : 0.0f));
             ga = 0.0f;
           } else {
-            gr = a.g_rgb[3 * r];
-            gg = a.g_rgb[3 * r + 1];
-            gb = a.g_rgb[3 * r + 2];
-            gd = a.g_depth[r];
-            ga = a.g_acc ? a.g_acc[r] : 0.0f;
+            gr = tg0;
+            gg = tg1;
+            gb = tg2;
+            gd = tg3;
+            ga = tg4;
           }
           float Sr = 0.0f, Sg = 0.0f, Sb = 0.0f, St = 0.0f, Sa = 0.0f;
           float surf_loss = 0.0f;
@@ -1183,22 +1337,21 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
             if (k == surf) {
               const CRec& rc = rec[p0 + k];
               const float ls2 = 2.0f * a.loss_scale;
-              const float eta_gt = (rc.tout - a.t_depth[r]) / (rc.tout - rc.tin);
+              const float eta_gt = (rc.tout - tg3) / (rc.tout - rc.tin);
               const float e2 = vb[0] * vb[0];
               if (a.loss_kind == kLfLossSurface) {
-                gc0 = ls2 * (c0 - tgt_r);
-                gc1 = ls2 * (c1 - tgt_g);
-                gc2 = ls2 * (c2 - tgt_b);
-                surf_loss += (c0 - tgt_r) * (c0 - tgt_r) + (c1 - tgt_g) * (c1 - tgt_g) +
-                             (c2 - tgt_b) * (c2 - tgt_b);
+                gc0 = ls2 * (c0 - tg0);
+                gc1 = ls2 * (c1 - tg1);
+                gc2 = ls2 * (c2 - tg2);
+                surf_loss += (c0 - tg0) * (c0 - tg0) + (c1 - tg1) * (c1 - tg1) +
+                             (c2 - tg2) * (c2 - tg2);
               }
               geta = ls2 * a.lambda_eta * (rc.eta - eta_gt);
               gt -= ls2 * a.lambda_tau * e2;
               surf_loss += a.lambda_eta * (rc.eta - eta_gt) * (rc.eta - eta_gt) + a.lambda_tau * e2;
             }
-            *reinterpret_cast<f32x4*>(hp) =
-                f32x4{gc0 * c0 * (1.0f - c0), gc1 * c1 * (1.0f - c1), gc2 * c2 * (1.0f - c2),
-                      gt * vb[1]};
+            const float z0 = gc0 * c0 * (1.0f - c0), z1 = gc1 * c1 * (1.0f - c1), z2 = gc2 * c2 * (1.0f - c2);
+            *reinterpret_cast<f32x4*>(hp) = f32x4{z0, z1, z2, gt * vb[1]};
             hp[4] = w * gd;                     // dL/dt_s
             hp[5] = geta;                       // direct dL/deta
           }
@@ -1210,128 +1363,125 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
 
       if constexpr (CF::BWD) {
         __syncthreads();
-        El* GZ = reinterpret_cast<El*>(g_lds + CF::L_GZ);
-        El* XT = reinterpret_cast<El*>(g_lds + CF::L_XT);
-        f32x16 gz[M::MTH];
+        const bool train_color = !a.freeze_color;
+        constexpr int A0 = CF::L_ACT, A1 = CF::L_ACT + CF::ACT, A2 = CF::L_ACT + 2 * CF::ACT;
+        if constexpr (!BF) load_b1();
+        // output layer: dL/do [output][hit] for its weight gradient
+        if (tid < tp) {
+          f32x4 go = {0.0f, 0.0f, 0.0f, 0.0f};
+          if (tid < tw) go = *reinterpret_cast<const f32x4*>(out + 8 * tid);
 #pragma unroll
-        for (int mt = 0; mt < M::MTH; ++mt) gz[mt] = zero16();
-        if (has_tile && g == 0 && col < tw) {
-          const f32x4 go = *reinterpret_cast<const f32x4*>(out + 8 * col);
-          gz[0][0] = go[0];
-          gz[0][1] = go[1];
-          gz[0][2] = go[2];
-        }
-        f32x16 gx[1];
-        static_for<M::NL>([&](auto lc) {
-          constexpr int l = M::NH - decltype(lc)::value;
-          constexpr int OT = M::out_p(l) / 32;
-          if (wave < CF::NTILE) {
-            if (has_tile) {
-#pragma unroll
-              for (int mt = 0; mt < OT; ++mt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) GZ[(32 * mt + drow(i, g)) * CF::TS + col] = to_el<BF>(gz[mt][i]);
-              if constexpr (CF::ACT_REG && l > 1) {
-#pragma unroll
-                for (int mt = 0; mt < M::MTH; ++mt)
-#pragma unroll
-                  for (int i = 0; i < 16; ++i) cACT<CF>()[(32 * mt + drow(i, g)) * CF::TS + col] = act[l - 2][mt].elem(i);
-              }
-            } else {
-              for (int rr = g; rr < 32 * OT; rr += 2) GZ[rr * CF::TS + col] = to_el<BF>(0.0f);
-              if constexpr (CF::ACT_REG && l > 1)
-                for (int rr = g; rr < kLfH; rr += 2) cACT<CF>()[rr * CF::TS + col] = to_el<BF>(0.0f);
-            }
+          for (int c = 0; c < 3; ++c) {
+            const El e = to_el<BF>(go[c]);
+            *reinterpret_cast<El*>(g_lds + CF::L_GO + c * CF::GOS + tid * CF::EB) = e;
+            if constexpr (BF) bo[c] += bf16_f32(e);
+            else bo[c] += e;
           }
-          El* XTs = CF::ACT_REG ? cACT<CF>() : XT;      // X^T (layer 0)
-          if constexpr (l == 0)
-            transpose_tile<BF, CF::WIN, CF::XS, CF::TS, M::IN0P, CF::XT_ROWS, kThreads>(cX<CF>(), XTs, tid);
-          __syncthreads();
-          // layer l's input: X^T (l = 0), layer 0 from LDS, or the staged register layer
-          const El* AT = (l == 0) ? XTs
-                         : CF::ACT_REG ? cACT<CF>() + (l == 1 ? CF::L0_ROW * CF::TS : 0)
-                                       : cACT<CF>() + (l - 1) * kLfH * CF::TS;
-          if (!a.freeze_color) dw_window<BF, M, l, CF::WIN, CF::TS>(GZ, AT, part, wave, lane);
-          if (!a.freeze_color)
-            bias_part<BF, M::out_p(l), M::out_r(l), CF::WIN, CF::TS>(GZ, tid, dbp[l]);
-          if (has_tile) {
-            constexpr int BMT = M::bm(l) / 32;
-            constexpr int S = M::out_p(l) / M::KS;
-            constexpr int BB = BWD_BASE + M::bwd_off(l) * CF::EB;
-            f32x16 rr_[BMT];
-#pragma unroll
-            for (int mt = 0; mt < BMT; ++mt) rr_[mt] = zero16();
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-              const typename Types<BF>::Op bo = dop<BF>(gz, s);
-#pragma unroll
-              for (int mt = 0; mt < BMT; ++mt) rr_[mt] = mma(gopb<BF>(rs, BB, mt, s, S, lane), bo, rr_[mt]);
-              chunk_fence<kChunk<BF>>(s);
-            }
-            if constexpr (l > 1 && CF::ACT_REG) {
-#pragma unroll
-              for (int mt = 0; mt < M::MTH; ++mt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) gz[mt][i] = act[l - 2][mt].positive(i) ? rr_[mt][i] : 0.0f;
-            } else if constexpr (l > 0) {
-              const El* actl = cACT<CF>() + (CF::ACT_REG ? CF::L0_ROW : (l - 1) * kLfH) * CF::TS;
-#pragma unroll
-              for (int mt = 0; mt < M::MTH; ++mt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                  const El av = actl[(32 * mt + drow(i, g)) * CF::TS + col];
-                  bool pos;
-                  if constexpr (BF) pos = static_cast<short>(av) > 0;
-                  else pos = av > 0.0f;
-                  gz[mt][i] = pos ? rr_[mt][i] : 0.0f;
-                }
-            } else {
-              gx[0] = rr_[0];
-            }
-          }
-          __syncthreads();
-        });
-        // scatter dL/dZ_C and carry dL/deta through the interpolation at x_s
-        float* gxs = reinterpret_cast<float*>(g_lds + CF::L_GZ);       // [WIN][C_C]
-        if (has_tile) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) gxs[col * kLfCC + drow(i, g)] = gx[0][i];
         }
         __syncthreads();
-        if (has_tile) {
-          const int c = lane & 31, hs = lane >> 5;
-#pragma unroll 4
-          for (int k = 0; k < 32; k += 2) {
-            const int hh = n0 + k + hs;
-            const bool ok = hh < tw;
-            float proj[8];
-            CRec rc;
-            float wv[8];
-            if (ok) {
-              rc = rec[hh];
-              trilinear(clamp01(rc.us[0]), clamp01(rc.us[1]), clamp01(rc.us[2]), wv);
-              const int vid[8] = {rc.v0.x, rc.v0.y, rc.v0.z, rc.v0.w, rc.v1.x, rc.v1.y, rc.v1.z, rc.v1.w};
-              const float gv = gxs[hh * kLfCC + c];
+        if (train_color) dw_out_mma<BF, CF::ROWH, 3>(dw3, A2, wave, CF::L_GO, CF::GOS, tw, lane);
+        // dL/dz_2 (the output's gradient fills 3 of the K positions, all in lane group 0)
 #pragma unroll
-              for (int j = 0; j < 8; ++j) {
-                const int64_t idx = static_cast<int64_t>(vid[j]) * kLfCC + c;
-                float fv;
-                if constexpr (BF) fv = bf16_f32(featC16[idx]);
-                else fv = featC32[idx];
-                proj[j] = fv * gv;
-                if (!a.freeze_color) unsafeAtomicAdd(gradC + idx, wv[j] * gv);
+        for (int t = 0; t < CF::NT; ++t) {
+          if (32 * t < tp) {
+            const int hit = 32 * t + row;
+            frag_t gb = {0, 0, 0, 0};
+            if (g == 0) {
+              El e[3];
+#pragma unroll
+              for (int c = 0; c < 3; ++c) e[c] = *reinterpret_cast<const El*>(g_lds + CF::L_GO + c * CF::GOS + hit * CF::EB);
+              if constexpr (BF) {
+                gb[0] = static_cast<int>(e[0] | (static_cast<uint32_t>(e[1]) << 16));
+                gb[1] = static_cast<int>(e[2]);
+              } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) gb[c] = __float_as_int(e[c]);
               }
-            } else {
+            }
+            const f32x16 ga = mma_frag<BF>(b3[0], gb, zero16());
+            mask_store_tile<BF, CF::ROWH>(A2, wave, hit, g, ga, bs2);
+          }
+        }
+        __syncthreads();
+        // layers 2 and 1: weight gradient (reads the layer's inputs), then
+        // dL/dz of the layer below, in place of those inputs
+        auto hidden = [&](f32x16 (&dw)[4], const frag_t (&bw)[NFB], int gz, int in, f32x16& bs) {
+          if (train_color) dw_mma<BF, CF::ROWH, CF::ROWH>(dw, gz, wave, in, tw, lane);
+          __syncthreads();
+          layer_mma<BF, CF::ROWH, CF::NT>(zero16(), bw, gz, tw, lane, [&](int t, f32x16& acc) {
+            mask_store_tile<BF, CF::ROWH>(in, wave, 32 * t + row, g, acc, bs);
+          });
+          __syncthreads();
+        };
+        hidden(dw2, b2, A2, A1, bs1);
+        hidden(dw1, b1, A1, A0, bs0);
+        if (train_color) dw_mma<BF, CF::ROWH, CF::ROWX>(dw0, A0, wave, CF::L_X, tw, lane);
+        // dL/dx of the features, split by hits: the wave that makes a hit's
+        // row also uses it below
+        if (has_tile) {
+          f32x16 gx = zero16();
 #pragma unroll
-              for (int j = 0; j < 8; ++j) proj[j] = 0.0f;
+          for (int i = 0; i < CF::NFH; ++i)
+            gx = mma_frag<BF>(narrow(CF::L_B0, BWD_BASE + M::bwd_off(0) * CF::EB, i),
+                              frag_at<CF::ROWH>(A0, n0 + row, 2 * i + g), gx);
+          store_tile<false, CF::ROWG>(CF::L_GX, 0, n0 + row, g, gx);
+          // dL/deta through the interpolation at x_s: per corner, dL/dx . Z_C
+          // summed in a fixed tree over the channels (channels 16, 8, 4, 2 and
+          // 1 apart), in the gather's layout (16 bytes of a row per lane)
+          constexpr int VPT = kRowVals<BF>, TPH = kLfCC / VPT, HPW = 64 / TPH;
+          const int q = lane % TPH, hl = lane / TPH;
+          uint4 raw[8];
+          auto issue = [&](int p, uint4 (&rw)[8]) {
+            const int hh = n0 + p * HPW + hl;
+            if (hh < tw) {
+              const CRec& rc = rec[hh];
+#pragma unroll
+              for (int j = 0; j < 8; ++j) rw[j] = load_row<BF>(sc, zc, static_cast<int64_t>(rc.v[j]) * kLfCC + VPT * q);
+            }
+          };
+          auto project = [&](int p, const uint4 (&rw)[8]) {
+            const int hh = n0 + p * HPW + hl;
+            float proj[8], gv[VPT];
+            const bool ok = hh < tw;
+#pragma unroll
+            for (int i = 0; i < VPT / 4; ++i) {
+              const f32x4 v = __builtin_bit_cast(f32x4, frag_at<CF::ROWG>(CF::L_GX, ok ? hh : n0, (VPT / 4) * q + i));
+#pragma unroll
+              for (int e = 0; e < 4; ++e) gv[4 * i + e] = v[e];
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
+#pragma clang fp contract(off)
+              float f[VPT], s[VPT];
+              unpack_row<BF>(rw[j], f);
 #pragma unroll
-              for (int m = 16; m > 0; m >>= 1) proj[j] += __shfl_xor(proj[j], m, 64);
+              for (int i = 0; i < VPT; ++i) s[i] = ok ? f[i] * gv[i] : 0.0f;
+              if constexpr (BF) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) s[i] = s[i] + quad_xor2(s[i]);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) s[i] = s[i] + quad_xor1(s[i]);
+#pragma unroll
+                for (int m = 4; m > 0; m >>= 1)
+#pragma unroll
+                  for (int i = 0; i < m; ++i) s[i] = s[i] + s[i + m];
+              } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] = s[i] + __shfl_xor(s[i], 4, 64);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] = s[i] + quad_xor2(s[i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] = s[i] + quad_xor1(s[i]);
+#pragma unroll
+                for (int m = 2; m > 0; m >>= 1)
+#pragma unroll
+                  for (int i = 0; i < m; ++i) s[i] = s[i] + s[i + m];
+              }
+              proj[j] = s[0];
             }
-            if (ok && c == 0) {
+            if (ok && q == 0) {
               // dL/du_s from the trilinear weights' derivatives
+              const CRec& rc = rec[hh];
               const float u[3] = {clamp01(rc.us[0]), clamp01(rc.us[1]), clamp01(rc.us[2])};
               float gu[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -1345,8 +1495,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
                   gu[ax] += dwv * proj[j];
                 }
               }
-              const int64_t ray = ir.ray(rc.ray_lane);
-              const float dir[3] = {a.d[3 * ray], a.d[3 * ray + 1], a.d[3 * ray + 2]};
+              const float4 dv = dirs[hh];
+              const float dir[3] = {dv.x, dv.y, dv.z};
               float gx_d = 0.0f;
 #pragma unroll
               for (int ax = 0; ax < 3; ++ax) {
@@ -1355,13 +1505,20 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
               }
               const float* hp = out + 8 * hh;
               const float g_eta = (rc.tin - rc.tout) * (hp[4] + gx_d * inv_h) + hp[5];
-              const int mp = wmap[hh];
-              const int64_t slot = ray * a.K + (mp >> 16);
-              *reinterpret_cast<float2*>(a.gT + 2 * slot) =
-                  make_float2(hp[3], g_eta * rc.eta * (1.0f - rc.eta));
+              *reinterpret_cast<float2*>(a.gT + 2 * rc.slot) = make_float2(hp[3], g_eta * rc.eta * (1.0f - rc.eta));
             }
+          };
+#pragma unroll 1
+          for (int p = 0; p < 32 / HPW; ++p) {
+            issue(p, raw);
+            project(p, raw);
           }
         }
+        if (train_color) {
+          pend_tw = tw;
+          pend_grad = sc.grad + zc;
+        }
+        rb ^= 1;
       }
       __syncthreads();
       s0 = s1;
@@ -1375,24 +1532,39 @@ __global__ __launch_bounds__(kThreads, 1) void k_color(LfArgs a) {
           a.rgb[3 * r + 2] = cb;
         }
         if (a.depth) a.depth[r] = dep;
-        if (a.acc) a.acc[r] = acc;
+        if (a.acc) a.acc[r] = acc_w;
       }
       if (MODE == kTrain && a.loss_kind == kLfLossDefault) {
-        const float er = cr - a.t_rgb[3 * r], eg = cg - a.t_rgb[3 * r + 1],
-                    eb = cb - a.t_rgb[3 * r + 2], ed = dep - a.t_depth[r];
+        const float er = cr - tg0, eg = cg - tg1, eb = cb - tg2, ed = dep - tg3;
         loss_acc += a.loss_scale * ((er * er + eg * eg + eb * eb) * (1.0f / 3.0f) +
                                     a.lambda_depth * fabsf(ed));
       } else if (MODE == kTrain && a.loss_kind == kLfLossVolume) {
-        const float er = cr - a.t_rgb[3 * r], eg = cg - a.t_rgb[3 * r + 1],
-                    eb = cb - a.t_rgb[3 * r + 2];
+        const float er = cr - tg0, eg = cg - tg1, eb = cb - tg2;
         loss_acc += a.loss_scale * (er * er + eg * eg + eb * eb);
       }
     }
   }
 
   if constexpr (CF::BWD) {
-    static_assert(M::NL * kThreads * 4 <= kLfH * CF::TS * CF::EB, "bias parts fit in GZ");
-    bias_combine<M>(dbp, reinterpret_cast<float*>(g_lds + CF::L_GZ), part, tid);
+    if (pend_tw > 0) scatter();
+    float* part = a.partC + static_cast<int64_t>(blockIdx.x) * M::NPARAMS;
+    const float keep = a.freeze_color ? 0.0f : 1.0f;      // frozen: the bias sums are dropped
+#pragma unroll
+    for (int c = 0; c < 3; ++c) bo[c] *= keep;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      bs0[i] *= keep;
+      bs1[i] *= keep;
+      bs2[i] *= keep;
+    }
+    write_dw<BF, M, 0, false>(dw0, part, wave, lane);
+    write_dw<BF, M, 1, true>(dw1, part, wave, lane);
+    write_dw<BF, M, 2, true>(dw2, part, wave, lane);
+    write_dw_out<BF, M>(dw3, part, wave, lane);
+    write_bias<M, 0>(bs0, part, wave, lane);
+    write_bias<M, 1>(bs1, part, wave, lane);
+    write_bias<M, 2>(bs2, part, wave, lane);
+    write_bias_out<M>(bo, reinterpret_cast<float*>(scr), part, wave, lane, tid);
     if (MODE == kTrain) {
       const float tot = block_sum<kWaves>(loss_acc, reinterpret_cast<float*>(scr));
       if (tid == 0) a.ws_loss[blockIdx.x] = tot;
