@@ -34,10 +34,9 @@
 // the layer is split over the block's four waves by OUTPUT features: wave w
 // owns features [32 w, 32 w + 32) of every hidden layer, for all hits of the
 // window.
-//  * BF16: a wave's share of all layers, forward and transposed, is loaded
-//    into registers once per launch (36 to 148 VGPRs / AGPRs) and stays there;
-//  * FP32: a share is 64 VGPRs per layer, read once per 64-hit window (the
-//    next layer's while the current one multiplies);
+//  * the wave's share of a layer is 32 VGPRs in BF16 and 64 in FP32; it stays in
+//    registers for the launch where they suffice (BF16 but the colour
+//    backward) and is read once per window otherwise;
 //  * activations pass through LDS, [hit][feature] in 16-byte chunks that are
 //    MFMA operands as they stand (Tile), written once and read by all waves;
 //  * weight gradients: wave w owns the rows of its features, accumulated in
@@ -345,12 +344,12 @@ __device__ __forceinline__ int here(int x) {
 // (operands with the hits along K).  A 256- or 512-byte row covers all banks,
 // so hit bits 0-1 choose the 64-byte quarter and bits 2-3 the chunk in it;
 // the other widths start neighbouring rows in different banks already and
-// need fewer bits.
+// need fewer bits or none.
 template <int ROWB>
 __device__ __forceinline__ int tile_swz(int hit) {
   if constexpr (ROWB == 256 || ROWB == 512) return ((hit & 3) << 2) | ((hit >> 2) & 3);
   else if constexpr (ROWB == 640) return (hit >> 1) & 7;
-  else if constexpr (ROWB == 320) return (hit >> 2) & 3;
+  else if constexpr (ROWB == 304) return 0;     // 76 words: 16 rows start 4 banks apart each
   else {
     static_assert(ROWB == 128, "tile width");
     return ((hit & 2) << 1) | ((hit >> 2) & 3);
@@ -389,10 +388,9 @@ __device__ __forceinline__ void store_tile(int base, int t, int hit, int g, cons
 }
 
 // dL/dz of a hidden layer's tile from dL/da (v): masked by the activations
-// that the tile holds, stored in their place, and added to the bias
-// gradient's per-lane sums bs (of the values as stored).
+// that the tile holds and stored in their place.
 template <bool BF, int ROWB>
-__device__ __forceinline__ void mask_store_tile(int base, int t, int hit, int g, const f32x16& v, f32x16& bs) {
+__device__ __forceinline__ void mask_store_tile(int base, int t, int hit, int g, const f32x16& v) {
   hit = here(hit);
 #pragma unroll
   for (int q = 0; q < kTileChunks<BF>; ++q) {
@@ -402,18 +400,12 @@ __device__ __forceinline__ void mask_store_tile(int base, int t, int hit, int g,
       float z[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) z[j] = act[j] > 0 ? v[8 * q + j] : 0.0f;
-      const s16x8 r = bf16_rne8(z[0], z[1], z[2], z[3], z[4], z[5], z[6], z[7]);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) bs[8 * q + j] += bf16_f32(static_cast<uint16_t>(r[j]));
-      *at = __builtin_bit_cast(frag_t, r);
+      *at = __builtin_bit_cast(frag_t, bf16_rne8(z[0], z[1], z[2], z[3], z[4], z[5], z[6], z[7]));
     } else {
       const f32x4 act = __builtin_bit_cast(f32x4, *at);
       f32x4 r;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        r[j] = act[j] > 0.0f ? v[4 * q + j] : 0.0f;
-        bs[4 * q + j] += r[j];
-      }
+      for (int j = 0; j < 4; ++j) r[j] = act[j] > 0.0f ? v[4 * q + j] : 0.0f;
       *at = __builtin_bit_cast(frag_t, r);
     }
   }
@@ -479,10 +471,12 @@ __device__ __forceinline__ float hits_operand_fp32(int base, int t, int k, int l
   return *reinterpret_cast<const float*>(tile_at<ROWB>(base, 2 * k + (lane >> 5), 8 * t + (col >> 2)) + (col & 3) * 4);
 }
 
-// dw[nt] += (tile tA of A)^T x (tile nt of B) over the window's hits (hits from
-// tw to the next multiple of 16 are zero in one of the two and finite in the other).
+// dw[nt] += (tile ta of A)^T x (tile nt of B) over the window's hits (hits from
+// tw to the next multiple of 16 are zero in one of the two and finite in the
+// other); bs += the sum of A's row (the bias gradient, half of the hits in
+// each lane group).
 template <bool BF, int ROWA, int ROWB, int NT>
-__device__ __forceinline__ void dw_mma(f32x16 (&dw)[NT], int base_a, int ta, int base_b, int tw, int lane) {
+__device__ __forceinline__ void dw_mma(f32x16 (&dw)[NT], float& bs, int base_a, int ta, int base_b, int tw, int lane) {
   lane = here(lane);
 #pragma unroll 1
   for (int k = 0; k < (tw + 15) >> 4; ++k) {
@@ -490,12 +484,17 @@ __device__ __forceinline__ void dw_mma(f32x16 (&dw)[NT], int base_a, int ta, int
       const s16x8 a = hits_operand_bf16<ROWA>(base_a, ta, k, lane);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) dw[nt] = mma(a, hits_operand_bf16<ROWB>(base_b, nt, k, lane), dw[nt]);
+      float sum = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) sum += bf16_f32(static_cast<uint16_t>(a[j]));
+      bs += sum;
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const float a = hits_operand_fp32<ROWA>(base_a, ta, 8 * k + j, lane);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) dw[nt] = mma(a, hits_operand_fp32<ROWB>(base_b, nt, 8 * k + j, lane), dw[nt]);
+        bs += a;
       }
     }
   }
@@ -548,16 +547,11 @@ __device__ __forceinline__ void write_dw_out(const f32x16& dw, float* __restrict
       part[M::par_w(M::NH) + n * kLfH + 32 * wave + tile_feature<BF>(drow(i, g))] = dw[i];
   }
 }
-// Bias gradient of a hidden layer: sums the 32 lanes (hits) of each group.
-template <class M, int l>
-__device__ __forceinline__ void write_bias(f32x16 bs, float* __restrict__ part, int wave, int lane) {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    float v = bs[i];
-#pragma unroll
-    for (int m = 16; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
-    if ((lane & 31) == 0) part[M::par_b(l) + 32 * wave + drow(i, lane >> 5)] = v;
-  }
+// Bias gradient of a hidden layer, from dw_mma's sums.
+template <bool BF, class M, int l>
+__device__ __forceinline__ void write_bias(float bs, float* __restrict__ part, int wave, int lane) {
+  const float v = bs + __shfl_xor(bs, 32, 64);
+  if (lane < 32) part[M::par_b(l) + 32 * wave + tile_feature<BF>(lane)] = v;
 }
 // Bias gradient of the output layer: per-lane sums of every wave, combined
 // through LDS (kWaves x OUT floats at `lds`) in wave order.  Called by all threads.
@@ -621,7 +615,9 @@ struct DCfg {
   static constexpr int WIN = BF ? 128 : 64;
   static constexpr int NT = WIN / 32;
   static constexpr int ROWH = kLfH * EB;                 // activations
-  static constexpr int ROWX = align32(M::IN0) * EB;      // decoder inputs (columns up to the dW tiles)
+  // decoder inputs; BF16: the last dW tile's columns past the row are the next
+  // row's (finite, and of no gradient entry)
+  static constexpr int ROWX = BF ? M::IN0P * 2 + 16 : align32(M::IN0) * 4;
   static constexpr int ROWG = 2 * kLfCT * 4;             // dL/dx, FP32
   static constexpr int NF0 = M::IN0P / kFragK<BF>, NFH = kLfH / kFragK<BF>;
   static constexpr int GOS = (WIN + 16 / EB) * EB;
@@ -631,7 +627,7 @@ struct DCfg {
   static constexpr int L_X = 0;
   static constexpr int L_ACT = BWD ? L_X + WIN * ROWX : L_X;
   static constexpr int L_GX = L_X + WIN * ROWX + (BWD ? WIN * ROWH : 0);
-  static constexpr int REC = 56;                         // bytes of a record
+  static constexpr int REC = 64;                         // bytes of a record
   static constexpr int L_REC = L_GX + (BWD ? WIN * ROWG : 0);
   static constexpr int L_GO = L_REC + (BWD ? 2 : 1) * WIN * REC;
   static constexpr int L_WO = align16(L_GO + (BWD ? 2 * GOS : 0));
@@ -645,9 +641,10 @@ struct DCfg {
 // Density record: unclamped cell coordinates of x1 and x2 and the 8 corner
 // ids (the surface point needs them in the forward pass, the scatter in the
 // backward pass).
-struct DRec {
+struct __attribute__((aligned(16))) DRec {
   float u1[3];
   float u2[3];
+  float pad[2];
   int v[8];
 };
 
@@ -657,7 +654,8 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
   using M = typename CF::M;
   constexpr bool BF = CF::BF;
   static_assert(sizeof(DRec) == CF::REC, "record size");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, row = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, row = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar offsets and branches
   uint16_t* imap = reinterpret_cast<uint16_t*>(g_lds + CF::L_MAP);
   int* scr = reinterpret_cast<int*>(g_lds + CF::L_SCR);
   const auto rs = pack_rsrc(a.packs, static_cast<int>(M::pack_bytes(CF::EB)));
@@ -682,7 +680,8 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
 
   // gradients of this wave's rows, over the whole launch
   constexpr int NX = align32(M::IN0) / 32;
-  f32x16 dw0[NX], dw1 = zero16(), bs0 = zero16();
+  f32x16 dw0[NX], dw1 = zero16();
+  float bs0 = 0.0f;
 #pragma unroll
   for (int i = 0; i < NX; ++i) dw0[i] = zero16();
   float bo[2] = {0.0f, 0.0f};
@@ -696,9 +695,9 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
     if constexpr (CF::BWD) {
       const DRec* rec = records(rb ^ 1);
       const int n0 = 32 * wave;
-      for (int k = 0; k < 32; ++k) {
-        const int hh = n0 + k;
-        if (wave >= CF::NT || hh >= pend_tw) break;
+      const int n1 = wave >= CF::NT ? n0 : n0 + 32 < pend_tw ? n0 + 32 : pend_tw;
+#pragma unroll 2
+      for (int hh = n0; hh < n1; ++hh) {
         const DRec rc = rec[hh];
         float w1[8], w2[8];
         trilinear(clamp01(rc.u1[0]), clamp01(rc.u1[1]), clamp01(rc.u1[2]), w1);
@@ -740,6 +739,8 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
       };
       // records: one thread per hit; r into the input columns
       const bool saved = BF && CF::BWD && a.xsave != nullptr;
+      float2 go = make_float2(0.0f, 0.0f);         // dL/d(o_0, o_1), left by the colour kernel
+      if (CF::BWD && tid < tw) go = *reinterpret_cast<const float2*>(a.gT + 2 * slot_of(tid));
       if (tid < tp) {
         float rr[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         if (tid < tw) {
@@ -783,11 +784,18 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
       if (saved) {
         // the forward pass kept this window's decoder inputs
         constexpr int CPR = M::IN0P * 2 / 16;      // 16-byte chunks per row
-        for (int e = tid; e < tp * CPR; e += kThreads) {
-          const int hh = e / CPR, c = e % CPR;
-          uint4 v = make_uint4(0u, 0u, 0u, 0u);
-          if (hh < tw) v = *reinterpret_cast<const uint4*>(a.xsave + slot_of(hh) * M::IN0P + 8 * c);
-          *reinterpret_cast<uint4*>(tile_at<CF::ROWX>(CF::L_X, hh, c)) = v;
+        constexpr int N = (CF::WIN * CPR + kThreads - 1) / kThreads;
+        uint4 v[N];                                // all loads in flight at once
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const int e = i * kThreads + tid, hh = e / CPR, c = e % CPR;
+          v[i] = make_uint4(0u, 0u, 0u, 0u);
+          if (hh < tw) v[i] = *reinterpret_cast<const uint4*>(a.xsave + slot_of(hh) * M::IN0P + 8 * c);
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const int e = i * kThreads + tid, hh = e / CPR, c = e % CPR;
+          if (hh < tp) *reinterpret_cast<uint4*>(tile_at<CF::ROWX>(CF::L_X, hh, c)) = v[i];
         }
       } else {
         __syncthreads();
@@ -892,20 +900,14 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
           }
         }
       } else {
-        // backward of F_T from dL/d(o_0, o_1) left by the colour kernel
+        // backward of F_T
         if constexpr (!BF) {
           load_frags(b1, rs, BWD_BASE + M::bwd_off(1) * CF::EB, wave, 32 / kFragK<BF>, lane);
           load_frags(b0, rs, BWD_BASE + M::bwd_off(0) * CF::EB, wave, CF::NFH, lane);
         }
         using El = typename CF::El;
-        float go0 = 0.0f, go1 = 0.0f;
         if (tid < tp) {
-          if (tid < tw) {
-            const float2 gv = *reinterpret_cast<const float2*>(a.gT + 2 * slot_of(tid));
-            go0 = gv.x;
-            go1 = gv.y;
-          }
-          const El e0 = to_el<BF>(go0), e1 = to_el<BF>(go1);
+          const El e0 = to_el<BF>(go.x), e1 = to_el<BF>(go.y);
           *reinterpret_cast<El*>(g_lds + CF::L_GO + tid * CF::EB) = e0;
           *reinterpret_cast<El*>(g_lds + CF::L_GO + CF::GOS + tid * CF::EB) = e1;
           if constexpr (BF) {
@@ -934,12 +936,12 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
               }
             }
             const f32x16 ga = mma_frag<BF>(b1[0], gb, zero16());
-            mask_store_tile<BF, CF::ROWH>(CF::L_ACT, wave, hit, g, ga, bs0);
+            mask_store_tile<BF, CF::ROWH>(CF::L_ACT, wave, hit, g, ga);
           }
         }
         __syncthreads();
         // input layer: weight gradient, dL/dx (wave w: input features [32 w, 32 w + 32))
-        dw_mma<BF, CF::ROWH, CF::ROWX>(dw0, CF::L_ACT, wave, CF::L_X, tw, lane);
+        dw_mma<BF, CF::ROWH, CF::ROWX>(dw0, bs0, CF::L_ACT, wave, CF::L_X, tw, lane);
         layer_mma<BF, CF::ROWH, CF::NT>(zero16(), b0, CF::L_ACT, tw, lane, [&](int t, f32x16& gx) {
           store_tile<false, CF::ROWG>(CF::L_GX, wave, 32 * t + row, g, gx);
         });
@@ -957,7 +959,7 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
     float* part = a.partT + static_cast<int64_t>(blockIdx.x) * M::NPARAMS;
     write_dw<BF, M, 0, false>(dw0, part, wave, lane);
     write_dw_out<BF, M>(dw1, part, wave, lane);
-    write_bias<M, 0>(bs0, part, wave, lane);
+    write_bias<BF, M, 0>(bs0, part, wave, lane);
     write_bias_out<M>(bo, reinterpret_cast<float*>(scr), part, wave, lane, tid);
   }
 }
@@ -1022,7 +1024,8 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
   using M = typename CF::M;
   using El = typename CF::El;
   constexpr bool BF = CF::BF;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, row = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, row = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar offsets and branches
   float* out = reinterpret_cast<float*>(g_lds + CF::L_OUT);
   float4* dirs = reinterpret_cast<float4*>(g_lds + CF::L_DIR);
   uint16_t* imap = reinterpret_cast<uint16_t*>(g_lds + CF::L_MAP);
@@ -1033,7 +1036,11 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
   constexpr int BWD_BASE = M::FWD * CF::EB;
   const float* bias = reinterpret_cast<const float*>(cpack + M::pack_bytes(CF::EB) - M::BIAS * 4);
 
-  // this wave's weights (BF16: for the whole launch; FP32: loaded per window)
+  // This wave's weights.  BF16 forward: kept for the launch (KEEP).  Backward:
+  // the registers hold the weight gradients, so the weights are read once per
+  // window, BF16 all before the pending scatter's atomics (a load issued after
+  // them would wait for them), FP32, whose shares are twice as large and whose
+  // windows are long, a layer ahead.
   constexpr int NFB = CF::BWD ? CF::NFH : 1;
   frag_t w0[CF::NF0], w1[CF::NFH], w2[CF::NFH], b1[NFB], b2[NFB], b3[1];
   auto load_w0 = [&]() { load_frags(w0, rs, M::fwd_off(0) * CF::EB, wave, CF::NF0, lane); };
@@ -1042,15 +1049,13 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
   auto load_b1 = [&]() { load_frags(b1, rs, BWD_BASE + M::bwd_off(1) * CF::EB, wave, CF::NFH, lane); };
   auto load_b2 = [&]() { load_frags(b2, rs, BWD_BASE + M::bwd_off(2) * CF::EB, wave, CF::NFH, lane); };
   auto load_b3 = [&]() { load_frags(b3, rs, BWD_BASE + M::bwd_off(3) * CF::EB, wave, 32 / kFragK<BF>, lane); };
-  if constexpr (BF) {
+  constexpr bool KEEP = BF && !CF::BWD;
+  if constexpr (KEEP) {
     load_w0();
     load_w1();
     load_w2();
-    if constexpr (CF::BWD) {
-      load_b1();
-      load_b2();
-      load_b3();
-    }
+  }
+  if constexpr (BF) {
     for (int e = tid; e < CF::NFH * 64; e += kThreads) {
       *reinterpret_cast<frag_t*>(g_lds + CF::L_WO + e * 16) = __builtin_bit_cast(
           frag_t, __builtin_amdgcn_raw_buffer_load_b128(rs, e * 16, M::fwd_off(3) * CF::EB, 0));
@@ -1067,7 +1072,7 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
   };
 
   f32x16 dw0[2], dw1[4], dw2[4], dw3 = zero16();
-  f32x16 bs0 = zero16(), bs1 = zero16(), bs2 = zero16();
+  float bs0 = 0.0f, bs1 = 0.0f, bs2 = 0.0f;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     dw1[i] = dw2[i] = zero16();
@@ -1132,9 +1137,10 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
       const int tw = s1 - s0;
       const int tp = (tw + 63) & ~63;              // rows that the layers touch
       CRec* rec = records(rb);
-      if constexpr (!BF) {
+      if constexpr (!KEEP) {
         load_w0();
         load_w1();
+        if constexpr (BF) load_w2();
       }
       // records: one thread per hit; r and the direction into the input columns
       if (tid < tp) {
@@ -1211,6 +1217,11 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
           }
           *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, hh, q)) = pack_row<BF>(v);
         }
+      }
+      if constexpr (BF && CF::BWD) {
+        load_b3();
+        load_b2();
+        load_b1();
       }
       __syncthreads();
       if (pend_tw > 0) scatter();
@@ -1363,7 +1374,7 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
 
       if constexpr (CF::BWD) {
         __syncthreads();
-        const bool train_color = !a.freeze_color;
+        const int tw_dw = a.freeze_color ? 0 : tw;    // hits of the colour side's weight gradients
         constexpr int A0 = CF::L_ACT, A1 = CF::L_ACT + CF::ACT, A2 = CF::L_ACT + 2 * CF::ACT;
         if constexpr (!BF) load_b1();
         // output layer: dL/do [output][hit] for its weight gradient
@@ -1374,12 +1385,11 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
           for (int c = 0; c < 3; ++c) {
             const El e = to_el<BF>(go[c]);
             *reinterpret_cast<El*>(g_lds + CF::L_GO + c * CF::GOS + tid * CF::EB) = e;
-            if constexpr (BF) bo[c] += bf16_f32(e);
-            else bo[c] += e;
+            if (!a.freeze_color) bo[c] += BF ? bf16_f32(static_cast<uint16_t>(e)) : static_cast<float>(e);
           }
         }
         __syncthreads();
-        if (train_color) dw_out_mma<BF, CF::ROWH, 3>(dw3, A2, wave, CF::L_GO, CF::GOS, tw, lane);
+        dw_out_mma<BF, CF::ROWH, 3>(dw3, A2, wave, CF::L_GO, CF::GOS, tw_dw, lane);
         // dL/dz_2 (the output's gradient fills 3 of the K positions, all in lane group 0)
 #pragma unroll
         for (int t = 0; t < CF::NT; ++t) {
@@ -1399,23 +1409,23 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
               }
             }
             const f32x16 ga = mma_frag<BF>(b3[0], gb, zero16());
-            mask_store_tile<BF, CF::ROWH>(A2, wave, hit, g, ga, bs2);
+            mask_store_tile<BF, CF::ROWH>(A2, wave, hit, g, ga);
           }
         }
         __syncthreads();
         // layers 2 and 1: weight gradient (reads the layer's inputs), then
         // dL/dz of the layer below, in place of those inputs
-        auto hidden = [&](f32x16 (&dw)[4], const frag_t (&bw)[NFB], int gz, int in, f32x16& bs) {
-          if (train_color) dw_mma<BF, CF::ROWH, CF::ROWH>(dw, gz, wave, in, tw, lane);
+        auto hidden = [&](f32x16 (&dw)[4], float& bs, const frag_t (&bw)[NFB], int gz, int in) {
+          dw_mma<BF, CF::ROWH, CF::ROWH>(dw, bs, gz, wave, in, tw_dw, lane);
           __syncthreads();
           layer_mma<BF, CF::ROWH, CF::NT>(zero16(), bw, gz, tw, lane, [&](int t, f32x16& acc) {
-            mask_store_tile<BF, CF::ROWH>(in, wave, 32 * t + row, g, acc, bs);
+            mask_store_tile<BF, CF::ROWH>(in, wave, 32 * t + row, g, acc);
           });
           __syncthreads();
         };
-        hidden(dw2, b2, A2, A1, bs1);
-        hidden(dw1, b1, A1, A0, bs0);
-        if (train_color) dw_mma<BF, CF::ROWH, CF::ROWX>(dw0, A0, wave, CF::L_X, tw, lane);
+        hidden(dw2, bs2, b2, A2, A1);
+        hidden(dw1, bs1, b1, A1, A0);
+        dw_mma<BF, CF::ROWH, CF::ROWX>(dw0, bs0, A0, wave, CF::L_X, tw_dw, lane);
         // dL/dx of the features, split by hits: the wave that makes a hit's
         // row also uses it below
         if (has_tile) {
@@ -1514,7 +1524,7 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
             project(p, raw);
           }
         }
-        if (train_color) {
+        if (!a.freeze_color) {
           pend_tw = tw;
           pend_grad = sc.grad + zc;
         }
@@ -1548,22 +1558,13 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
   if constexpr (CF::BWD) {
     if (pend_tw > 0) scatter();
     float* part = a.partC + static_cast<int64_t>(blockIdx.x) * M::NPARAMS;
-    const float keep = a.freeze_color ? 0.0f : 1.0f;      // frozen: the bias sums are dropped
-#pragma unroll
-    for (int c = 0; c < 3; ++c) bo[c] *= keep;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      bs0[i] *= keep;
-      bs1[i] *= keep;
-      bs2[i] *= keep;
-    }
     write_dw<BF, M, 0, false>(dw0, part, wave, lane);
     write_dw<BF, M, 1, true>(dw1, part, wave, lane);
     write_dw<BF, M, 2, true>(dw2, part, wave, lane);
     write_dw_out<BF, M>(dw3, part, wave, lane);
-    write_bias<M, 0>(bs0, part, wave, lane);
-    write_bias<M, 1>(bs1, part, wave, lane);
-    write_bias<M, 2>(bs2, part, wave, lane);
+    write_bias<BF, M, 0>(bs0, part, wave, lane);
+    write_bias<BF, M, 1>(bs1, part, wave, lane);
+    write_bias<BF, M, 2>(bs2, part, wave, lane);
     write_bias_out<M>(bo, reinterpret_cast<float*>(scr), part, wave, lane, tid);
     if (MODE == kTrain) {
       const float tot = block_sum<kWaves>(loss_acc, reinterpret_cast<float*>(scr));

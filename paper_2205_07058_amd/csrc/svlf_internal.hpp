@@ -28,6 +28,7 @@ struct DevScene {
   int64_t ray_end;
   int32_t depth;
   int32_t item_begin;     // first work item of this scene (plan_items)
+  int32_t items;          // work items of this scene (plan_items)
   int32_t trace_begin;    // first traversal block of this scene
 };
 
@@ -35,6 +36,7 @@ struct SceneTable {
   DevScene s[SVLF_MAX_SCENES];
   int32_t n;
   int32_t item_rays;      // rays per work item (plan_items)
+  int32_t spread;         // items take rays over the whole scene (plan_items)
   int32_t n_items;        // work items over all scenes (plan_items)
   int32_t n_trace;        // traversal blocks over all scenes
 };
@@ -56,9 +58,12 @@ constexpr int kTraceThreads = 64;    // rays (threads) of a traversal block
 // takes the share of the rays that gives every block the same number of
 // items, in as few rounds as 256-ray items would need: 4,096 rays in 256-ray
 // items keep 16 of 256 blocks busy, and 100,003 rays give 391 items, two
-// rounds with the second half empty.  From kBalancedRounds rounds on, full
-// items are interleaved (below) and the last rounds are handed out on demand,
-// which balances as well.
+// rounds with the second half empty.  Such items are spread over the scene's
+// rays (item j takes rays j, j + items, j + 2 items, ...): consecutive rays hit
+// or miss together, and the launch would wait for the items with the most
+// hits (40,009 rays in 255 items: 2.9 times the mean; spread, within a few
+// percent).  Beyond kBalancedRounds rounds, full items are interleaved (below)
+// and the last rounds are handed out on demand, which balances as well.
 constexpr int kBalancedRounds = 3;
 constexpr int kMinItemRays = 16;
 
@@ -72,10 +77,12 @@ inline void plan_items(SceneTable* tab, int blocks) {
     if (rays < kMinItemRays) rays = kMinItemRays;
   }
   tab->item_rays = static_cast<int32_t>(rays);
+  tab->spread = rounds <= kBalancedRounds ? 1 : 0;
   int64_t items = 0;
   for (int s = 0; s < tab->n; ++s) {
     tab->s[s].item_begin = static_cast<int32_t>(items);
-    items += (tab->s[s].ray_end - tab->s[s].ray_begin + rays - 1) / rays;
+    tab->s[s].items = static_cast<int32_t>((tab->s[s].ray_end - tab->s[s].ray_begin + rays - 1) / rays);
+    items += tab->s[s].items;
   }
   tab->n_items = static_cast<int32_t>(items);
 }
@@ -84,9 +91,10 @@ inline void plan_items(SceneTable* tab, int blocks) {
 // kRaysPerBlock-ray items of a scene are interleaved: item j of such a group
 // takes rays j, j + kIlvItems, j + 2 kIlvItems, ... of the group, so that one
 // item's rays lie far apart in the caller's order while the group, whose
-// items run at about the same time, covers one contiguous range.  Other items
-// take consecutive rays.  Lane t < n of the item handles ray base + t * stride
-// (it may be past the scene's last ray only in a scene's last, partial item).
+// items run at about the same time, covers one contiguous range.  Spread items
+// (plan_items) are interleaved over the whole scene; other items take
+// consecutive rays.  Lane t < n of the item handles ray base + t * stride
+// (which may be past the scene's last ray).
 constexpr int kIlvItems = 256;
 
 struct ItemRays {
@@ -100,6 +108,7 @@ struct ItemRays {
 __device__ __forceinline__ ItemRays item_rays(const SceneTable& tab, const DevScene& sc, int item) {
   const int n = tab.item_rays;
   const int64_t li = item - sc.item_begin, g0 = li / kIlvItems * kIlvItems;
+  if (tab.spread) return {sc.ray_begin + li, sc.items, n};
   if (n == kRaysPerBlock && (g0 + kIlvItems) * kRaysPerBlock <= sc.ray_end - sc.ray_begin)
     return {sc.ray_begin + g0 * kRaysPerBlock + (li - g0), kIlvItems, n};
   return {sc.ray_begin + li * n, 1, n};
