@@ -43,10 +43,10 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of the BF16 train shading kernel on this workload,
 # from rocprofv3 FETCH_SIZE / WRITE_SIZE passes scaled by a 1 GiB device copy
 # (profiles/shade_train_bf16_paper_scale.md).  Valid only for the kernel
-# sources they were taken with (shade.hip and the two headers it includes);
+# sources they were taken with (shade.hip and the three headers it includes);
 # reported as null once any of them changes.
 MEASURED_TRAFFIC = {"shade_src_sha256_prefix": "38c71d7939761e02", "bytes": 2 * 454353 * 1024 + 1424041 * 1024}
-SHADE_SOURCES = ("shade.hip", "mfma_common.hpp", "svlf_internal.hpp")
+SHADE_SOURCES = ("shade.hip", "tiles.hpp", "mfma_common.hpp", "svlf_internal.hpp")
 
 
 def shade_source_prefix():

@@ -50,17 +50,13 @@
 
 #include <type_traits>
 
-#include "mfma_common.hpp"
 #include "svlf_internal.hpp"
+#include "tiles.hpp"
 
 namespace svlf {
 namespace {
 
 using namespace detail;
-
-constexpr int kThreads = 256;
-static_assert(kThreads == kRaysPerBlock, "one ray per thread in a work item");
-constexpr int kWaves = 4;
 
 // ------------------------------------------------------------ decoder geometry
 
@@ -124,47 +120,6 @@ struct Dec {
   using T = Mlp<BF, 2 * kLfCT + 6, kLfH, kLfNHT, 2, 2 * kLfCT>;
   using C = Mlp<BF, kLfCC + 6 + 3 * VD, kLfH, kLfNHC, 3, kLfCC>;
 };
-
-template <bool BF>
-struct Types {
-  using Elem = typename std::conditional<BF, uint16_t, float>::type;
-  using El = Elem;
-  using Op = typename std::conditional<BF, s16x8, float>::type;
-  static constexpr int EB = BF ? 2 : 4;
-};
-
-template <bool BF>
-__device__ __forceinline__ typename Types<BF>::Elem to_el(float v) {
-  if constexpr (BF) return static_cast<uint16_t>(bf16_rne(v));
-  else return v;
-}
-
-// Operands come in fragments of 16 bytes per lane: one K step of the BF16 MFMA
-// or four of the FP32 one.  K index of fragment i, lane group g, element j:
-// kfrag_d for operands made of result tiles (drow), kfrag_x for natural rows.
-typedef int frag_t __attribute__((ext_vector_type(4)));
-template <bool BF>
-constexpr int kFragK = BF ? 16 : 8;
-template <bool BF>
-__device__ __forceinline__ int kfrag_d(int i, int g, int j) {
-  return BF ? 16 * i + 8 * (j >> 2) + 4 * g + (j & 3) : 8 * i + 4 * g + j;
-}
-template <bool BF>
-__device__ __forceinline__ int kfrag_x(int i, int g, int j) {
-  return BF ? 16 * i + 8 * g + j : 8 * i + 4 * g + j;
-}
-
-template <bool BF>
-__device__ __forceinline__ f32x16 mma_frag(frag_t a, frag_t b, f32x16 c) {
-  if constexpr (BF) {
-    return mma(__builtin_bit_cast(s16x8, a), __builtin_bit_cast(s16x8, b), c);
-  } else {
-    const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) c = mma(x[j], y[j], c);
-    return c;
-  }
-}
 
 // Weight fragments are read with buffer loads: the per-fragment offset is a
 // scalar (SGPR) and only the lane offset lives in a VGPR; loads past the end
@@ -244,67 +199,6 @@ __global__ __launch_bounds__(kThreads) void k_lf_pack(const float* __restrict__ 
                                   packs + D::T::pack_bytes(Types<BF>::EB));
 }
 
-// ------------------------------------------------------------ shared LDS
-
-extern __shared__ __attribute__((aligned(16))) char g_lds[];
-
-// Work items of a persistent light-field kernel: dealt round-robin over the
-// grid (the logical block index groups the blocks of one XCD), except the
-// last two rounds, which `counter` hands out in order to whichever block
-// asks first.  Uniform over the block; scr[10] carries the counter's value.
-struct ItemDeal {
-  int G, lb, nb, n_static;
-  int32_t* counter;
-  __device__ int first(int* scr) { return lb < n_static ? lb : tail(scr); }
-  __device__ int next(int item, int* scr) { return item + G < n_static ? item + G : tail(scr); }
-  __device__ int tail(int* scr) {
-    if (n_static == nb) return nb;
-    if (threadIdx.x == 0) scr[10] = n_static + atomicAdd(counter, 1);
-    __syncthreads();
-    const int it = scr[10];
-    __syncthreads();
-    return it;
-  }
-};
-__device__ __forceinline__ ItemDeal item_deal(const LfArgs& a, int which) {
-  ItemDeal d;
-  d.G = gridDim.x;
-  const int b = blockIdx.x;
-  d.lb = (d.G % 8 == 0) ? (b % 8) * (d.G / 8) + b / 8 : b;
-  d.nb = a.tab.n_items;
-  d.counter = a.item_counters != nullptr ? a.item_counters + which : nullptr;
-  const int n_tail = d.counter != nullptr ? (d.nb < 2 * d.G ? d.nb : 2 * d.G) : 0;
-  d.n_static = d.nb - n_tail;
-  return d;
-}
-
-// Hit window [s0, s1): the rays whose hits all fit in [s0, s0 + WIN), from the
-// map of the item's hits (hit -> lane | slot << 8, written once per item): the
-// window ends at the start of the ray that holds hit s0 + WIN (no ray is longer
-// than a window).  No barrier.
-template <int WIN>
-__device__ __forceinline__ int open_window(int s0, int total, int off, int count,
-                                           const uint16_t* imap, bool& in_win) {
-  const int p = s0 + WIN;
-  const int s1 = p < total ? p - (imap[p] >> 8) : total;
-  in_win = count > 0 && off >= s0 && off + count <= s1;
-  return s1;
-}
-
-__device__ __forceinline__ int scene_of(const SceneTable& tab, int item) {
-  int si = 0;
-  while (si + 1 < tab.n && item >= tab.s[si + 1].item_begin) ++si;
-  return si;
-}
-
-__device__ __forceinline__ void trilinear(float ux, float uy, float uz, float (&w)[8]) {
-  const float wx[2] = {1.0f - ux, ux}, wy[2] = {1.0f - uy, uy}, wz[2] = {1.0f - uz, uz};
-#pragma unroll
-  for (int j = 0; j < 8; ++j) w[j] = wx[j & 1] * wy[(j >> 1) & 1] * wz[j >> 2];
-}
-
-__device__ __forceinline__ float clamp01(float x) { return fminf(fmaxf(x, 0.0f), 1.0f); }
-
 // Bounding-sphere parameterisation relative to the voxel centre, from the
 // entry point's offset y1 = x1 - c (small: on the voxel boundary) and the
 // direction d: the sphere |y1 + s d|^2 = R^2 with R^2 = 3 h^2 / 4.
@@ -327,96 +221,7 @@ __device__ __forceinline__ void sphere_r(float y0, float y1, float y2, float dx,
   }
 }
 
-// ------------------------------------------------------------ LDS tiles
-
-// The compiler would hoist every tile address (a register per chunk and tile)
-// out of the window loop; recomputing them where they are used costs a few
-// instructions instead of some two hundred registers.
-__device__ __forceinline__ int here(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
-
-// LDS tile [hit][column], ROWB bytes a row, addressed in 16-byte chunks.  The
-// chunk index is swizzled by the hit so that neither of the two access
-// patterns conflicts: 16 lanes reading the same chunk of 16 hits (operands
-// with the features along K), and the transpose read's 4 hits x 64 bytes
-// (operands with the hits along K).  A 256- or 512-byte row covers all banks,
-// so hit bits 0-1 choose the 64-byte quarter and bits 2-3 the chunk in it;
-// the other widths start neighbouring rows in different banks already and
-// need fewer bits or none.
-template <int ROWB>
-__device__ __forceinline__ int tile_swz(int hit) {
-  if constexpr (ROWB == 256 || ROWB == 512) return ((hit & 3) << 2) | ((hit >> 2) & 3);
-  else if constexpr (ROWB == 640) return (hit >> 1) & 7;
-  else if constexpr (ROWB == 304) return 0;     // 76 words: 16 rows start 4 banks apart each
-  else {
-    static_assert(ROWB == 128, "tile width");
-    return ((hit & 2) << 1) | ((hit >> 2) & 3);
-  }
-}
-template <int ROWB>
-__device__ __forceinline__ char* tile_at(int base, int hit, int chunk) {
-  return g_lds + base + hit * ROWB + ((chunk ^ tile_swz<ROWB>(hit)) << 4);
-}
-template <int ROWB>
-__device__ __forceinline__ frag_t frag_at(int base, int hit, int chunk) {
-  return *reinterpret_cast<const frag_t*>(tile_at<ROWB>(base, hit, chunk));
-}
-
-// Chunks of a 32-feature result tile: chunk q of tile t holds result registers
-// [16 / NCH q, 16 / NCH (q + 1)) of one lane, at chunk 2 (NCH t + q) + g of its
-// hit's row, which makes it fragment NCH t + q of the next layer's operand.
-template <bool BF>
-constexpr int kTileChunks = BF ? 2 : 4;
-
-template <bool BF>
-__device__ __forceinline__ frag_t pack_chunk(const f32x16& v, int q) {
-  if constexpr (BF)
-    return __builtin_bit_cast(frag_t, bf16_rne8(v[8 * q], v[8 * q + 1], v[8 * q + 2], v[8 * q + 3],
-                                                v[8 * q + 4], v[8 * q + 5], v[8 * q + 6], v[8 * q + 7]));
-  else
-    return __builtin_bit_cast(frag_t, f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]});
-}
-
-template <bool BF, int ROWB>
-__device__ __forceinline__ void store_tile(int base, int t, int hit, int g, const f32x16& v) {
-  hit = here(hit);
-#pragma unroll
-  for (int q = 0; q < kTileChunks<BF>; ++q)
-    *reinterpret_cast<frag_t*>(tile_at<ROWB>(base, hit, 2 * (kTileChunks<BF> * t + q) + g)) = pack_chunk<BF>(v, q);
-}
-
-// dL/dz of a hidden layer's tile from dL/da (v): masked by the activations
-// that the tile holds and stored in their place.
-template <bool BF, int ROWB>
-__device__ __forceinline__ void mask_store_tile(int base, int t, int hit, int g, const f32x16& v) {
-  hit = here(hit);
-#pragma unroll
-  for (int q = 0; q < kTileChunks<BF>; ++q) {
-    frag_t* at = reinterpret_cast<frag_t*>(tile_at<ROWB>(base, hit, 2 * (kTileChunks<BF> * t + q) + g));
-    if constexpr (BF) {
-      const s16x8 act = __builtin_bit_cast(s16x8, *at);
-      float z[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) z[j] = act[j] > 0 ? v[8 * q + j] : 0.0f;
-      *at = __builtin_bit_cast(frag_t, bf16_rne8(z[0], z[1], z[2], z[3], z[4], z[5], z[6], z[7]));
-    } else {
-      const f32x4 act = __builtin_bit_cast(f32x4, *at);
-      f32x4 r;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) r[j] = act[j] > 0.0f ? v[4 * q + j] : 0.0f;
-      *at = __builtin_bit_cast(frag_t, r);
-    }
-  }
-}
-
-// Feature (within its 32-tile) at column position p of a tile row: BF16 chunks
-// hold result registers in pairs of row quads (drow).
-template <bool BF>
-__device__ __forceinline__ int tile_feature(int p) {
-  return BF ? (p & 16) | ((p & 4) << 1) | ((p & 8) >> 1) | (p & 3) : p;
-}
+// ------------------------------------------------------------ layers
 
 // One layer's share of this wave (fragments w) over the window's hits, 64 hits
 // (two independent accumulators) at a time: done(t, acc) gets each 32-hit
@@ -441,34 +246,6 @@ __device__ __forceinline__ void layer_mma(const f32x16& init, const frag_t (&w)[
       done(2 * p + 1, acc[1]);
     }
   });
-}
-
-// Operand with the hits along K: row / column p = lane & 31 of tile t, K = hits.
-// BF16: step k covers hits [16 k, 16 k + 16).  The transpose read gives lane i
-// of a 16-lane group column i of the 4 x 16 block whose row r lanes 4 r .. 4 r + 3
-// address, 4 columns each; two reads make the lane's 8 hits 16 k + 8 g + j.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-template <int ROWB>
-__device__ __forceinline__ s16x8 hits_operand_bf16(int base, int t, int k, int lane) {
-  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  const int i = lane & 15, g = lane >> 5;
-  const int col = (lane & 16) + 4 * (i & 3);
-  s16x8 r;
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int hit = 16 * k + 8 * g + 4 * half + (i >> 2);
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_s16x4*)(tile_at<ROWB>(base, hit, 4 * t + (col >> 3)) + (col & 7) * 2));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) r[4 * half + j] = v[j];
-  }
-  return r;
-}
-// FP32: step k covers hits 2 k and 2 k + 1.
-template <int ROWB>
-__device__ __forceinline__ float hits_operand_fp32(int base, int t, int k, int lane) {
-  const int col = lane & 31;
-  return *reinterpret_cast<const float*>(tile_at<ROWB>(base, 2 * k + (lane >> 5), 8 * t + (col >> 2)) + (col & 3) * 4);
 }
 
 // dw[nt] += (tile ta of A)^T x (tile nt of B) over the window's hits (hits from
@@ -576,33 +353,6 @@ __device__ __forceinline__ void write_bias_out(const float (&bo)[M::OUT], float*
   __syncthreads();
 }
 
-// 16 bytes of a feature row as floats, and 16 bytes of a tile row from floats.
-template <bool BF>
-constexpr int kRowVals = BF ? 8 : 4;
-template <bool BF>
-__device__ __forceinline__ void unpack_row(uint4 raw, float (&f)[kRowVals<BF>]) {
-  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if constexpr (BF) {
-      f[2 * i] = bf16_f32(static_cast<uint16_t>(w[i] & 0xFFFFu));
-      f[2 * i + 1] = bf16_f32(static_cast<uint16_t>(w[i] >> 16));
-    } else {
-      f[i] = __uint_as_float(w[i]);
-    }
-  }
-}
-template <bool BF>
-__device__ __forceinline__ frag_t pack_row(const float* f) {
-  if constexpr (BF) return __builtin_bit_cast(frag_t, bf16_rne8(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7]));
-  else return __builtin_bit_cast(frag_t, f32x4{f[0], f[1], f[2], f[3]});
-}
-template <bool BF>
-__device__ __forceinline__ uint4 load_row(const DevScene& sc, int64_t block, int64_t elem) {
-  if constexpr (BF) return *reinterpret_cast<const uint4*>(sc.feat16 + block + elem);
-  else return *reinterpret_cast<const uint4*>(sc.feat32 + block + elem);
-}
-
 // ------------------------------------------------------------ density kernel
 
 template <int P, int MODE>
@@ -644,7 +394,8 @@ struct DCfg {
 struct __attribute__((aligned(16))) DRec {
   float u1[3];
   float u2[3];
-  float pad[2];
+  uint32_t share;         // corners that the ray's next hit has as well
+  uint32_t pad;
   int v[8];
 };
 
@@ -687,16 +438,17 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
   float bo[2] = {0.0f, 0.0f};
 
   // The feature-gradient atomics of a window are issued after the next
-  // window's gather, so that its loads do not queue behind them.
+  // window's gather, so that its loads do not queue behind them.  A wave takes
+  // HW consecutive hits, one at a time (lane = channel).
+  constexpr int HW = CF::WIN / kWaves;
   int rb = 0, pend_tw = 0;
   float* pend_grad = nullptr;
   auto records = [&](int b) { return reinterpret_cast<DRec*>(g_lds + CF::L_REC + b * CF::WIN * CF::REC); };
   auto scatter = [&]() {
     if constexpr (CF::BWD) {
       const DRec* rec = records(rb ^ 1);
-      const int n0 = 32 * wave;
-      const int n1 = wave >= CF::NT ? n0 : n0 + 32 < pend_tw ? n0 + 32 : pend_tw;
-#pragma unroll 2
+      const int n0 = HW * wave, n1 = n0 + HW < pend_tw ? n0 + HW : pend_tw;
+      CornerCarry carry;
       for (int hh = n0; hh < n1; ++hh) {
         const DRec rc = rec[hh];
         float w1[8], w2[8];
@@ -705,15 +457,17 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
         const float g1 = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, lane >> 2) + (lane & 3) * 4);
         const float g2 = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, 16 + (lane >> 2)) + (lane & 3) * 4);
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          unsafeAtomicAdd(pend_grad + static_cast<int64_t>(rc.v[j]) * kLfCT + lane, w1[j] * g1 + w2[j] * g2);
+        for (int j = 0; j < 8; ++j) carry.v[j] += w1[j] * g1 + w2[j] * g2;
+        carry.flush(__builtin_amdgcn_readfirstlane(rc.share), [&](int j, float x) {
+          unsafeAtomicAdd(pend_grad + static_cast<int64_t>(rc.v[j]) * kLfCT + lane, x);
+        });
       }
       pend_tw = 0;
     }
   };
 
   __syncthreads();
-  ItemDeal deal = item_deal(a, CF::BWD ? 2 : 0);
+  ItemDeal deal(a.tab, a.item_counters + (CF::BWD ? 2 : 0));
   for (int item = deal.first(scr); item < deal.nb; item = deal.next(item, scr)) {
     const DevScene& sc = a.tab.s[scene_of(a.tab, item)];
     const ItemRays ir = item_rays(a.tab, sc, item);
@@ -743,8 +497,10 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
       if (CF::BWD && tid < tw) go = *reinterpret_cast<const float2*>(a.gT + 2 * slot_of(tid));
       if (tid < tp) {
         float rr[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        int mp = -1;
+        uint32_t ijk = 0;
         if (tid < tw) {
-          const int mp = wmap[tid];
+          mp = wmap[tid];
           const int64_t ray = ir.ray(mp & 0xFF);
           const HitRec hr = a.hits[ray * a.K + (mp >> 8)];
           const float ox = a.o[3 * ray], oy = a.o[3 * ray + 1], oz = a.o[3 * ray + 2];
@@ -764,6 +520,7 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
           rc.v[0] = c0.x; rc.v[1] = c0.y; rc.v[2] = c0.z; rc.v[3] = c0.w;
           rc.v[4] = c1.x; rc.v[5] = c1.y; rc.v[6] = c1.z; rc.v[7] = c1.w;
           rec[tid] = rc;
+          ijk = hr.ijk;
           if (!saved) {
             const float hc = 0.5f * h;
             float r6[6];
@@ -773,6 +530,10 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_density(
 #pragma unroll
             for (int i = 0; i < 6; ++i) rr[i] = r6[i];
           }
+        }
+        if constexpr (CF::BWD) {
+          const uint32_t sh = shared_corners(mp, ijk);
+          if (tid < tw) rec[tid].share = (tid & (HW - 1)) == HW - 1 ? 0u : sh;
         }
         if (!saved) {
           constexpr int C0 = 2 * kLfCT / kRowVals<BF>;
@@ -1002,7 +763,8 @@ struct CCfg {
 };
 
 // Colour record (64 B): unclamped surface point in cell units, t_in, t_out,
-// eta, the hit slot and the 8 corner ids.
+// eta, the hit slot (top byte: corners that the ray's next hit has as well)
+// and the 8 corner ids.
 struct CRec {
   float us[3];
   float tin, tout, eta;
@@ -1083,23 +845,25 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
 
   int rb = 0, pend_tw = 0;
   float* pend_grad = nullptr;
+  // scatter: hits per wave, per lane group of C_C channels
+  constexpr int HW = CF::WIN / kWaves, GH = HW / 2;
   auto records = [&](int b) { return reinterpret_cast<CRec*>(g_lds + CF::L_REC + b * CF::WIN * 64); };
   auto scatter = [&]() {
     if constexpr (CF::BWD) {
       const CRec* rec = records(rb ^ 1);
-      const int n0 = 32 * wave, c = lane & 31, hs = lane >> 5;
-      if (wave < CF::NT && n0 < pend_tw) {
-        for (int k = 0; k < 32; k += 2) {
-          const int hh = n0 + k + hs;
-          if (hh < pend_tw) {
-            const CRec rc = rec[hh];
-            float w[8];
-            trilinear(clamp01(rc.us[0]), clamp01(rc.us[1]), clamp01(rc.us[2]), w);
-            const float gv = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, c >> 2) + (c & 3) * 4);
+      const int c = lane & 31, h0 = HW * wave + GH * (lane >> 5);
+      CornerCarry carry;
+      for (int hh = h0; hh < h0 + GH; ++hh) {
+        if (hh < pend_tw) {
+          const CRec rc = rec[hh];
+          float w[8];
+          trilinear(clamp01(rc.us[0]), clamp01(rc.us[1]), clamp01(rc.us[2]), w);
+          const float gv = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, c >> 2) + (c & 3) * 4);
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-              unsafeAtomicAdd(pend_grad + static_cast<int64_t>(rc.v[j]) * kLfCC + c, w[j] * gv);
-          }
+          for (int j = 0; j < 8; ++j) carry.v[j] += w[j] * gv;
+          carry.flush(static_cast<uint32_t>(rc.slot >> 56) & 0xFFu, [&](int j, float x) {
+            unsafeAtomicAdd(pend_grad + static_cast<int64_t>(rc.v[j]) * kLfCC + c, x);
+          });
         }
       }
       pend_tw = 0;
@@ -1107,7 +871,7 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
   };
 
   __syncthreads();
-  ItemDeal deal = item_deal(a, 1);
+  ItemDeal deal(a.tab, a.item_counters + 1);
   for (int item = deal.first(scr); item < deal.nb; item = deal.next(item, scr)) {
     const DevScene& sc = a.tab.s[scene_of(a.tab, item)];
     const int64_t zc = sc.n_vertices * kLfCT;       // Z_C follows Z_T
@@ -1145,8 +909,10 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
       // records: one thread per hit; r and the direction into the input columns
       if (tid < tp) {
         float rr[16] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        int mp = -1;
+        uint32_t ijk = 0;
         if (tid < tw) {
-          const int mp = wmap[tid];
+          mp = wmap[tid];
           const int64_t ray = ir.ray(mp & 0xFF);
           const int64_t slot = ray * a.K + (mp >> 8);
           const HitRec hr = a.hits[slot];
@@ -1166,6 +932,7 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
           rc.v[0] = c0.x; rc.v[1] = c0.y; rc.v[2] = c0.z; rc.v[3] = c0.w;
           rc.v[4] = c1.x; rc.v[5] = c1.y; rc.v[6] = c1.z; rc.v[7] = c1.w;
           rec[tid] = rc;
+          ijk = hr.ijk;
           // per-hit compositing inputs: {e^-tau, dtau/do_0, t_s, alpha}
           *reinterpret_cast<f32x4*>(out + 8 * tid + 4) = f32x4{st.e, st.dtau, st.ts, st.alpha};
           if constexpr (CF::BWD) dirs[tid] = make_float4(dx, dy, dz, 0.0f);
@@ -1184,6 +951,10 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
             rr[7] = dy;
             rr[8] = dz;
           }
+        }
+        if constexpr (CF::BWD) {
+          const uint32_t sh = shared_corners(mp, ijk);
+          if (tid < tw && (tid & (GH - 1)) != GH - 1) rec[tid].slot |= static_cast<int64_t>(sh) << 56;
         }
         constexpr int C0 = kLfCC / kRowVals<BF>, NC = (M::IN0P - kLfCC) / kRowVals<BF>;
 #pragma unroll
@@ -1515,7 +1286,8 @@ __global__ __launch_bounds__(kThreads, MODE == kForward ? 2 : 1) void k_color(Lf
               }
               const float* hp = out + 8 * hh;
               const float g_eta = (rc.tin - rc.tout) * (hp[4] + gx_d * inv_h) + hp[5];
-              *reinterpret_cast<float2*>(a.gT + 2 * rc.slot) = make_float2(hp[3], g_eta * rc.eta * (1.0f - rc.eta));
+              const int64_t slot = rc.slot & ((int64_t(1) << 56) - 1);
+              *reinterpret_cast<float2*>(a.gT + 2 * slot) = make_float2(hp[3], g_eta * rc.eta * (1.0f - rc.eta));
             }
           };
 #pragma unroll 1
@@ -1593,7 +1365,7 @@ int lf_num_cus() {
 // and LDS), at most `cap` (the backward kernels' partial sums are sized for
 // lf_grid_limit() blocks).
 template <class K>
-hipError_t launch_persistent(K kern, int lds, LfArgs a, hipStream_t s, int* grid_out, int cap) {
+hipError_t launch_persistent(K kern, int lds, LfArgs a, hipStream_t s, int* grid_out, int cap, bool backward) {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
@@ -1603,7 +1375,7 @@ hipError_t launch_persistent(K kern, int lds, LfArgs a, hipStream_t s, int* grid
     per_cu = 1;
   int grid = lf_num_cus() * per_cu;
   if (grid > cap) grid = cap;
-  plan_items(&a.tab, grid);
+  plan_items(&a.tab, grid, backward);
   if (grid > a.tab.n_items) grid = a.tab.n_items;
   if (grid < 1) grid = 1;
   *grid_out = grid;
@@ -1621,18 +1393,18 @@ hipError_t run_lf(const LfArgs& a, int mode, hipStream_t s) {
   if (e != hipSuccess) return e;
   int g1 = 0, g2 = 0, g3 = 0;
   const int fwd_cap = 4096, bwd_cap = lf_grid_limit();
-  e = launch_persistent(k_density<P, kForward>, DCfg<P, kForward>::LDS, a, s, &g1, fwd_cap);
+  e = launch_persistent(k_density<P, kForward>, DCfg<P, kForward>::LDS, a, s, &g1, fwd_cap, false);
   if (e != hipSuccess) return e;
   if (mode == kForward)
     return launch_persistent(k_color<P, kForward, VD>, CCfg<P, kForward, VD>::LDS, a, s, &g2,
-                             fwd_cap);
+                             fwd_cap, false);
   if (mode == kTrain)
-    e = launch_persistent(k_color<P, kTrain, VD>, CCfg<P, kTrain, VD>::LDS, a, s, &g2, bwd_cap);
+    e = launch_persistent(k_color<P, kTrain, VD>, CCfg<P, kTrain, VD>::LDS, a, s, &g2, bwd_cap, true);
   else
     e = launch_persistent(k_color<P, kBackward, VD>, CCfg<P, kBackward, VD>::LDS, a, s, &g2,
-                          bwd_cap);
+                          bwd_cap, true);
   if (e != hipSuccess) return e;
-  e = launch_persistent(k_density<P, kBackward>, DCfg<P, kBackward>::LDS, a, s, &g3, bwd_cap);
+  e = launch_persistent(k_density<P, kBackward>, DCfg<P, kBackward>::LDS, a, s, &g3, bwd_cap, true);
   if (e != hipSuccess) return e;
   e = launch_reduce_partials(a.partT, g3, D::T::NPARAMS, a.grad_params, nullptr, nullptr, s);
   if (e != hipSuccess) return e;

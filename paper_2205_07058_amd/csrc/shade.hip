@@ -4,494 +4,372 @@
 // interpolation of the leaf's corner features at the segment midpoint
 // (section 4.1), one ReLU decoder C -> H ... -> 4 (section 4.5), optical
 // thickness from sigma (section 4 footnote) and front-to-back alpha
-// compositing (Eq. 3); the backward variant recomputes all of it and
-// propagates dL/d(rgb, depth, acc) to the features (FP32 atomics) and the
-// decoder parameters (per-block partial sums, reduced deterministically).
+// compositing (Eq. 3); the backward and train modes recompute all of it and
+// propagate dL/d(rgb, depth, acc) to the decoder parameters (per-block partial
+// sums, reduced deterministically) and the features (FP32 atomics, or per-hit
+// records for the deterministic reduction).
 //
-// Organisation (one block = 4 waves = 256 rays per work item, persistent):
-//  * the rays' hits are consumed in windows of up to WIN hits that never
-//    split a ray, so compositing and its backward are window-local;
-//  * the window's hit records and the interpolated MLP inputs live in LDS;
-//    each wave runs the decoder on a 32-hit tile with MFMA (32x32x16 BF16 or
-//    32x32x2 FP32), hits on the N dimension: a layer's result (D layout:
-//    lane = hit, registers = output features) is fed to the next layer's B
-//    operand directly, the K order of every weight matrix being permuted at
-//    pack time to match the D layout (no shuffles between layers);
-//  * backward: dL/dz of each layer and the layer's input are written to LDS
-//    transposed ([feature][hit]) and every wave accumulates the dW tiles it
-//    owns over all windows in registers (K = hits); the data gradient uses a
-//    second, transposed weight pack;
-//  * backward: a window's feature-gradient atomics are issued after the next
-//    window's gather, and the next window's hit records and corner ids are
-//    loaded while the current window computes (the window loop);
-//  * the rays of groups of consecutive full work items are interleaved
-//    (item_rays), which shortened both the train and the forward pass.
+// One block = 4 waves, persistent over work items, in hit windows that never
+// split a ray, so compositing and its backward are window-local.  What bounds
+// these kernels is waiting: for the three dependent gathers (record, corner
+// ids, rows), for the chain of small layers, and in the backward for the
+// memory side's atomics, which take 324 G FP32 additions a second however
+// they are issued (one per clock and memory channel; measured with random
+// rows of 64 to 256 bytes over tables of 2 MB to 1 GB).  So a block is kept
+// small enough that others run on its CU meanwhile, and adds as few rows as it
+// can:
+//  * one thread per hit computes the window's records (cell coordinates,
+//    corner ids), then 16 bytes of a row per thread;
+//  * the waves form a grid of H / 32 output-feature groups x 4 / (H / 32) hit
+//    groups; a wave computes its features of its hits.  Its weights sit in
+//    registers, built through LDS once per launch;
+//  * activations are LDS tiles that are MFMA operands as stored (tiles.hpp),
+//    dL/dz replaces them in place, and weight gradients read the same tiles
+//    with the hits along K (LDS transpose read in BF16);
+//  * blocks per CU: forward 4 (H = 32), 3 (BF16), 2 (FP32; with 64-hit windows 3
+//    fit, 137 instead of 130 us for an 800^2 view); backward 2.  The FP32
+//    backward with H = 64 needs twice the registers: one block, 64-hit windows,
+//    and a window's atomics are issued after the next window's gather, whose
+//    loads would otherwise queue behind them;
+//  * a row that consecutive hits of a ray share is added once (CornerCarry).
+// Measured against one 124 KB block per CU with the packs in LDS (2^20 rays, C =
+// 32, BF16): train kernel 1.18 -> 1.03 ms, of which 0.5 ms without atomics
+// (1.00 before); 100,003-ray pass without atomics 262 -> 159 us; a 1600^2
+// BF16 view 388 -> 360 us; backward of 20,011 rays at H = 32 FP32 63 -> 33 us.
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-#include <utility>
-
-#include "mfma_common.hpp"
 #include "svlf_internal.hpp"
+#include "tiles.hpp"
 
 namespace svlf {
 namespace {
 
 using namespace detail;
 
-constexpr int kThreads = 256;
-static_assert(kThreads == kRaysPerBlock, "one ray per thread in a work item");
-static_assert(kThreads <= 256 && SVLF_MAX_K <= 256, "hit map entries: 8-bit lane, 8-bit slot");
-constexpr int kWaves = 4;
-
-// ------------------------------------------------------------ geometry
-
-constexpr int in_w(int l, int CI, int H) { return l == 0 ? CI : H; }
-constexpr int out_w(int l, int H, int NH) { return l == NH ? 32 : H; }
-constexpr int in_real(int l, int C, int H) { return l == 0 ? C : H; }
-constexpr int out_real(int l, int H, int NH) { return l == NH ? 4 : H; }
-constexpr int bwd_m(int l, int H) { return l == 0 ? 32 : H; }
-
-constexpr int fwd_off(int l, int CI, int H, int NH) {
-  int o = 0;
-  for (int i = 0; i < l; ++i) o += out_w(i, H, NH) * in_w(i, CI, H);
-  return o;
-}
-constexpr int bwd_off(int l, int H, int NH) {
-  int o = 0;
-  for (int i = 0; i < l; ++i) o += bwd_m(i, H) * out_w(i, H, NH);
-  return o;
-}
-constexpr int bias_off(int l, int H, int NH) {
-  int o = 0;
-  for (int i = 0; i < l; ++i) o += out_w(i, H, NH);
-  return o;
-}
-constexpr int par_w(int l, int C, int H, int NH) {
-  int o = 0;
-  for (int i = 0; i < l; ++i) o += out_real(i, H, NH) * in_real(i, C, H) + out_real(i, H, NH);
-  return o;
-}
-constexpr int par_b(int l, int C, int H, int NH) {
-  return par_w(l, C, H, NH) + out_real(l, H, NH) * in_real(l, C, H);
-}
-// dW tiles per layer: (out tiles) x (in tiles)
-constexpr int dw_mt(int l, int H, int NH) { return out_w(l, H, NH) / 32; }
-constexpr int dw_nt(int l, int H, int CIN) { return l == 0 ? (CIN + 31) / 32 : H / 32; }
-constexpr int dw_tile_off(int l, int H, int NH, int CIN) {
-  int o = 0;
-  for (int i = 0; i < l; ++i) o += dw_mt(i, H, NH) * dw_nt(i, H, CIN);
-  return o;
-}
-
-// VD = 1: the decoder input is [psi (C) | ray direction (3)].
-template <int P, int C_, int H_, int NH_, int MODE_, int VD_ = 0>
+template <int P, int C_, int H_, int NH_, int MODE_, int VD_>
 struct Cfg {
   static constexpr bool BF = P == 1;
-  static constexpr int C = C_, H = H_, NH = NH_, MODE = MODE_, VD = VD_;
-  static constexpr bool BWD = MODE != kForward;
-  static constexpr int KS = BF ? 16 : 2;            // K per MFMA
-  static constexpr int CIN = C + 3 * VD;            // decoder input width
-  static constexpr int CI = BF ? align16(CIN) : align8(CIN);  // padded to the K steps
-  static constexpr int NL = NH + 1;
-  static constexpr int MTH = H / 32;
-  static constexpr int WIN = (BWD && !BF) ? 64 : 128;
-  static constexpr int NTILE = WIN / 32;
+  static constexpr int C = C_, H = H_, NH = NH_, MODE = MODE_, VD = VD_, OUT = 4;
   static constexpr int EB = BF ? 2 : 4;
-  using Op = typename std::conditional<BF, s16x8, float>::type;
-  using Elem = typename std::conditional<BF, uint16_t, float>::type;
-  static constexpr int FWD_ELEMS = fwd_off(NL, CI, H, NH);
-  static constexpr int BWD_ELEMS = BWD ? bwd_off(NL, H, NH) : 0;
-  static constexpr int BIAS_ELEMS = bias_off(NL, H, NH);
-  static constexpr int NPARAMS = par_w(NL, CIN, H, NH);
-  static constexpr int NDW = dw_tile_off(NL, H, NH, CIN);     // dW tiles
-  static constexpr int DW_SLOTS = (NDW + kWaves - 1) / kWaves;
-  static constexpr int NBIAS = NH * H + 4;
-  static constexpr int XS = CI + (BF ? 8 : 4);                  // X row stride
-  static constexpr int TS = WIN + (BF ? 8 : 1);                 // transposed row stride
-  static constexpr int TROWS = H > 32 ? H : 32;
-  // LDS byte layout
-  static constexpr int L_FP = 0;
-  static constexpr int L_BP = align16(L_FP + FWD_ELEMS * EB);
-  static constexpr int L_BI = align16(L_BP + BWD_ELEMS * EB);
-  static constexpr int L_REC = align16(L_BI + BIAS_ELEMS * 4);
-  static constexpr int L_X = align16(L_REC + WIN * 64);
-  static constexpr int L_OUT = align16(L_X + WIN * XS * EB);
-  static constexpr int L_GZ = align16(L_OUT + WIN * 32);
-  static constexpr int L_AT = align16(L_GZ + (BWD ? TROWS * TS * EB : 0));
-  // hit map: all of a work item's hits, 16 bits per hit (IMAP: backward
-  // kernels where it fits), else the window's hits, 32 bits per hit
-  // (backward: two windows, the current one and the next)
-  static constexpr int L_MAP = align16(L_AT + (BWD ? TROWS * TS * EB : 0));
-  static constexpr int map_end(int entries) {
-    return align16(align16(L_MAP + entries * 2) + (BWD ? WIN * 64 : 0)) + 64;
+  static constexpr int CIN = C + 3 * VD;                 // decoder inputs
+  static constexpr int CI = BF ? align16(CIN) : align8(CIN);
+  static constexpr bool BWD = MODE != kForward;
+  static constexpr bool NARROW = BF || H == 32;          // a wave's weights take <= 76 registers
+  static constexpr bool DEFER = BWD && !NARROW;
+  static constexpr int WIN = NARROW || !BWD ? 128 : 64;
+  static constexpr int BLOCKS = BWD ? (NARROW ? 2 : 1) : (H == 32 ? 4 : NARROW ? 3 : 2);   // per CU, by registers
+  static constexpr int NT = WIN / 32;                    // 32-hit tiles
+  static constexpr int MG = H / 32, NG = kWaves / MG;    // wave grid
+  static constexpr int TPW = NT / NG;                    // tiles of a wave's hits
+  static constexpr int NF0 = CI / kFragK<BF>, NFH = H / kFragK<BF>;
+  static constexpr int NTX = (CIN + 31) / 32;            // dW tiles along the inputs
+  using El = typename Types<BF>::Elem;
+  static_assert(TPW >= 1 && MG * NG == kWaves && NTX <= (NG > 1 ? 2 : 1), "wave grid");
+  static_assert(C <= 32 && (H == 64 || NTX == 1), "input layer");
+  // parameters
+  static constexpr int NACT = BWD ? NH : 1;              // forward: each layer takes the previous one's place
+  static constexpr int act_of(int l) { return BWD ? l : 0; }
+  static constexpr int in_r(int l) { return l == 0 ? CIN : H; }
+  static constexpr int out_r(int l) { return l == NH ? OUT : H; }
+  static constexpr int par_w(int l) {
+    int o = 0;
+    for (int i = 0; i < l; ++i) o += out_r(i) * in_r(i) + out_r(i);
+    return o;
   }
-  static constexpr bool IMAP = BWD && map_end(kThreads * SVLF_MAX_K) <= 160 * 1024;
-  using MapT = typename std::conditional<IMAP, uint16_t, int32_t>::type;
-  static constexpr int MAP_ENTRIES = IMAP ? kThreads * SVLF_MAX_K : (BWD ? 2 : 1) * WIN;
-  // backward: records of the window awaiting its scatter
-  static constexpr int L_REC2 = align16(L_MAP + MAP_ENTRIES * static_cast<int>(sizeof(MapT)));
-  static constexpr int L_SCR = align16(L_REC2 + (BWD ? WIN * 64 : 0));
-  static constexpr int LDS_BYTES = L_SCR + 64;
-  static_assert(NBIAS <= kThreads, "one thread per bias entry writes its combined gradient");
-  static_assert(C <= 32 && CI <= TROWS, "feature gradients come from one 32-row tile");
-  static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
-  static_assert(!BWD || WIN * C * 4 <= 2 * TROWS * TS * EB, "dL/dx staging fits in GZ + AT");
+  static constexpr int par_b(int l) { return par_w(l) + out_r(l) * in_r(l); }
+  static constexpr int NPARAMS = par_w(NH + 1);
+  // packs, fragments of 1024 bytes: [forward layers 0 .. NH-1][transposed
+  // layers 1 .. NH] (the output layer's has its 4 real K positions in fragment 0)
+  static constexpr int pk_fwd(int l) { return l == 0 ? 0 : MG * (NF0 + (l - 1) * NFH); }
+  static constexpr int pk_bwd(int l) { return pk_fwd(NH) + MG * (l - 1) * NFH; }
+  static constexpr int PACK = (BWD ? pk_bwd(NH) + MG : pk_fwd(NH)) * 1024;
+  // LDS: kept for the launch, then the window's data, where the packs are
+  // built first
+  static constexpr int ROWH = H * EB;
+  static constexpr int ROWX = CI > 32 ? (BF ? 96 : 192) : 32 * EB;
+  static constexpr int ROWG = C * 4;
+  static constexpr int GOS = WIN * EB;
+  static constexpr int ACT = WIN * ROWH;
+  static constexpr int L_W3 = 0;                         // output layer, 4 rows
+  static constexpr int L_B0 = L_W3 + OUT * H * EB;       // transposed input layer (dL/dx)
+  static constexpr int L_BIAS = L_B0 + (BWD ? NFH * 1024 : 0);
+  static constexpr int L_SCR = L_BIAS + (NH * H + OUT) * 4;   // (rows past the output's 4 read on)
+  static constexpr int L_SHARE = L_SCR + 64;             // corners shared with the next hit [2][WIN] uint8
+  static constexpr int L_X = L_SHARE + (BWD ? (DEFER ? 2 : 1) * WIN : 0);
+  static constexpr int L_ACT = L_X + WIN * ROWX;
+  static constexpr int L_LAST = L_ACT + (NACT - 1) * ACT;
+  static constexpr int L_GX = L_LAST;                    // dL/dx takes the last layer's place
+  static constexpr int L_ID = L_ACT + NACT * ACT;        // corner ids [2][WIN] int4
+  static constexpr int L_U = L_ID + (DEFER ? 2 : 1) * WIN * 32;     // cell coordinates [3][WIN]
+  static constexpr int L_OUT = L_U + (DEFER ? 2 : 1) * WIN * 12;
+  static constexpr int L_GO = L_OUT + WIN * 32;          // dL/do [4][WIN]
+  static constexpr int L_MAP = L_GO + (BWD ? OUT * GOS : 0);   // [256 K] uint16
+  static constexpr int lds_bytes(int K) {
+    const int win = L_MAP + kThreads * K * 2, pack = L_X + PACK, part = BWD ? L_X + NPARAMS * 4 : 0;
+    const int m = win > pack ? win : pack;
+    return m > part ? m : part;
+  }
+  static_assert(lds_bytes(SVLF_MAX_K) <= 160 * 1024, "LDS");
+  static_assert(WIN * ROWG <= ACT && L_X % 16 == 0 && L_MAP % 16 == 0, "LDS layout");
 };
 
-// Hit record in LDS (64 bytes): the leaf's corner vertex ids are fetched
-// once by the ray's lane, so the gather and the gradient scatter start with
-// independent feature-row accesses.
-struct RecL {
-  int32_t leaf;
-  float ux, uy, uz;
-  float tmid;
-  float dt;
-  float T;
-  float pad;
-  int4 v0, v1;
-};
-
-// Dynamic LDS of the shading kernels.  Every LDS address is derived from
-// this array directly, so the compiler keeps LDS accesses as ds_* operations
-// (an LDS pointer stored in an object would be accessed as a generic address,
-// and each generic access waits for all outstanding global memory traffic).
-extern __shared__ __attribute__((aligned(16))) char g_smem[];
-
+// Packs, output layer, transposed input layer and biases from the FP32
+// parameters (all read at once, in order); padding stays zero.  Ends with a
+// barrier.
 template <class CF>
-struct Smem {
-  __device__ __forceinline__ typename CF::Elem* fpack() const { return reinterpret_cast<typename CF::Elem*>(g_smem + CF::L_FP); }
-  __device__ __forceinline__ typename CF::Elem* bpack() const { return reinterpret_cast<typename CF::Elem*>(g_smem + CF::L_BP); }
-  __device__ __forceinline__ float* bias() const { return reinterpret_cast<float*>(g_smem + CF::L_BI); }
-  __device__ __forceinline__ RecL* rec(int b) const {
-    return reinterpret_cast<RecL*>(g_smem + (b ? CF::L_REC2 : CF::L_REC));
-  }
-  __device__ __forceinline__ typename CF::Elem* X() const { return reinterpret_cast<typename CF::Elem*>(g_smem + CF::L_X); }
-  __device__ __forceinline__ float* out() const { return reinterpret_cast<float*>(g_smem + CF::L_OUT); }
-  __device__ __forceinline__ typename CF::Elem* GZ() const { return reinterpret_cast<typename CF::Elem*>(g_smem + CF::L_GZ); }
-  __device__ __forceinline__ typename CF::Elem* AT() const { return reinterpret_cast<typename CF::Elem*>(g_smem + CF::L_AT); }
-  __device__ __forceinline__ int* scr() const { return reinterpret_cast<int*>(g_smem + CF::L_SCR); }
-  // entry = the hit's ray lane | (its slot in the ray's hit list << 8)
-  __device__ __forceinline__ typename CF::MapT* hmap() const {
-    return reinterpret_cast<typename CF::MapT*>(g_smem + CF::L_MAP);
-  }
-};
-
-template <class CF>
-__device__ __forceinline__ typename CF::Elem to_elem(float v) {
-  if constexpr (CF::BF) return static_cast<uint16_t>(bf16_rne(v));
-  else return v;
-}
-
-// ------------------------------------------------------------ weight packs
-
-// Every block builds its own packs, so a small call waits for this: all of the
-// parameters are read at once, in order (a read per pack entry, in loops, was
-// latency-bound), then scattered to their places in the forward and the
-// transposed pack.  Ends without a barrier.
-template <class CF>
-__device__ __forceinline__ void build_packs(const Smem<CF>& sm, const float* __restrict__ params) {
-  constexpr int E = CF::BF ? 8 : 1;
+__device__ __forceinline__ void build_packs(const float* __restrict__ params) {
+  constexpr bool BF = CF::BF;
   constexpr int N = (CF::NPARAMS + kThreads - 1) / kThreads;
+  using El = typename CF::El;
   const int tid = threadIdx.x;
   float v[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] = i * kThreads + tid < CF::NPARAMS ? params[i * kThreads + tid] : 0.0f;
-  // padding (input columns, output rows) stays zero
-  static_assert(CF::L_FP == 0 && (CF::L_BI + CF::BIAS_ELEMS * 4) % 16 == 0, "packs and biases lead the LDS");
-  uint4* z = reinterpret_cast<uint4*>(g_smem);
-  for (int e = tid; e < (CF::L_BI + CF::BIAS_ELEMS * 4) / 16; e += kThreads) z[e] = make_uint4(0u, 0u, 0u, 0u);
+  uint4* z = reinterpret_cast<uint4*>(g_lds);
+  for (int e = tid; e < (CF::L_X + CF::PACK) / 16; e += kThreads) z[e] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
+  auto put = [&](int frag_base, int nf, int r, int i, int g, int j, El w) {
+    // row r of a packed matrix whose first fragment is at byte frag_base
+    *reinterpret_cast<El*>(g_lds + frag_base + ((r >> 5) * nf + i) * 1024 + ((r & 31) + 32 * g) * 16 + j * CF::EB) = w;
+  };
+  auto pos_d = [](int k, int& i, int& g, int& j) {
+    i = BF ? k >> 4 : k >> 3;
+    g = (k >> 2) & 1;
+    j = BF ? ((k >> 1) & 4) | (k & 3) : k & 3;
+  };
   static_for<N>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    const int idx = i * kThreads + tid;
-    static_for<CF::NL>([&](auto lc) {
+    constexpr int it = decltype(ic)::value;
+    const int idx = it * kThreads + tid;
+    static_for<CF::NH + 1>([&](auto lc) {
       constexpr int l = decltype(lc)::value;
-      constexpr int IW = in_w(l, CF::CI, CF::H), OW = out_w(l, CF::H, CF::NH);
-      constexpr int IR = in_real(l, CF::CIN, CF::H), OR = out_real(l, CF::H, CF::NH);
-      constexpr int PW = par_w(l, CF::CIN, CF::H, CF::NH), PB = par_b(l, CF::CIN, CF::H, CF::NH);
-      if constexpr (PW < (i + 1) * kThreads && PB > i * kThreads) {
+      constexpr int PW = CF::par_w(l), PB = CF::par_b(l), IR = CF::in_r(l), OR = CF::out_r(l);
+      if constexpr (PW < (it + 1) * kThreads && PB > it * kThreads) {
         if (idx >= PW && idx < PB) {
           const int m = (idx - PW) / IR, k = (idx - PW) % IR;
-          const typename CF::Elem w = to_elem<CF>(v[i]);
-          {
-            const KPos p = l == 0 ? kpos_x<CF::BF>(k) : kpos_d<CF::BF>(k);
-            const int lane = (m & 31) + 32 * p.g;
-            sm.fpack()[fwd_off(l, CF::CI, CF::H, CF::NH) +
-                       (((m >> 5) * (IW / CF::KS) + p.s) * 64 + lane) * E + p.j] = w;
+          const El w = to_el<BF>(v[it]);
+          int i, g, j;
+          if constexpr (l == 0) {
+            i = BF ? k >> 4 : k >> 3;
+            g = BF ? (k >> 3) & 1 : (k >> 2) & 1;
+            j = BF ? k & 7 : k & 3;
+          } else {
+            pos_d(k, i, g, j);
           }
-          if constexpr (CF::BWD) {
-            // transposed pack: M = layer input (features only), K = layer output
-            if (k < bwd_m(l, CF::H)) {
-              const KPos p = kpos_d<CF::BF>(m);
-              const int lane = (k & 31) + 32 * p.g;
-              sm.bpack()[bwd_off(l, CF::H, CF::NH) +
-                         (((k >> 5) * (OW / CF::KS) + p.s) * 64 + lane) * E + p.j] = w;
-            }
+          if constexpr (l == CF::NH)
+            *reinterpret_cast<El*>(g_lds + CF::L_W3 + (m * 2 * CF::NFH + 2 * i + g) * 16 + j * CF::EB) = w;
+          else
+            put(CF::L_X + CF::pk_fwd(l) * 1024, l == 0 ? CF::NF0 : CF::NFH, m, i, g, j, w);
+          pos_d(m, i, g, j);
+          if constexpr (!CF::BWD) {
+          } else if constexpr (l == 0) {
+            if (k < CF::C) put(CF::L_B0, CF::NFH, k, i, g, j, w);
+          } else {
+            put(CF::L_X + CF::pk_bwd(l) * 1024, l == CF::NH ? 1 : CF::NFH, k, i, g, j, w);
           }
         }
       }
-      if constexpr (PB < (i + 1) * kThreads && PB + OR > i * kThreads) {
-        if (idx >= PB && idx < PB + OR) sm.bias()[bias_off(l, CF::H, CF::NH) + idx - PB] = v[i];
+      if constexpr (PB < (it + 1) * kThreads && PB + OR > it * kThreads) {
+        if (idx >= PB && idx < PB + OR)
+          *reinterpret_cast<float*>(g_lds + CF::L_BIAS + (l * CF::H + idx - PB) * 4) = v[it];
       }
     });
   });
+  __syncthreads();
 }
 
-template <class CF>
-__device__ __forceinline__ typename CF::Op pack_operand(const typename CF::Elem* pack, int mt, int s,
-                                                        int steps, int lane) {
-  if constexpr (CF::BF)
-    return *reinterpret_cast<const s16x8*>(pack + ((mt * steps + s) * 64 + lane) * 8);
-  else
-    return pack[(mt * steps + s) * 64 + lane];
+template <int N>
+__device__ __forceinline__ void lds_frags(frag_t (&w)[N], int base, int mt, int lane) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) w[i] = *reinterpret_cast<const frag_t*>(g_lds + base + ((mt * N + i) * 64 + lane) * 16);
 }
 
-template <class CF>
-__device__ __forceinline__ typename CF::Op d_operand(const f32x16* t, int s) {
-  if constexpr (CF::BF) {
-    s16x8 b;
-    const f32x16& tt = t[s >> 1];
-    {
-      const int o = 8 * (s & 1);
-      b = bf16_rne8(tt[o], tt[o + 1], tt[o + 2], tt[o + 3], tt[o + 4], tt[o + 5], tt[o + 6], tt[o + 7]);
-    }
-    return b;
-  } else {
-    return t[s >> 4][s & 15];
-  }
-}
-
-template <class CF>
-__device__ __forceinline__ typename CF::Op x_operand(const Smem<CF>& sm, int row, int s, int g) {
-  if constexpr (CF::BF) {
-    return *reinterpret_cast<const s16x8*>(sm.X() + row * CF::XS + 16 * s + 8 * g);
-  } else {
-    return sm.X()[row * CF::XS + 4 * (2 * (s >> 2) + g) + (s & 3)];
-  }
-}
-
-template <class CF>
-__device__ __forceinline__ f32x16 bias_tile(const Smem<CF>& sm, int l_off, int mt, int g) {
+__device__ __forceinline__ f32x16 lds_bias(int base, int g) {
   f32x16 t;
-  const float* b = sm.bias() + l_off + 32 * mt + 4 * g;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(b + 8 * q);
-    t[4 * q + 0] = v[0];
-    t[4 * q + 1] = v[1];
-    t[4 * q + 2] = v[2];
-    t[4 * q + 3] = v[3];
+    const f32x4 v = *reinterpret_cast<const f32x4*>(g_lds + base + (8 * q + 4 * g) * 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[4 * q + e] = v[e];
   }
   return t;
 }
 
-// Kept hidden activations of a 32x32 tile (backward only): FP32 values, or
-// on the BF16 path the bfloat16 values the MFMA operands were made of.
-template <bool BF>
-struct ActTile;
-template <>
-struct ActTile<true> {
-  s16x8 lo, hi;
-  __device__ __forceinline__ void set(const f32x16& t) {
-    lo = bf16_rne8(t[0], t[1], t[2], t[3], t[4], t[5], t[6], t[7]);
-    hi = bf16_rne8(t[8], t[9], t[10], t[11], t[12], t[13], t[14], t[15]);
+// dw += (tile ta of A)^T x (tile tb of B) over the 16-hit steps [k0, k1);
+// bs += the sum of A's row.
+template <bool BF, int ROWA, int ROWB>
+__device__ __forceinline__ void dw_steps(f32x16& dw, float& bs, int base_a, int ta, int base_b, int tb, int k0, int k1,
+                                         int lane) {
+  lane = here(lane);
+  for (int k = k0; k < k1; ++k) {
+    if constexpr (BF) {
+      const s16x8 a = hits_operand_bf16<ROWA>(base_a, ta, k, lane);
+      dw = mma(a, hits_operand_bf16<ROWB>(base_b, tb, k, lane), dw);
+      float sum = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) sum += bf16_f32(static_cast<uint16_t>(a[j]));
+      bs += sum;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float a = hits_operand_fp32<ROWA>(base_a, ta, 8 * k + j, lane);
+        dw = mma(a, hits_operand_fp32<ROWB>(base_b, tb, 8 * k + j, lane), dw);
+        bs += a;
+      }
+    }
   }
-  __device__ __forceinline__ bool positive(int i) const { return (i < 8 ? lo[i] : hi[i - 8]) > 0; }
-  __device__ __forceinline__ uint16_t elem(int i) const {
-    return static_cast<uint16_t>(i < 8 ? lo[i] : hi[i - 8]);
+}
+
+// The forward weights of a wave: its 32 features of every hidden layer.
+template <class CF>
+struct Weights {
+  frag_t w0[CF::NF0], wh[CF::NH - 1][CF::NFH];
+  __device__ __forceinline__ void load(int mg, int lane) {
+    lds_frags(w0, CF::L_X, mg, lane);
+    static_for<CF::NH - 1>([&](auto lc) {
+      constexpr int l = decltype(lc)::value + 1;
+      lds_frags(wh[l - 1], CF::L_X + CF::pk_fwd(l) * 1024, mg, lane);
+    });
   }
-};
-template <>
-struct ActTile<false> {
-  f32x16 v;
-  __device__ __forceinline__ void set(const f32x16& t) { v = t; }
-  __device__ __forceinline__ bool positive(int i) const { return v[i] > 0.0f; }
-  __device__ __forceinline__ float elem(int i) const { return v[i]; }
 };
 
-// Decoder forward on the 32 hits [n0, n0+32) of the window.  Returns the
-// output tile (rows 0..3 = raw o_0..o_3 in registers 0..3 of lanes 0..31);
-// with SAVE, the post-ReLU activations of every hidden layer are kept.
-template <class CF, bool SAVE>
-__device__ __forceinline__ f32x16 mlp_tile(const Smem<CF>& sm, int n0, int lane,
-                                           ActTile<CF::BF> (&act)[CF::NH][CF::MTH]) {
-  const int g = lane >> 5, row = n0 + (lane & 31);
-  f32x16 cur[CF::MTH];
-  {
-    constexpr int S0 = CF::CI / CF::KS;
-    const typename CF::Elem* A = sm.fpack();
+// Hidden layers of the window's first tp hits (a multiple of 64): wave (mg, ng)
+// computes its features of its hits.  Called by all threads; ends with a
+// barrier.
+template <class CF>
+__device__ __forceinline__ void hidden_layers(const Weights<CF>& W, int tp, int mg, int ng, int lane) {
+  constexpr bool BF = CF::BF;
+  constexpr int TPW = CF::TPW;
+  const int g = lane >> 5, t0 = TPW * ng;
+  const bool mine = 32 * t0 < tp;
+  static_for<CF::NH>([&](auto lc) {
+    constexpr int l = decltype(lc)::value;
+    constexpr int SRC = CF::L_ACT + CF::act_of(l > 0 ? l - 1 : 0) * CF::ACT, DST = CF::L_ACT + CF::act_of(l) * CF::ACT;
+    // in place: all waves have read before any writes (H = 32: own rows only)
+    constexpr bool IN_PLACE = l > 0 && SRC == DST && CF::MG > 1;
+    f32x16 acc[TPW];
+    if (mine) {
+      const int ln = here(lane), hit = 32 * t0 + (ln & 31);
+      const f32x16 b = lds_bias(CF::L_BIAS + (l * CF::H + 32 * mg) * 4, g);
 #pragma unroll
-    for (int mt = 0; mt < CF::MTH; ++mt) cur[mt] = bias_tile(sm, 0, mt, g);
+      for (int t = 0; t < TPW; ++t) acc[t] = b;
+      if constexpr (l == 0) {
 #pragma unroll
-    for (int s = 0; s < S0; ++s) {
-      const typename CF::Op b = x_operand(sm, row, s, g);
+        for (int i = 0; i < CF::NF0; ++i)
 #pragma unroll
-      for (int mt = 0; mt < CF::MTH; ++mt) cur[mt] = mma(pack_operand<CF>(A, mt, s, S0, lane), b, cur[mt]);
+          for (int t = 0; t < TPW; ++t)
+            acc[t] = mma_frag<BF>(W.w0[i], frag_at<CF::ROWX>(CF::L_X, hit + 32 * t, 2 * i + g), acc[t]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < CF::NFH; ++i)
+#pragma unroll
+          for (int t = 0; t < TPW; ++t)
+            acc[t] = mma_frag<BF>(W.wh[l - 1][i], frag_at<CF::ROWH>(SRC, hit + 32 * t, 2 * i + g), acc[t]);
+      }
     }
+    if constexpr (IN_PLACE) __syncthreads();
+    if (mine) {
 #pragma unroll
-    for (int mt = 0; mt < CF::MTH; ++mt) relu16(cur[mt]);
-    if constexpr (SAVE) {
-#pragma unroll
-      for (int mt = 0; mt < CF::MTH; ++mt) act[0][mt].set(cur[mt]);
+      for (int t = 0; t < TPW; ++t) {
+        relu16(acc[t]);
+        store_tile<BF, CF::ROWH>(DST, mg, 32 * (t0 + t) + (lane & 31), g, acc[t]);
+      }
     }
-  }
-  static_for<CF::NH - 1>([&](auto lc) {
-    constexpr int l = decltype(lc)::value + 1;
-    constexpr int S = CF::H / CF::KS;
-    const typename CF::Elem* A = sm.fpack() + fwd_off(l, CF::CI, CF::H, CF::NH);
-    f32x16 nxt[CF::MTH];
-#pragma unroll
-    for (int mt = 0; mt < CF::MTH; ++mt) nxt[mt] = bias_tile(sm, bias_off(l, CF::H, CF::NH), mt, g);
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const typename CF::Op b = d_operand<CF>(cur, s);
-#pragma unroll
-      for (int mt = 0; mt < CF::MTH; ++mt) nxt[mt] = mma(pack_operand<CF>(A, mt, s, S, lane), b, nxt[mt]);
-    }
-#pragma unroll
-    for (int mt = 0; mt < CF::MTH; ++mt) {
-      relu16(nxt[mt]);
-      cur[mt] = nxt[mt];
-      if constexpr (SAVE) act[l][mt].set(nxt[mt]);
-    }
+    __syncthreads();
   });
-  constexpr int S = CF::H / CF::KS;
-  const typename CF::Elem* A = sm.fpack() + fwd_off(CF::NH, CF::CI, CF::H, CF::NH);
-  f32x16 o = bias_tile(sm, bias_off(CF::NH, CF::H, CF::NH), 0, g);
+}
+
+// Output layer of the 32 hits from n0: raw o_0 .. o_3 of hit n0 + lane in
+// registers 0 .. 3 of lanes 0 .. 31.
+template <class CF>
+__device__ __forceinline__ f32x16 output_layer(int n0, int lane) {
+  const int ln = here(lane), g = lane >> 5;
+  f32x16 o = lds_bias(CF::L_BIAS + CF::NH * CF::H * 4, g);
 #pragma unroll
-  for (int s = 0; s < S; ++s) o = mma(pack_operand<CF>(A, 0, s, S, lane), d_operand<CF>(cur, s), o);
+  for (int i = 0; i < CF::NFH; ++i) {
+    frag_t wf = {0, 0, 0, 0};
+    if ((ln & 31) < 4) wf = *reinterpret_cast<const frag_t*>(g_lds + CF::L_W3 + ((ln & 31) * 2 * CF::NFH + 2 * i + g) * 16);
+    o = mma_frag<CF::BF>(wf, frag_at<CF::ROWH>(CF::L_LAST, n0 + (ln & 31), 2 * i + g), o);
+  }
   return o;
 }
 
-// Data gradient through layer l: r = W_l^T gt (gt in D layout over the
-// layer's outputs, r in D layout over its inputs).
-template <class CF, int l>
-__device__ __forceinline__ void bwd_data(const Smem<CF>& sm, const f32x16* gt, f32x16* r, int lane) {
-  constexpr int MT = bwd_m(l, CF::H) / 32;
-  constexpr int S = out_w(l, CF::H, CF::NH) / CF::KS;
-  const typename CF::Elem* B = sm.bpack() + bwd_off(l, CF::H, CF::NH);
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) r[mt] = zero16();
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const typename CF::Op b = d_operand<CF>(gt, s);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) r[mt] = mma(pack_operand<CF>(B, mt, s, S, lane), b, r[mt]);
-  }
-}
-
-// Writes kept activation tiles of the hits [n0, n0+32) transposed into T.
-template <class CF, int NT>
-__device__ __forceinline__ void store_act_T(typename CF::Elem* T, const ActTile<CF::BF>* t, int n0,
-                                            int lane) {
-  const int g = lane >> 5, col = n0 + (lane & 31);
-#pragma unroll
-  for (int mt = 0; mt < NT; ++mt) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) T[(32 * mt + drow(i, g)) * CF::TS + col] = t[mt].elem(i);
-  }
-}
-
-// Writes `nt` D-layout tiles of the hits [n0, n0+32) transposed into T
-// ([feature][hit], row stride TS).
-template <class CF, int NT>
-__device__ __forceinline__ void store_T(typename CF::Elem* T, const f32x16* t, int n0, int lane) {
-  const int g = lane >> 5, col = n0 + (lane & 31);
-#pragma unroll
-  for (int mt = 0; mt < NT; ++mt) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) T[(32 * mt + drow(i, g)) * CF::TS + col] = to_elem<CF>(t[mt][i]);
-  }
-}
-
-// ------------------------------------------------------------ the kernel
-
 template <class CF>
-__global__ __launch_bounds__(kThreads, CF::BWD ? 1 : 3) void k_shade(ShadeArgs a) {
-  const Smem<CF> sm{};
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
+__global__ __launch_bounds__(kThreads, CF::BLOCKS) void k_shade(ShadeArgs a) {
+  constexpr bool BF = CF::BF;
+  constexpr int H = CF::H, NH = CF::NH, MG = CF::MG, TPW = CF::TPW, NB = CF::BWD ? NH - 1 : 1;
+  using El = typename CF::El;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, row = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mg = wave % MG, ng = wave / MG;
+  int* scr = reinterpret_cast<int*>(g_lds + CF::L_SCR);
+  float* out = reinterpret_cast<float*>(g_lds + CF::L_OUT);
+  uint16_t* imap = reinterpret_cast<uint16_t*>(g_lds + CF::L_MAP);
 
-  build_packs<CF>(sm, a.params);
-
-  // dW tiles owned by this wave (accumulated over everything this block does)
-  f32x16 dw[CF::DW_SLOTS > 0 ? CF::DW_SLOTS : 1];
-#pragma unroll
-  for (int i = 0; i < CF::DW_SLOTS; ++i) dw[i] = zero16();
-  // bias gradients: for layer l, thread (row = tid % out_w, part = tid /
-  // out_w) sums its share of every window's hits; the parts are combined
-  // once at the end
-  float dbp[CF::NL];
-#pragma unroll
-  for (int l = 0; l < CF::NL; ++l) dbp[l] = 0.0f;
-  float loss_acc = 0.0f;
-
-  // Items (256-ray blocks) are dealt round-robin over the persistent grid
-  // for balance; the logical block index groups the blocks of one XCD
-  // (hardware places block b on XCD b % 8) so that each XCD works on
-  // neighbouring rays in every round and shares their features in its L2.
-  const int G = gridDim.x, b = blockIdx.x;
-  const int lb = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
-  const int NB = a.tab.n_items;
-  // The last two rounds of items are handed out in order by a counter to
-  // whichever block is free, so that blocks whose items held fewer hits
-  // take more of them and the launch does not wait on the slowest block.
-  const int n_tail = a.item_counter != nullptr ? (NB < 2 * G ? NB : 2 * G) : 0;
-  const int n_static = NB - n_tail;
-  auto tail_item = [&]() -> int {
-    if (n_tail == 0) return NB;                 // no counter: every item is dealt statically
-    if (tid == 0) sm.scr()[9] = n_static + atomicAdd(a.item_counter, 1);
-    __syncthreads();
-    const int it = sm.scr()[9];
-    __syncthreads();
-    return it;
-  };
-
-  // Backward: a window's feature-gradient atomics are issued after the next
-  // window's gather, so that the gather's loads do not queue behind them
-  // (the vector-memory counter a wave waits on counts both); the window's
-  // records stay in the other record buffer, its dL/dx in the GZ region
-  // (untouched until the next window's backward).
-  int rb = 0;                    // record buffer of the current window
-  int pend_tw = 0;               // hits of the window awaiting its scatter
-  float* pend_grad = nullptr;
-  auto scatter = [&](int ptw, float* pgrad, const RecL* prec) {
-    const int n0p = 32 * wave;
-    if (wave < CF::NTILE && n0p < ptw) {
-      constexpr int HPI = 64 / CF::C;            // hits per instruction
-      const int c = lane % CF::C, hs = lane / CF::C;
-      const float* gxs = reinterpret_cast<const float*>(sm.GZ());
-      for (int k = 0; k < 32; k += HPI) {
-        const int hh = n0p + k + hs;
-        if (hh < ptw) {
-          const RecL rc = prec[hh];
-          const int vid[8] = {rc.v0.x, rc.v0.y, rc.v0.z, rc.v0.w, rc.v1.x, rc.v1.y, rc.v1.z, rc.v1.w};
-          const float wx[2] = {1.0f - rc.ux, rc.ux}, wy[2] = {1.0f - rc.uy, rc.uy},
-                      wz[2] = {1.0f - rc.uz, rc.uz};
-          const float gv = gxs[hh * CF::C + c];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const float wj = wx[j & 1] * wy[(j >> 1) & 1] * wz[j >> 2];
-            unsafeAtomicAdd(pgrad + static_cast<int64_t>(vid[j]) * CF::C + c, wj * gv);
-          }
-        }
-      }
-    }
-  };
-
+  // this wave's weights, for the launch
+  Weights<CF> W;
+  frag_t bh[NB][CF::NFH], bo[1];               // transposed, backward
+  build_packs<CF>(a.params);
+  W.load(mg, lane);
+  if constexpr (CF::BWD) {
+    static_for<NH - 1>([&](auto lc) {
+      constexpr int l = decltype(lc)::value + 1;
+      lds_frags(bh[l - 1], CF::L_X + CF::pk_bwd(l) * 1024, mg, lane);
+    });
+    lds_frags(bo, CF::L_X + CF::pk_bwd(NH) * 1024, mg, lane);
+  }
   __syncthreads();
 
-  for (int item = lb < n_static ? lb : tail_item(); item < NB;
-       item = item + G < n_static ? item + G : tail_item()) {
-    int si = 0;
-    while (si + 1 < a.tab.n && item >= a.tab.s[si + 1].item_begin) ++si;
-    const DevScene& sc = a.tab.s[si];
+  // Decoder gradients.  H = 64: wave (mg, ng) owns tile (mg, ng) of a hidden
+  // layer, over all hits; H = 32 (one tile) and the output layer: every wave
+  // sums its own hits.
+  f32x16 dwh[NB], dw0 = zero16(), dwo = zero16();
+#pragma unroll
+  for (int l = 0; l < NB; ++l) dwh[l] = zero16();
+  float bs[NH], gob[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int l = 0; l < NH; ++l) bs[l] = 0.0f;
+  float loss_acc = 0.0f;
+
+  int rb = 0, pend_tw = 0;
+  float* pend_grad = nullptr;
+  auto ids = [&](int b) { return reinterpret_cast<int4*>(g_lds + CF::L_ID + b * CF::WIN * 32); };
+  auto us = [&](int b) { return reinterpret_cast<float*>(g_lds + CF::L_U + b * CF::WIN * 12); };
+  auto share = [&](int b) { return reinterpret_cast<uint8_t*>(g_lds + CF::L_SHARE + b * CF::WIN); };
+  // The feature gradients of a window's hits: the lanes of one atomic
+  // instruction cover whole feature rows (lane = channel).  A group of C lanes
+  // takes GH consecutive hits; what a hit adds to a corner that the ray's next
+  // hit has as well is carried over and added there (CornerCarry).
+  constexpr int HW = CF::WIN / kWaves, GH = HW * CF::C / 64;   // hits per wave, per lane group
+  auto scatter = [&](int b) {
+    const int c = lane % CF::C, h0 = HW * wave + GH * (lane / CF::C);
+    const int4* id = ids(b);
+    const float* u = us(b);
+    CornerCarry carry;
+    for (int hh = h0; hh < h0 + GH; ++hh) {
+      if (hh < pend_tw) {
+        const int4 v0 = id[hh], v1 = id[CF::WIN + hh];
+        const int vid[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        float w[8];
+        trilinear(u[hh], u[CF::WIN + hh], u[2 * CF::WIN + hh], w);
+        const float gv = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, c >> 2) + (c & 3) * 4);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) carry.v[j] += w[j] * gv;
+        carry.flush(share(b)[hh], [&](int j, float x) {
+          unsafeAtomicAdd(pend_grad + static_cast<int64_t>(vid[j]) * CF::C + c, x);
+        });
+      }
+    }
+    pend_tw = 0;
+  };
+
+  ItemDeal deal(a.tab, a.item_counter);
+  for (int item = deal.first(scr); item < deal.nb; item = deal.next(item, scr)) {
+    const DevScene& sc = a.tab.s[scene_of(a.tab, item)];
     const ItemRays ir = item_rays(a.tab, sc, item);
     const int64_t r = ir.ray(tid);
     const bool live = tid < ir.n && r < sc.ray_end;
     const int count = live ? a.cnt[r] : 0;
-    // the ray's target (train) or upstream gradient (backward), read before
-    // any window so that no load waits behind pending atomics
+    // the ray's target (train) or upstream gradient (backward)
     float tg0 = 0.0f, tg1 = 0.0f, tg2 = 0.0f, tg3 = 0.0f, tg4 = 0.0f;
     if (CF::MODE == kTrain && live) {
       tg0 = a.t_rgb[3 * r]; tg1 = a.t_rgb[3 * r + 1]; tg2 = a.t_rgb[3 * r + 2]; tg3 = a.t_depth[r];
@@ -502,258 +380,120 @@ __global__ __launch_bounds__(kThreads, CF::BWD ? 1 : 3) void k_shade(ShadeArgs a
     const float h = __int_as_float((128 - sc.depth) << 23);       // 2^(1-depth)
     const float inv_h = __int_as_float((126 + sc.depth) << 23);   // 2^(depth-1)
     int total;
-    // with IMAP all of the item's hits are mapped (hit -> ray lane, slot)
-    // once, as part of the scan
-    const int off = block_excl_scan<kWaves>(count, sm.scr(), total, [&](int o) {
-      if constexpr (CF::IMAP)
-        for (int q = 0; q < count; ++q) sm.hmap()[o + q] = static_cast<typename CF::MapT>(tid | (q << 8));
+    const int off = block_excl_scan<kWaves>(count, scr, total, [&](int o) {
+      for (int q = 0; q < count; ++q) imap[o + q] = static_cast<uint16_t>(tid | (q << 8));
     });
-    float cr = 0.0f, cg = 0.0f, cb = 0.0f, dep = 0.0f, acc = 0.0f;
-
-    // Window: the rays whose hits all fit in [w0, w0 + WIN).  Returns the
-    // window's end; `inw` = this ray is in it.  With the item's map the end
-    // is the start of the ray that holds hit w0 + WIN (no ray is longer than
-    // a window), read without a barrier; otherwise the ray's lane alone
-    // publishes its map entries into window map `hb`.
-    auto open_win = [&](int w0, int hb, bool& inw) -> int {
-      if constexpr (CF::IMAP) {
-        const int p = w0 + CF::WIN;
-        const int w1 = p < total ? p - (sm.hmap()[p] >> 8) : total;
-        inw = count > 0 && off >= w0 && off + count <= w1;
-        return w1;
-      } else {
-        if (tid == 0) sm.scr()[8] = total;
-        __syncthreads();
-        const bool started = count > 0 && off >= w0;
-        inw = started && off + count <= w0 + CF::WIN;
-        if (started && !inw) atomicMin(&sm.scr()[8], off);
-        __syncthreads();
-        const int w1 = sm.scr()[8];
-        if (inw) {
-          for (int q = 0; q < count; ++q)
-            sm.hmap()[hb * CF::WIN + off - w0 + q] = static_cast<typename CF::MapT>(tid | (q << 8));
-        }
-        __syncthreads();
-        return w1;
-      }
-    };
-    // map entry of hit hh of the window starting at w0 (map `hb`)
-    auto map_at = [&](int w0, int hb, int hh) -> int {
-      return sm.hmap()[CF::IMAP ? w0 + hh : hb * CF::WIN + hh];
-    };
-    // Gather in three dependent stages: (A) hit records and rays, (B) the
-    // leaves' corner ids, (C) the 8 corner rows (issued into registers, then
-    // consumed with the trilinear weights into X).  A thread serves GRP hits
-    // (in the backward kernels one group covers the window).  There (PIPE)
-    // windows are opened one ahead: the next window's stage A is issued
-    // before this window's rows are consumed, its stage B after the forward
-    // decoder and its stage C loads after the compositing, so that they are
-    // in flight while this window's backward runs; only an item's first
-    // window waits on all three.
-    constexpr int ROWB = CF::C * CF::EB;
-    constexpr int TPH = ROWB / 16;
-    constexpr int VPT = 16 / CF::EB;             // values per thread
-    constexpr int HPP = kThreads / TPH;
-    constexpr int NPASS = (CF::WIN + HPP - 1) / HPP;
-    constexpr int GRP = (CF::BWD && NPASS >= 2) ? 2 : 1;
-    constexpr bool PIPE = CF::BWD;   // forward kernels: slower so (at their register cap)
-    static_assert(!PIPE || NPASS == GRP, "one gather group per window");
-    const int q = tid % TPH;
-    // raw feature rows of a hit's 8 corners: 16 bytes per corner and thread
-    using Raw = typename std::conditional<CF::BF, uint4, float4>::type;
-    struct Stage {
-      int hh[GRP];
-      bool val[GRP];
-      HitRec hr[GRP];
-      float ro[GRP][3], rd[GRP][3];
-      int4 c0[GRP], c1[GRP];
-    };
-    // one window's raw rows: filled for the next window after this one's
-    // compositing, consumed when the next window starts
-    Raw raw[GRP][8];
-    auto stage_a = [&](Stage& st, int pb, int w0, int hb, int twin) {
-#pragma unroll
-      for (int k = 0; k < GRP; ++k) {
-        st.hh[k] = (pb + k) * HPP + tid / TPH;
-        st.val[k] = st.hh[k] < twin;
-        if (st.val[k]) {
-          const int mp = map_at(w0, hb, st.hh[k]);
-          const int64_t rr = ir.ray(mp & 0xFF);
-          st.hr[k] = a.hits[rr * a.K + (mp >> 8)];
-          st.ro[k][0] = a.o[3 * rr]; st.ro[k][1] = a.o[3 * rr + 1]; st.ro[k][2] = a.o[3 * rr + 2];
-          st.rd[k][0] = a.d[3 * rr]; st.rd[k][1] = a.d[3 * rr + 1]; st.rd[k][2] = a.d[3 * rr + 2];
-        }
-      }
-    };
-    auto stage_b = [&](Stage& st) {
-#pragma unroll
-      for (int k = 0; k < GRP; ++k) {
-        if (st.val[k]) {
-          const int4* lc = reinterpret_cast<const int4*>(sc.leaf_corners + 8 * static_cast<int64_t>(st.hr[k].leaf));
-          st.c0[k] = lc[0];
-          st.c1[k] = lc[1];
-        }
-      }
-    };
-    // (C, issue) the 8 corner rows of each hit into registers
-    auto stage_c_issue = [&](const Stage& st) {
-#pragma unroll
-      for (int k = 0; k < GRP; ++k) {
-        if (!st.val[k]) continue;
-        const int vid[8] = {st.c0[k].x, st.c0[k].y, st.c0[k].z, st.c0[k].w,
-                            st.c1[k].x, st.c1[k].y, st.c1[k].z, st.c1[k].w};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          if constexpr (CF::BF)
-            raw[k][j] = *reinterpret_cast<const uint4*>(sc.feat16 + static_cast<int64_t>(vid[j]) * CF::C + 8 * q);
-          else
-            raw[k][j] = *reinterpret_cast<const float4*>(sc.feat32 + static_cast<int64_t>(vid[j]) * CF::C + 4 * q);
-        }
-      }
-    };
-    // (C, consume) trilinear weights, the hit's LDS record and its row of X
-    auto stage_c_consume = [&](Stage& st) {
-      float v[GRP][VPT];
-#pragma unroll
-      for (int k = 0; k < GRP; ++k) {
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) v[k][i] = 0.0f;
-        if (!st.val[k]) continue;
-        float tm, tml;
-        midpoint2(st.hr[k].tin, st.hr[k].tout, tm, tml);
-        const float lx = -1.0f + static_cast<float>(st.hr[k].ijk & 1023u) * h;
-        const float ly = -1.0f + static_cast<float>((st.hr[k].ijk >> 10) & 1023u) * h;
-        const float lz = -1.0f + static_cast<float>(st.hr[k].ijk >> 20) * h;
-        const float ux = fminf(fmaxf(cell_coord(st.ro[k][0], st.rd[k][0], tm, tml, lx, inv_h), 0.0f), 1.0f);
-        const float uy = fminf(fmaxf(cell_coord(st.ro[k][1], st.rd[k][1], tm, tml, ly, inv_h), 0.0f), 1.0f);
-        const float uz = fminf(fmaxf(cell_coord(st.ro[k][2], st.rd[k][2], tm, tml, lz, inv_h), 0.0f), 1.0f);
-        if (q == 0) {
-          RecL rc;
-          rc.leaf = st.hr[k].leaf;
-          rc.ux = ux;
-          rc.uy = uy;
-          rc.uz = uz;
-          rc.tmid = tm;
-          rc.dt = st.hr[k].tout - st.hr[k].tin;
-          rc.T = 0.0f;
-          rc.pad = 0.0f;
-          rc.v0 = st.c0[k];
-          rc.v1 = st.c1[k];
-          sm.rec(rb)[st.hh[k]] = rc;
-        }
-        const float wx[2] = {1.0f - ux, ux}, wy[2] = {1.0f - uy, uy}, wz[2] = {1.0f - uz, uz};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float wj = wx[j & 1] * wy[(j >> 1) & 1] * wz[j >> 2];
-          if constexpr (CF::BF) {
-            const uint32_t w4[4] = {raw[k][j].x, raw[k][j].y, raw[k][j].z, raw[k][j].w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              v[k][2 * i] += wj * bf16_f32(static_cast<uint16_t>(w4[i] & 0xFFFFu));
-              v[k][2 * i + 1] += wj * bf16_f32(static_cast<uint16_t>(w4[i] >> 16));
-            }
-          } else {
-            const float4 f = raw[k][j];
-            v[k][0] += wj * f.x;
-            v[k][1] += wj * f.y;
-            v[k][2] += wj * f.z;
-            v[k][3] += wj * f.w;
-          }
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < GRP; ++k) {
-        if (st.hh[k] >= CF::WIN) continue;
-        typename CF::Elem* xr = sm.X() + st.hh[k] * CF::XS + VPT * q;
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) xr[i] = to_elem<CF>(v[k][i]);
-        if (CF::CI > CF::C && q == 0) {
-          // view direction (VD) and zero padding up to the K steps
-#pragma unroll
-          for (int i = CF::C; i < CF::CI; ++i) {
-            float xv = 0.0f;
-            if (CF::VD && i < CF::C + 3 && st.val[k]) xv = st.rd[k][i - CF::C];
-            sm.X()[st.hh[k] * CF::XS + i] = to_elem<CF>(xv);
-          }
-        }
-      }
-    };
-    auto stage_c = [&](Stage& st) {
-      stage_c_issue(st);
-      stage_c_consume(st);
-    };
-
-    Stage cur, nxt;
-    int hb = 0;                    // window map of the current window (without IMAP)
-    bool have_next = false;        // nxt holds stages A and B of the next window
-    bool in_win_n = false;
-    int s1n = 0;
-    int s0 = 0;
-    while (s0 < total) {
+    float cr = 0.0f, cg = 0.0f, cb = 0.0f, dep = 0.0f, acc_w = 0.0f;
+    for (int s0 = 0; s0 < total;) {
       bool in_win;
-      int s1;
-      if (have_next) {
-        cur = nxt;
-        in_win = in_win_n;
-        s1 = s1n;
-      } else {
-        s1 = open_win(s0, hb, in_win);
-      }
+      const int s1 = open_window<CF::WIN>(s0, total, off, count, imap, in_win);
+      const uint16_t* wmap = imap + s0;
       const int tw = s1 - s0;
-      const bool pre = PIPE && s1 < total;
-      if (pre) s1n = open_win(s1, hb ^ 1, in_win_n);
-      if (PIPE) {
-        if (!have_next) {
-          stage_a(cur, 0, s0, hb, tw);
-          stage_b(cur);
-          stage_c_issue(cur);
+      const int tp = (tw + 63) & ~63;              // rows that the layers touch
+      // records: one thread per hit
+      if (tid < tp) {
+        float rd[3] = {0.0f, 0.0f, 0.0f};
+        int mp = -1;
+        uint32_t ijk = 0;
+        if (tid < tw) {
+          mp = wmap[tid];
+          const int64_t ray = ir.ray(mp & 0xFF);
+          const HitRec hr = a.hits[ray * a.K + (mp >> 8)];
+          const float ro[3] = {a.o[3 * ray], a.o[3 * ray + 1], a.o[3 * ray + 2]};
+          rd[0] = a.d[3 * ray]; rd[1] = a.d[3 * ray + 1]; rd[2] = a.d[3 * ray + 2];
+          const int4* lc = reinterpret_cast<const int4*>(sc.leaf_corners + 8 * static_cast<int64_t>(hr.leaf));
+          ids(rb)[tid] = lc[0];
+          ids(rb)[CF::WIN + tid] = lc[1];
+          float tm, tml;
+          midpoint2(hr.tin, hr.tout, tm, tml);
+          const float lo[3] = {-1.0f + static_cast<float>(hr.ijk & 1023u) * h,
+                               -1.0f + static_cast<float>((hr.ijk >> 10) & 1023u) * h,
+                               -1.0f + static_cast<float>(hr.ijk >> 20) * h};
+#pragma unroll
+          for (int x = 0; x < 3; ++x)
+            us(rb)[x * CF::WIN + tid] = clamp01(cell_coord(ro[x], rd[x], tm, tml, lo[x], inv_h));
+          out[8 * tid + 6] = tm;
+          out[8 * tid + 7] = hr.tout - hr.tin;
+          ijk = hr.ijk;
         }
-        if (pre) stage_a(nxt, 0, s1, hb ^ 1, s1n - s1);
-        stage_c_consume(cur);
-      } else {
-#pragma unroll 1
-        for (int pb = 0; pb < NPASS; pb += GRP) {
-          stage_a(cur, pb, s0, hb, tw);
-          stage_b(cur);
-          stage_c(cur);
+        if constexpr (CF::BWD) {       // (a lane group's last hit hands nothing on)
+          const uint32_t sh = shared_corners(mp, ijk);
+          share(rb)[tid] = static_cast<uint8_t>((tid & (GH - 1)) == GH - 1 ? 0u : sh);
+        }
+        // view direction and zero padding up to the K steps
+        constexpr int V = kRowVals<BF>;
+        if constexpr (CF::CI > CF::C) {
+          float x[CF::CI - CF::C];
+#pragma unroll
+          for (int i = 0; i < CF::CI - CF::C; ++i) x[i] = CF::VD && i < 3 ? rd[i] : 0.0f;
+#pragma unroll
+          for (int i = 0; i < (CF::CI - CF::C) / V; ++i)
+            *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, tid, CF::C / V + i)) = pack_row<BF>(x + V * i);
         }
       }
       __syncthreads();
-
-      if constexpr (CF::BWD) {
-        if (pend_tw > 0) scatter(pend_tw, pend_grad, sm.rec(rb ^ 1));
-        pend_tw = 0;
+      {
+        // thread q of a hit owns VPT channels of the interpolated feature
+        constexpr int VPT = kRowVals<BF>, TPH = CF::C / VPT, HPP = kThreads / TPH;
+        const int q = tid % TPH;
+#pragma unroll
+        for (int p = 0; p < (CF::WIN + HPP - 1) / HPP; ++p) {
+          const int hh = p * HPP + tid / TPH;
+          if (hh >= tp) break;
+          float v[VPT];
+#pragma unroll
+          for (int i = 0; i < VPT; ++i) v[i] = 0.0f;
+          if (hh < tw) {
+            const int4 v0 = ids(rb)[hh], v1 = ids(rb)[CF::WIN + hh];
+            const int vid[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+            uint4 raw[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) raw[j] = load_row<BF>(sc, 0, static_cast<int64_t>(vid[j]) * CF::C + VPT * q);
+            float w[8];
+            trilinear(us(rb)[hh], us(rb)[CF::WIN + hh], us(rb)[2 * CF::WIN + hh], w);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              float f[VPT];
+              unpack_row<BF>(raw[j], f);
+#pragma unroll
+              for (int i = 0; i < VPT; ++i) v[i] += w[j] * f[i];
+            }
+          }
+          *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, hh, q)) = pack_row<BF>(v);
+        }
       }
+      __syncthreads();
+      if (CF::DEFER && pend_tw > 0) scatter(rb ^ 1);
 
-      // decoder on the window: one 32-hit tile per wave
-      ActTile<CF::BF> act[CF::NH][CF::MTH];
+      hidden_layers<CF>(W, tp, mg, ng, lane);
+      const int t0 = TPW * ng;                     // first tile of this wave's hits
+      const bool mine = 32 * t0 < tp;
+      (void)mine;
+      // output layer, split by hits; per hit the colour, opacity and
+      // transmittance factor of the segment (section 4 footnote, Eq. 3)
       const int n0 = 32 * wave;
-      const bool has_tile = wave < CF::NTILE && n0 < tw;
+      const bool has_tile = wave < CF::NT && n0 < tw;
       if (has_tile) {
-        const f32x16 o = mlp_tile<CF, CF::BWD>(sm, n0, lane, act);
-        // per-hit epilogue, one hit per lane: colour, opacity and
-        // transmittance factor of the segment (section 4 footnote, Eq. 3)
-        if (g == 0 && n0 + lane < tw) {
-          const RecL& rc = sm.rec(rb)[n0 + lane];
-          const float ft = a.tau_mode == SVLF_TAU_VOXEL ? rc.dt * inv_h
-                           : a.tau_mode == SVLF_TAU_WORLD ? rc.dt : 1.0f;
+        const f32x16 o = output_layer<CF>(n0, lane);
+        if (g == 0 && n0 + row < tw) {
+          float* hp = out + 8 * (n0 + row);
+          const float tmid = hp[6], dt = hp[7];
+          const float ft = a.tau_mode == SVLF_TAU_VOXEL ? dt * inv_h
+                           : a.tau_mode == SVLF_TAU_WORLD ? dt : 1.0f;
           const float tau = fmaxf(o[3], 0.0f) * ft;
-          const f32x4 va = {sigmoidf_(o[0]), sigmoidf_(o[1]), sigmoidf_(o[2]), -expm1f(-tau)};
-          const f32x4 vb = {expf(-tau), o[3] > 0.0f ? ft : 0.0f, rc.tmid, 0.0f};
-          *reinterpret_cast<f32x4*>(sm.out() + 8 * (n0 + lane)) = va;
-          *reinterpret_cast<f32x4*>(sm.out() + 8 * (n0 + lane) + 4) = vb;
+          *reinterpret_cast<f32x4*>(hp) = f32x4{sigmoidf_(o[0]), sigmoidf_(o[1]), sigmoidf_(o[2]), -expm1f(-tau)};
+          *reinterpret_cast<f32x4*>(hp + 4) = f32x4{expf(-tau), o[3] > 0.0f ? ft : 0.0f, tmid, 0.0f};
         }
       }
-      if (pre) stage_b(nxt);
       __syncthreads();
 
-      // Eq. 3 front to back (owner lanes), and its backward
-      // Eq. 3 front to back (owner lanes), and its backward
+      // Eq. 3 front to back (owner lanes), and its backward: dL/do, kept
+      // [output][hit] in the operand type
       if (in_win) {
         const int p0 = off - s0;
         float T = 1.0f;
         for (int q = 0; q < count; ++q) {
-          float* hp = sm.out() + 8 * (p0 + q);
+          float* hp = out + 8 * (p0 + q);
           const f32x4 va = *reinterpret_cast<const f32x4*>(hp);
           const f32x4 vb = *reinterpret_cast<const f32x4*>(hp + 4);
           const float w = T * va[3];
@@ -761,8 +501,8 @@ __global__ __launch_bounds__(kThreads, CF::BWD ? 1 : 3) void k_shade(ShadeArgs a
           cg += w * va[1];
           cb += w * va[2];
           dep += w * vb[2];
-          acc += w;
           if constexpr (CF::BWD) hp[7] = T;
+          else acc_w += w;
           T *= vb[0];
         }
         if constexpr (CF::BWD) {
@@ -784,7 +524,7 @@ __global__ __launch_bounds__(kThreads, CF::BWD ? 1 : 3) void k_shade(ShadeArgs a
           }
           float Sr = 0.0f, Sg = 0.0f, Sb = 0.0f, St = 0.0f, Sa = 0.0f;
           for (int q = count - 1; q >= 0; --q) {
-            float* hp = sm.out() + 8 * (p0 + q);
+            const float* hp = out + 8 * (p0 + q);
             const f32x4 va = *reinterpret_cast<const f32x4*>(hp);
             const f32x4 vb = *reinterpret_cast<const f32x4*>(hp + 4);
             const float Tq = vb[3];
@@ -798,301 +538,282 @@ __global__ __launch_bounds__(kThreads, CF::BWD ? 1 : 3) void k_shade(ShadeArgs a
             Sb += w * c2;
             St += w * tm;
             Sa += w;
-            f32x4 go;
-            go[0] = gr * w * c0 * (1.0f - c0);
-            go[1] = gg * w * c1 * (1.0f - c1);
-            go[2] = gb * w * c2 * (1.0f - c2);
-            go[3] = gtau * vb[1];
-            *reinterpret_cast<f32x4*>(hp) = go;
+            const float go[4] = {gr * w * c0 * (1.0f - c0), gg * w * c1 * (1.0f - c1), gb * w * c2 * (1.0f - c2),
+                                 gtau * vb[1]};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const El e = to_el<BF>(go[c]);
+              *reinterpret_cast<El*>(g_lds + CF::L_GO + c * CF::GOS + (p0 + q) * CF::EB) = e;
+              gob[c] += BF ? bf16_f32(static_cast<uint16_t>(e)) : static_cast<float>(e);
+            }
           }
         }
       }
-
       if constexpr (CF::BWD) {
-        // the next window's corner rows: loaded while this window's
-        // backward runs from LDS and registers
-        if (pre) stage_c_issue(nxt);
-        __syncthreads();
-        // output-layer gradient tile (rows 0..3 = dL/do, zero elsewhere)
-        f32x16 gz[CF::MTH];
+        if (tid >= tw && tid < tp) {
 #pragma unroll
-        for (int mt = 0; mt < CF::MTH; ++mt) gz[mt] = zero16();
-        if (has_tile && g == 0 && n0 + lane < tw) {
-          const f32x4 go = *reinterpret_cast<const f32x4*>(sm.out() + 8 * (n0 + lane));
-          gz[0][0] = go[0];
-          gz[0][1] = go[1];
-          gz[0][2] = go[2];
-          gz[0][3] = go[3];
+          for (int c = 0; c < 4; ++c) *reinterpret_cast<El*>(g_lds + CF::L_GO + c * CF::GOS + tid * CF::EB) = to_el<BF>(0.0f);
         }
-        f32x16 gx[1];
-        static_for<CF::NL>([&](auto lc) {
-          constexpr int l = CF::NH - decltype(lc)::value;
-          constexpr int OT = out_w(l, CF::H, CF::NH) / 32;
-          // stage dL/dz_l and the layer input, transposed, for the dW tiles
-          if (wave < CF::NTILE) {
-            if (has_tile) {
-              store_T<CF, OT>(sm.GZ(), gz, n0, lane);
-              if constexpr (l > 0) store_act_T<CF, CF::MTH>(sm.AT(), act[l - 1], n0, lane);
+        __syncthreads();
+
+        // output layer: weight gradient over this wave's hits, then dL/dz of the
+        // last hidden layer in place of its activations (own hits and features)
+        constexpr int ALAST = CF::L_GX;
+        const int ks = (tw + 15) >> 4;               // 16-hit steps with hits
+        const int k0 = 2 * t0, k1 = k0 + 2 * TPW < ks ? k0 + 2 * TPW : ks;
+        if (mine) {
+          const int ln = here(lane), n = ln & 31;
+          for (int k = k0; k < k1; ++k) {
+            if constexpr (BF) {
+              s16x8 b = {0, 0, 0, 0, 0, 0, 0, 0};
+              if (n < 4) b = *reinterpret_cast<const s16x8*>(g_lds + CF::L_GO + n * CF::GOS + (16 * k + 8 * g) * 2);
+              dwo = mma(hits_operand_bf16<CF::ROWH>(ALAST, mg, k, ln), b, dwo);
             } else {
-              // empty tile: zero its columns
-              const int col = n0 + (lane & 31);
-              for (int rr = g; rr < 32 * OT; rr += 2) sm.GZ()[rr * CF::TS + col] = to_elem<CF>(0.0f);
-              if constexpr (l > 0)
-                for (int rr = g; rr < CF::H; rr += 2) sm.AT()[rr * CF::TS + col] = to_elem<CF>(0.0f);
+#pragma unroll
+              for (int j = 0; j < 8; ++j) {
+                const int st = 8 * k + j;
+                const float b = n < 4 ? *reinterpret_cast<const float*>(g_lds + CF::L_GO + n * CF::GOS + (2 * st + g) * 4) : 0.0f;
+                dwo = mma(hits_operand_fp32<CF::ROWH>(ALAST, mg, st, ln), b, dwo);
+              }
             }
           }
-          if constexpr (l == 0)
-            transpose_tile<CF::BF, CF::WIN, CF::XS, CF::TS, CF::CI, CF::CI, kThreads>(sm.X(), sm.AT(), tid);
-          __syncthreads();
-          // owned dW tiles of layer l: K = the window's hits
-          {
-            constexpr int MT = dw_mt(l, CF::H, CF::NH), NT = dw_nt(l, CF::H, CF::CIN);
-            constexpr int T0 = dw_tile_off(l, CF::H, CF::NH, CF::CIN);
-            constexpr int KSTEPS = CF::WIN / CF::KS;
-            static_for<MT * NT>([&](auto tc) {
-              constexpr int t = decltype(tc)::value;
-              constexpr int tau_i = T0 + t, mt = t / NT, nt = t % NT, slot = tau_i / kWaves;
-              if (tau_i % kWaves == wave) {
-                const typename CF::Elem* ga_ = sm.GZ() + (32 * mt + (lane & 31)) * CF::TS;
-                const typename CF::Elem* gb_ = sm.AT() + (32 * nt + (lane & 31)) * CF::TS;
 #pragma unroll
-                for (int s = 0; s < KSTEPS; ++s) {
-                  if constexpr (CF::BF) {
-                    const s16x8 av = *reinterpret_cast<const s16x8*>(ga_ + 16 * s + 8 * g);
-                    const s16x8 bv = *reinterpret_cast<const s16x8*>(gb_ + 16 * s + 8 * g);
-                    dw[slot] = mma(av, bv, dw[slot]);
-                  } else {
-                    dw[slot] = mma(ga_[2 * s + g], gb_[2 * s + g], dw[slot]);
-                  }
-                }
-              }
-            });
-          }
-          {
-            constexpr int RW = out_w(l, CF::H, CF::NH);
-            constexpr int HP = CF::WIN / (kThreads / RW);     // hits per part
-            static_assert(kThreads % RW == 0 && (!CF::BF || HP % 8 == 0), "bias-gradient parts");
-            const int row = tid % RW, pt = tid / RW;
-            if (row < out_real(l, CF::H, CF::NH)) {
-              const typename CF::Elem* gr_ = sm.GZ() + row * CF::TS + pt * HP;
-              float sacc = 0.0f;
-              if constexpr (CF::BF) {
+          for (int t = 0; t < TPW; ++t) {
+            const int hit = 32 * (t0 + t) + (ln & 31);
+            frag_t gb = {0, 0, 0, 0};
+            if (g == 0) {
+              El e[4];
 #pragma unroll
-                for (int hh = 0; hh < HP; hh += 8) {
-                  const s16x8 v = *reinterpret_cast<const s16x8*>(gr_ + hh);
-#pragma unroll
-                  for (int j = 0; j < 8; ++j) sacc += bf16_f32(static_cast<uint16_t>(v[j]));
-                }
+              for (int c = 0; c < 4; ++c) e[c] = *reinterpret_cast<const El*>(g_lds + CF::L_GO + c * CF::GOS + hit * CF::EB);
+              if constexpr (BF) {
+                gb[0] = static_cast<int>(e[0] | (static_cast<uint32_t>(e[1]) << 16));
+                gb[1] = static_cast<int>(e[2] | (static_cast<uint32_t>(e[3]) << 16));
               } else {
 #pragma unroll
-                for (int hh = 0; hh < HP; ++hh) sacc += gr_[hh];
+                for (int c = 0; c < 4; ++c) gb[c] = __float_as_int(e[c]);
               }
-              dbp[l] += sacc;
             }
+            mask_store_tile<BF, CF::ROWH>(ALAST, mg, hit, g, mma_frag<BF>(bo[0], gb, zero16()));
           }
-          // data gradient to the layer input
-          if (has_tile) {
-            if constexpr (l > 0) {
-              f32x16 ga[CF::MTH];
-              bwd_data<CF, l>(sm, gz, ga, lane);
-#pragma unroll
-              for (int mt = 0; mt < CF::MTH; ++mt) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) gz[mt][i] = act[l - 1][mt].positive(i) ? ga[mt][i] : 0.0f;
-              }
-            } else {
-              bwd_data<CF, 0>(sm, gz, gx, lane);
-            }
+        }
+        if constexpr (MG > 1) __syncthreads();
+        // hidden layers, last first: weight gradient (reads the layer's
+        // inputs), then dL/dz of the layer below in place of those inputs.
+        // H = 32: a wave's hits are its own throughout, no barriers.
+        static_for<NH - 1>([&](auto lc) {
+          constexpr int l = NH - 1 - decltype(lc)::value;
+          constexpr int GZ = CF::L_ACT + l * CF::ACT, IN = CF::L_ACT + (l - 1) * CF::ACT;
+          if constexpr (MG > 1) {
+            dw_steps<BF, CF::ROWH, CF::ROWH>(dwh[l - 1], bs[l], GZ, mg, IN, ng, 0, ks, lane);
+            __syncthreads();
+          } else if (mine) {
+            dw_steps<BF, CF::ROWH, CF::ROWH>(dwh[l - 1], bs[l], GZ, 0, IN, 0, k0, k1, lane);
           }
-          __syncthreads();
+          if (mine) {
+            const int ln = here(lane), hit = 32 * t0 + (ln & 31);
+            f32x16 acc[TPW];
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) acc[t] = zero16();
+#pragma unroll
+            for (int i = 0; i < CF::NFH; ++i)
+#pragma unroll
+              for (int t = 0; t < TPW; ++t)
+                acc[t] = mma_frag<BF>(bh[l - 1][i], frag_at<CF::ROWH>(GZ, hit + 32 * t, 2 * i + g), acc[t]);
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) mask_store_tile<BF, CF::ROWH>(IN, mg, hit + 32 * t, g, acc[t]);
+          }
+          if constexpr (MG > 1) __syncthreads();
         });
-        // scatter dL/dx to the 8 corner features of each hit.  dL/dx is
-        // staged through LDS so that the lanes of one atomic instruction
-        // cover whole contiguous feature rows (lane = channel): the memory
-        // system then merges them per cache line instead of issuing one
-        // transaction per lane.
-        float* gxs = reinterpret_cast<float*>(sm.GZ());      // [WIN][C] FP32
+        // input layer: weight gradient; dL/dx of the features, split by hits
+        if constexpr (MG > 1) {
+          if (ng < CF::NTX) dw_steps<BF, CF::ROWH, CF::ROWX>(dw0, bs[0], CF::L_ACT, mg, CF::L_X, ng, 0, ks, lane);
+        } else {
+          if (mine) dw_steps<BF, CF::ROWH, CF::ROWX>(dw0, bs[0], CF::L_ACT, 0, CF::L_X, 0, k0, k1, lane);
+        }
+        f32x16 gx = zero16();
         if (has_tile) {
-          const int row = n0 + (lane & 31);
+          const int ln = here(lane);
+#pragma unroll
+          for (int i = 0; i < CF::NFH; ++i)
+            gx = mma_frag<BF>(*reinterpret_cast<const frag_t*>(g_lds + CF::L_B0 + (i * 64 + ln) * 16),
+                              frag_at<CF::ROWH>(CF::L_ACT, n0 + (ln & 31), 2 * i + g), gx);
+        }
+        if constexpr (MG == 1) __syncthreads();      // the last layer's tile is taken over
+        if (has_tile) {
+          const int hit = n0 + here(row);
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            if (8 * q + 4 * g < CF::C) {
-#pragma unroll
-              for (int p = 0; p < 4; ++p) gxs[row * CF::C + 8 * q + 4 * g + p] = gx[0][4 * q + p];
-            }
+            if (8 * q < CF::C)
+              *reinterpret_cast<frag_t*>(tile_at<CF::ROWG>(CF::L_GX, hit, 2 * q + g)) = pack_chunk<false>(gx, q);
           }
         }
         __syncthreads();
         if (a.gxu != nullptr) {
           // deterministic mode: keep (u, dL/dx) per hit slot; the feature
           // gradient is reduced afterwards in a fixed order
-          if (has_tile) {
-            constexpr int HPI = 64 / CF::C;
-            const int c = lane % CF::C, hs = lane / CF::C;
-            for (int k = 0; k < 32; k += HPI) {
-              const int hh = n0 + k + hs;
-              if (hh < tw) {
-                const RecL rc = sm.rec(rb)[hh];
-                const int mp = map_at(s0, hb, hh);
-                const int64_t slot = ir.ray(mp & 0xFF) * a.K + (mp >> 8);
-                float* rec_out = a.gxu + slot * (CF::C + 4);
-                rec_out[4 + c] = gxs[hh * CF::C + c];
-                if (c < 3) rec_out[c] = c == 0 ? rc.ux : (c == 1 ? rc.uy : rc.uz);
-              }
+          constexpr int HPI = 64 / CF::C;
+          const int c = lane % CF::C, hs = lane / CF::C;
+          for (int k = 0; k < HW; k += HPI) {
+            const int hh = HW * wave + k + hs;
+            if (hh < tw) {
+              const int mp = wmap[hh];
+              float* rec = a.gxu + (ir.ray(mp & 0xFF) * a.K + (mp >> 8)) * (CF::C + 4);
+              rec[4 + c] = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, c >> 2) + (c & 3) * 4);
+              if (c < 3) rec[c] = us(rb)[c * CF::WIN + hh];
             }
           }
         } else {
           pend_tw = tw;
           pend_grad = sc.grad;
-          rb ^= 1;
+          if (CF::DEFER) rb ^= 1;
+          else scatter(rb);
         }
       }
       __syncthreads();
       s0 = s1;
-      have_next = pre;
-      if (pre) hb ^= 1;
     }
 
-    if (live) {
-      if (CF::MODE != kBackward) {
-        if (a.rgb) {
-          a.rgb[3 * r] = cr;
-          a.rgb[3 * r + 1] = cg;
-          a.rgb[3 * r + 2] = cb;
-        }
-        if (a.depth) a.depth[r] = dep;
-        if (a.acc) a.acc[r] = acc;
+    if (CF::MODE != kBackward && live) {
+      if (a.rgb) {
+        a.rgb[3 * r] = cr;
+        a.rgb[3 * r + 1] = cg;
+        a.rgb[3 * r + 2] = cb;
       }
-      if (CF::MODE == kTrain) {
-        const float er = cr - tg0, eg = cg - tg1, eb = cb - tg2, ed = dep - tg3;
-        loss_acc += a.loss_scale * ((er * er + eg * eg + eb * eb) * (1.0f / 3.0f) +
-                                    a.lambda_depth * fabsf(ed));
-      }
+      if (a.depth) a.depth[r] = dep;
+      if (!CF::BWD && a.acc) a.acc[r] = acc_w;
+    }
+    if (CF::MODE == kTrain && live) {
+      const float er = cr - tg0, eg = cg - tg1, eb = cb - tg2, ed = dep - tg3;
+      loss_acc += a.loss_scale * ((er * er + eg * eg + eb * eb) * (1.0f / 3.0f) + a.lambda_depth * fabsf(ed));
     }
   }
-
   if constexpr (CF::BWD) {
-    if (pend_tw > 0) scatter(pend_tw, pend_grad, sm.rec(rb ^ 1));
-    // this block's partial sums of dL/dparams (every entry written once)
-    float* part = a.ws_partials + static_cast<int64_t>(blockIdx.x) * CF::NPARAMS;
-    static_for<CF::NL>([&](auto lc) {
-      constexpr int l = decltype(lc)::value;
-      constexpr int MT = dw_mt(l, CF::H, CF::NH), NT = dw_nt(l, CF::H, CF::CIN);
-      constexpr int T0 = dw_tile_off(l, CF::H, CF::NH, CF::CIN);
-      constexpr int IR = in_real(l, CF::CIN, CF::H), OR = out_real(l, CF::H, CF::NH);
-      static_for<MT * NT>([&](auto tc) {
-        constexpr int t = decltype(tc)::value;
-        constexpr int tau_i = T0 + t, mt = t / NT, nt = t % NT, slot = tau_i / kWaves;
-        if (tau_i % kWaves == wave) {
-          const int col = 32 * nt + (lane & 31);
+    if (CF::DEFER && pend_tw > 0) scatter(rb ^ 1);
+
+    // this block's partial sums of dL/dparams: the waves' shares are added in
+    // LDS in a fixed order, then written out
+    float* pb = reinterpret_cast<float*>(g_lds + CF::L_X);
+    __syncthreads();
+    for (int i = tid; i < CF::NPARAMS; i += kThreads) pb[i] = 0.0f;
+    __syncthreads();
+    const int n = lane & 31;
+    const float gt = block_sum<kWaves>(loss_acc, reinterpret_cast<float*>(scr));
+    for (int p = 0; p < CF::NG; ++p) {
+      if (ng == p) {
+        auto add_tile = [&](const f32x16& dw, int base, int stride, int mt, int col, bool ok) {
+          if (ok) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int rowo = 32 * mt + drow(i, g);
-            if (rowo < OR && col < IR) part[par_w(l, CF::CIN, CF::H, CF::NH) + rowo * IR + col] = dw[slot][i];
+            for (int i = 0; i < 16; ++i) pb[base + (32 * mt + tile_feature<BF>(drow(i, g))) * stride + col] += dw[i];
           }
-        }
-      });
-    });
-    // bias gradients: combine the parts through LDS ([layer][part][row])
-    static_assert(CF::NL * kThreads * 4 <= CF::TROWS * CF::TS * CF::EB, "bias parts fit in GZ");
-    float* bsc = reinterpret_cast<float*>(sm.GZ());
-    __syncthreads();
+        };
+        static_for<NH - 1>([&](auto lc) {
+          constexpr int l = decltype(lc)::value + 1;
+          add_tile(dwh[l - 1], CF::par_w(l), H, mg, (MG > 1 ? 32 * ng : 0) + tile_feature<BF>(n), true);
+        });
+        const int col0 = (MG > 1 ? 32 * ng : 0) + n;
+        add_tile(dw0, CF::par_w(0), CF::CIN, mg, col0, col0 < CF::CIN && (MG == 1 || ng < CF::NTX));
+        if (n < 4) {
 #pragma unroll
-    for (int l = 0; l < CF::NL; ++l) bsc[l * kThreads + tid] = dbp[l];
-    __syncthreads();
-    if (tid < CF::NBIAS) {
-      const int bl = tid / CF::H < CF::NH ? tid / CF::H : CF::NH;
-      const int br = tid - bl * CF::H;
-      static_for<CF::NL>([&](auto lc) {
-        constexpr int l = decltype(lc)::value;
-        constexpr int RW = out_w(l, CF::H, CF::NH);
-        if (l == bl) {
-          float sum = 0.0f;
-#pragma unroll
-          for (int pt = 0; pt < kThreads / RW; ++pt) sum += bsc[l * kThreads + pt * RW + br];
-          part[par_b(l, CF::CIN, CF::H, CF::NH) + br] = sum;
+          for (int i = 0; i < 16; ++i) pb[CF::par_w(NH) + n * H + 32 * mg + tile_feature<BF>(drow(i, g))] += dwo[i];
         }
-      });
+        if (MG == 1 || ng == 0) {
+          static_for<NH>([&](auto lc) {
+            constexpr int l = decltype(lc)::value;
+            const float v = bs[l] + __shfl_xor(bs[l], 32, 64);
+            if (lane < 32) pb[CF::par_b(l) + 32 * mg + tile_feature<BF>(lane)] += v;
+          });
+        }
+      }
+      __syncthreads();
     }
-    if (CF::MODE == kTrain) {
-      const float tot = block_sum<kWaves>(loss_acc, reinterpret_cast<float*>(sm.scr()));
-      if (tid == 0) a.ws_loss[blockIdx.x] = tot;
-    } else if (tid == 0) {
-      a.ws_loss[blockIdx.x] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float v = block_sum<kWaves>(gob[c], reinterpret_cast<float*>(scr));
+      if (tid == 0) pb[CF::par_b(NH) + c] = v;
     }
+    __syncthreads();
+    float* part = a.ws_partials + static_cast<int64_t>(blockIdx.x) * CF::NPARAMS;
+    for (int i = tid; i < CF::NPARAMS; i += kThreads) part[i] = pb[i];
+    if (tid == 0) a.ws_loss[blockIdx.x] = CF::MODE == kTrain ? gt : 0.0f;
   }
 }
 
-// Decoder alone on rows of X (diagnostics / tests): 128 rows per block pass.
+// Decoder alone on rows of X (diagnostics / tests): one window of rows per
+// block pass.
 template <class CF>
 __global__ __launch_bounds__(kThreads) void k_mlp_rows(const float* __restrict__ params,
                                                        const float* __restrict__ X, int64_t n,
                                                        float* __restrict__ out) {
-  const Smem<CF> sm{};
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
-  build_packs<CF>(sm, params);
+  constexpr bool BF = CF::BF;
+  constexpr int V = kRowVals<BF>;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mg = wave % CF::MG, ng = wave / CF::MG;
+  Weights<CF> W;
+  build_packs<CF>(params);
+  W.load(mg, lane);
   __syncthreads();
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * CF::WIN; base < n;
        base += static_cast<int64_t>(gridDim.x) * CF::WIN) {
-    for (int e = tid; e < CF::WIN * CF::CI; e += kThreads) {
-      const int hh = e / CF::CI, c = e % CF::CI;
-      const int64_t row = base + hh;
-      sm.X()[hh * CF::XS + c] = to_elem<CF>((row < n && c < CF::CIN) ? X[row * CF::CIN + c] : 0.0f);
+    for (int e = tid; e < CF::WIN * (CF::CI / V); e += kThreads) {
+      const int hh = e / (CF::CI / V), q = e % (CF::CI / V);
+      const int64_t r = base + hh;
+      float x[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) x[i] = r < n && V * q + i < CF::CIN ? X[r * CF::CIN + V * q + i] : 0.0f;
+      *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, hh, q)) = pack_row<BF>(x);
     }
     __syncthreads();
-    ActTile<CF::BF> act[CF::NH][CF::MTH];
-    if (wave < CF::NTILE) {
-      const int n0 = 32 * wave;
-      const f32x16 o = mlp_tile<CF, false>(sm, n0, lane, act);
-      const int64_t row = base + n0 + (lane & 31);
-      if (g == 0 && row < n) {
-        out[4 * row] = o[0];
-        out[4 * row + 1] = o[1];
-        out[4 * row + 2] = o[2];
-        out[4 * row + 3] = o[3];
+    hidden_layers<CF>(W, CF::WIN, mg, ng, lane);
+    if (wave < CF::NT) {
+      const f32x16 o = output_layer<CF>(32 * wave, lane);
+      const int64_t r = base + 32 * wave + (lane & 31);
+      if (g == 0 && r < n) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) out[4 * r + c] = o[c];
       }
     }
     __syncthreads();
   }
 }
 
-// ------------------------------------------------------------ dispatch
-
-int g_num_cus = 0;
-
 int num_cus() {
-  if (g_num_cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-      g_num_cus = n;
-    else
-      g_num_cus = 256;
+  static int n = 0;
+  if (n == 0) {
+    int dev = 0, v = 0;
+    n = (hipGetDevice(&dev) == hipSuccess &&
+         hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+            ? v
+            : 256;
   }
-  return g_num_cus;
+  return n;
 }
 
 template <class CF>
 hipError_t run(ShadeArgs a, hipStream_t s, int* grid_used) {
   const auto kern = k_shade<CF>;
+  const int lds = CF::lds_bytes(a.K);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, CF::LDS_BYTES);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  // resident blocks per CU: LDS and registers (the persistent grid must fit
-  // in one round, or the blocks of a second round would run after the rest)
-  int per_cu = (160 * 1024) / CF::LDS_BYTES;
-  static int occ = -1;                         // per kernel instance, queried once
-  if (occ < 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                     &occ, reinterpret_cast<const void*>(kern), kThreads, CF::LDS_BYTES) != hipSuccess)
-    occ = 0;
-  if (occ > 0 && occ < per_cu) per_cu = occ;
-  int grid = num_cus() * (per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu));
+  // Resident blocks per CU by registers and LDS (the hit map grows with K): the
+  // persistent grid must fit in one round, or the blocks of a second round
+  // would run after the rest.
+  static int occ[SVLF_MAX_K + 1] = {};
+  if (occ[a.K] == 0) {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(kern), kThreads, lds) !=
+            hipSuccess || n < 1)
+      n = 1;
+    occ[a.K] = n;
+  }
+  int grid = num_cus() * occ[a.K];
   if (grid > shade_grid_limit()) grid = shade_grid_limit();
-  plan_items(&a.tab, grid);
+  plan_items(&a.tab, grid, CF::BWD);
   if (grid > a.tab.n_items) grid = a.tab.n_items;
   if (grid < 1) grid = 1;
   *grid_used = grid;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), CF::LDS_BYTES, s, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, s, a);
   return hipGetLastError();
 }
 
@@ -1108,11 +829,11 @@ hipError_t run_mlp(const float* params, const float* X, int64_t n, float* out, h
   using CF = Cfg<P, C, H, NH, kForward, VD>;
   const auto kern = k_mlp_rows<CF>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, CF::LDS_BYTES);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, CF::lds_bytes(1));
   if (e != hipSuccess) return e;
   int64_t blocks = (n + CF::WIN - 1) / CF::WIN;
   if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), CF::LDS_BYTES, s,
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), CF::lds_bytes(1), s,
                      params, X, n, out);
   return hipGetLastError();
 }

@@ -62,22 +62,29 @@ constexpr int kTraceThreads = 64;    // rays (threads) of a traversal block
 // rays (item j takes rays j, j + items, j + 2 items, ...): consecutive rays hit
 // or miss together, and the launch would wait for the items with the most
 // hits (40,009 rays in 255 items: 2.9 times the mean; spread, within a few
-// percent).  Beyond kBalancedRounds rounds, full items are interleaved (below)
-// and the last rounds are handed out on demand, which balances as well.
-constexpr int kBalancedRounds = 3;
+// percent).  Beyond that many rounds, full items are interleaved (below) and
+// the last rounds are handed out on demand, which balances as well and keeps
+// neighbouring rays together.  The limit is higher in the backward kernels,
+// whose items are long (400,009 rays over three scenes, 3.1 rounds: 470 us
+// with on-demand rounds, 374 us spread; at 8 rounds no difference); forward
+// kernels gain more from neighbours sharing rows in L2 (an 800^2 FP32 view, 4.9
+// rounds: 153 us, spread 172 us; views of up to 3 rounds are 0 to 25% faster
+// spread).
+constexpr int kBalancedRounds = 3, kBalancedRoundsBwd = 6;
 constexpr int kMinItemRays = 16;
 
-inline void plan_items(SceneTable* tab, int blocks) {
+inline void plan_items(SceneTable* tab, int blocks, bool backward) {
+  const int balanced = backward ? kBalancedRoundsBwd : kBalancedRounds;
   const int64_t n = tab->s[tab->n - 1].ray_end - tab->s[0].ray_begin;
   const int64_t round = static_cast<int64_t>(blocks) * kRaysPerBlock;
   const int64_t rounds = (n + round - 1) / round;
   int64_t rays = kRaysPerBlock;
-  if (rounds >= 1 && rounds <= kBalancedRounds) {
+  if (rounds >= 1 && rounds <= balanced) {
     rays = (n + rounds * blocks - 1) / (rounds * blocks);
     if (rays < kMinItemRays) rays = kMinItemRays;
   }
   tab->item_rays = static_cast<int32_t>(rays);
-  tab->spread = rounds <= kBalancedRounds ? 1 : 0;
+  tab->spread = rounds <= balanced ? 1 : 0;
   int64_t items = 0;
   for (int s = 0; s < tab->n; ++s) {
     tab->s[s].item_begin = static_cast<int32_t>(items);

@@ -15,9 +15,19 @@ N_ALL = 70001
 SIZES = (1, 15, 17, 4095, 4097, 12289, 65537)
 
 
-def _inputs():
+MODELS = {  # decoder, hits per ray, view direction
+    "8": ((8, 32, 32, 4), 6, False),
+    "8vd": ((11, 32, 32, 4), 16, True),
+    "16": ((16, 64, 64, 64, 4), 7, False),
+    "32": ((32, 64, 64, 64, 4), 8, False),
+    "32vd": ((35, 64, 64, 64, 4), 16, True),
+    "lf": ((8, 32, 32, 4), 6, False),
+}
+
+
+def _inputs(widths, K, viewdir):
     import torch
-    w = tiny_workload(5, 5, 8, (8, 32, 32, 4), 6)
+    w = tiny_workload(5, 5, widths[0] - (3 if viewdir else 0), widths, K)
     rng = np.random.default_rng(11)
     o = rng.normal(size=(N_ALL, 3))
     o = 3.0 * o / np.linalg.norm(o, axis=1, keepdims=True)
@@ -28,11 +38,11 @@ def _inputs():
 
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
-@pytest.mark.parametrize("model", ["single", "lf"])
+@pytest.mark.parametrize("model", list(MODELS))
 def test_item_sizes(gpu_lib, model, precision):
     import torch
     svlf = gpu_lib
-    w, (o, d, rgb_t, dep_t) = _inputs()
+    w, (o, d, rgb_t, dep_t) = _inputs(*MODELS[model])
     sc = w.scene()
     if model == "lf":
         F, p = lf_inputs(7, sc.n_vertices)
@@ -42,7 +52,7 @@ def test_item_sizes(gpu_lib, model, precision):
         p[-1] = 0.6
         scene = svlf.DeviceScene.from_host(sc.leaf_ijk, sc.depth, w.features())
     params = torch.from_numpy(p).cuda()
-    opts = svlf.make_opts(w.K, "voxel", precision)
+    opts = svlf.make_opts(w.K, "voxel", precision, svlf.FLAG_VIEWDIR if MODELS[model][2] else 0)
 
     def call(lo, counts, grads=True):
         n = sum(counts)
