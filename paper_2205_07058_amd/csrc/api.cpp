@@ -167,9 +167,10 @@ struct CallRange {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace: [hit slots n*K][counts n][per-block dW partials][per-block loss]
-// [work-item counter]
+// [work-item counter].  The live-ray arrays take the last rows of the partials,
+// which no grid reaches (shade_grid_rows()).
 struct WsLayout {
-  size_t hits, cnt, partials, loss, counter, total;
+  size_t hits, cnt, partials, live, loss, counter, total;
 };
 
 WsLayout ws_layout(int64_t n_rays, int K, int64_t n_params) {
@@ -181,6 +182,7 @@ WsLayout ws_layout(int64_t n_rays, int K, int64_t n_params) {
   off = align256(off + static_cast<size_t>(n_rays) * sizeof(int32_t));
   w.partials = off;
   off = align256(off + static_cast<size_t>(shade_grid_limit()) * n_params * sizeof(float));
+  w.live = w.partials + align256(static_cast<size_t>(shade_grid_rows()) * n_params * sizeof(float));
   w.loss = off;
   off = align256(off + static_cast<size_t>(shade_grid_limit()) * sizeof(float));
   w.counter = off;
@@ -300,6 +302,7 @@ int run_shade(int mode, const svlf_scene* scenes, int32_t n_scenes, const int64_
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
+    if (n_scenes == 1 && live_planned(n)) set_live(&a.tab, n, base + w.live);
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
                               const_cast<int32_t*>(a.cnt), a.item_counter,
                               a.item_counter != nullptr ? 1 : 0, s);
@@ -377,9 +380,9 @@ int check_lf_model(const svlf_lf_model* m, const svlf_render_opts* opts, int64_t
 // Workspace: [hit slots][counts][per-hit state][dL/d(o_T0, o_T1)][decoder
 // packs][per-block partials of F_T][of F_C][per-block loss][BF16 calls with
 // a backward pass: the density decoder's input rows per hit slot][work-item
-// counters]
+// counters][live-ray arrays]
 struct LfLayout {
-  size_t hits, cnt, st, gT, packs, partT, partC, loss, xs, ctr, total;
+  size_t hits, cnt, st, gT, packs, partT, partC, loss, xs, ctr, live, total;
 };
 
 LfLayout lf_layout(int64_t n, int K, int precision, int viewdir, bool backward) {
@@ -408,6 +411,8 @@ LfLayout lf_layout(int64_t n, int K, int precision, int viewdir, bool backward) 
     off = align256(off + slots * static_cast<size_t>(lf_x_row()) * sizeof(uint16_t));
   w.ctr = off;
   off = align256(off + 3 * sizeof(int32_t));
+  w.live = off;
+  off = align256(off + live_bytes(n));
   w.total = off;
   return w;
 }
@@ -457,6 +462,7 @@ int run_lf_call(int mode, const svlf_scene* scenes, int32_t n_scenes, const int6
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
+    if (n_scenes == 1 && live_planned(n)) set_live(&a.tab, n, base + w.live);
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
                               const_cast<int32_t*>(a.cnt), a.item_counters, 3, s);
   } else {

@@ -28,8 +28,9 @@
 //    with the hits along K (LDS transpose read in BF16);
 //  * blocks per CU: forward 4 (H = 32), 3 (BF16), 2 (FP32; with 64-hit windows 3
 //    fit, 137 instead of 130 us for an 800^2 view); backward 2.  The FP32
-//    backward with H = 64 needs twice the registers: one block, 64-hit windows,
-//    and a window's atomics are issued after the next window's gather, whose
+//    backward with H = 64 needs twice the registers: one block (two with the
+//    weights read per window took 374 instead of 348 us for a 262,144-ray train
+//    step), and a window's atomics are issued after the next window's gather, whose
 //    loads would otherwise queue behind them;
 //  * a row that consecutive hits of a ray share is added once (CornerCarry).
 // Measured against one 124 KB block per CU with the packs in LDS (2^20 rays, C =
@@ -56,7 +57,7 @@ struct Cfg {
   static constexpr bool BWD = MODE != kForward;
   static constexpr bool NARROW = BF || H == 32;          // a wave's weights take <= 76 registers
   static constexpr bool DEFER = BWD && !NARROW;
-  static constexpr int WIN = NARROW || !BWD ? 128 : 64;
+  static constexpr int WIN = 128;
   static constexpr int BLOCKS = BWD ? (NARROW ? 2 : 1) : (H == 32 ? 4 : NARROW ? 3 : 2);   // per CU, by registers
   static constexpr int NT = WIN / 32;                    // 32-hit tiles
   static constexpr int MG = H / 32, NG = kWaves / MG;    // wave grid
@@ -105,7 +106,8 @@ struct Cfg {
   static constexpr int L_GO = L_OUT + WIN * 32;          // dL/do [4][WIN]
   static constexpr int L_MAP = L_GO + (BWD ? OUT * GOS : 0);   // [256 K] uint16
   static constexpr int lds_bytes(int K) {
-    const int win = L_MAP + kThreads * K * 2, pack = L_X + PACK, part = BWD ? L_X + NPARAMS * 4 : 0;
+    const int map = kThreads * K * 2, live = kLiveItemRays * (K * 2 + 4);   // (live: the item's rays after it)
+    const int win = L_MAP + (map > live ? map : live), pack = L_X + PACK, part = BWD ? L_X + NPARAMS * 4 : 0;
     const int m = win > pack ? win : pack;
     return m > part ? m : part;
   }
@@ -362,12 +364,26 @@ __global__ __launch_bounds__(kThreads, CF::BLOCKS) void k_shade(ShadeArgs a) {
     pend_tw = 0;
   };
 
-  ItemDeal deal(a.tab, a.item_counter);
+  // work items over the live rays, or over all
+  const bool compact = a.tab.live_n != nullptr;
+  LiveRays lr = {};
+  if (compact) lr = live_rays(a.tab, scr);
+  int* ray_ids = reinterpret_cast<int*>(g_lds + CF::L_MAP + kLiveItemRays * a.K * 2);
+  ItemDeal deal(compact ? lr.items : a.tab.n_items, a.item_counter);
   for (int item = deal.first(scr); item < deal.nb; item = deal.next(item, scr)) {
-    const DevScene& sc = a.tab.s[scene_of(a.tab, item)];
+    const DevScene& sc = a.tab.s[compact ? 0 : scene_of(a.tab, item)];
     const ItemRays ir = item_rays(a.tab, sc, item);
-    const int64_t r = ir.ray(tid);
-    const bool live = tid < ir.n && r < sc.ray_end;
+    int64_t r;
+    bool live;
+    if (compact) {
+      const int q = find_rays(a.tab, lr, item, reinterpret_cast<int*>(g_lds + CF::L_X), ray_ids);
+      r = sc.ray_begin + q;
+      live = q >= 0;
+    } else {
+      r = ir.ray(tid);
+      live = tid < ir.n && r < sc.ray_end;
+    }
+    auto ray_of = [&](int lane) { return compact ? sc.ray_begin + ray_ids[lane] : ir.ray(lane); };
     const int count = live ? a.cnt[r] : 0;
     // the ray's target (train) or upstream gradient (backward)
     float tg0 = 0.0f, tg1 = 0.0f, tg2 = 0.0f, tg3 = 0.0f, tg4 = 0.0f;
@@ -397,7 +413,7 @@ __global__ __launch_bounds__(kThreads, CF::BLOCKS) void k_shade(ShadeArgs a) {
         uint32_t ijk = 0;
         if (tid < tw) {
           mp = wmap[tid];
-          const int64_t ray = ir.ray(mp & 0xFF);
+          const int64_t ray = ray_of(mp & 0xFF);
           const HitRec hr = a.hits[ray * a.K + (mp >> 8)];
           const float ro[3] = {a.o[3 * ray], a.o[3 * ray + 1], a.o[3 * ray + 2]};
           rd[0] = a.d[3 * ray]; rd[1] = a.d[3 * ray + 1]; rd[2] = a.d[3 * ray + 2];
@@ -657,7 +673,7 @@ __global__ __launch_bounds__(kThreads, CF::BLOCKS) void k_shade(ShadeArgs a) {
             const int hh = HW * wave + k + hs;
             if (hh < tw) {
               const int mp = wmap[hh];
-              float* rec = a.gxu + (ir.ray(mp & 0xFF) * a.K + (mp >> 8)) * (CF::C + 4);
+              float* rec = a.gxu + (ray_of(mp & 0xFF) * a.K + (mp >> 8)) * (CF::C + 4);
               rec[4 + c] = *reinterpret_cast<const float*>(tile_at<CF::ROWG>(CF::L_GX, hh, c >> 2) + (c & 3) * 4);
               if (c < 3) rec[c] = us(rb)[c * CF::WIN + hh];
             }
@@ -685,6 +701,25 @@ __global__ __launch_bounds__(kThreads, CF::BLOCKS) void k_shade(ShadeArgs a) {
     if (CF::MODE == kTrain && live) {
       const float er = cr - tg0, eg = cg - tg1, eb = cb - tg2, ed = dep - tg3;
       loss_acc += a.loss_scale * ((er * er + eg * eg + eb * eb) * (1.0f / 3.0f) + a.lambda_depth * fabsf(ed));
+    }
+  }
+  // rays without hits that no item took
+  if (compact && CF::MODE != kBackward) {
+    const DevScene& sc = a.tab.s[0];
+    for (int64_t r = sc.ray_begin + static_cast<int64_t>(blockIdx.x) * kThreads + tid; r < sc.ray_end;
+         r += static_cast<int64_t>(gridDim.x) * kThreads) {
+      if (a.cnt[r] != 0) continue;
+      if (a.rgb) {
+        a.rgb[3 * r] = 0.0f;
+        a.rgb[3 * r + 1] = 0.0f;
+        a.rgb[3 * r + 2] = 0.0f;
+      }
+      if (a.depth) a.depth[r] = 0.0f;
+      if (!CF::BWD && a.acc) a.acc[r] = 0.0f;
+      if (CF::MODE == kTrain) {
+        const float er = a.t_rgb[3 * r], eg = a.t_rgb[3 * r + 1], eb = a.t_rgb[3 * r + 2], ed = a.t_depth[r];
+        loss_acc += a.loss_scale * ((er * er + eg * eg + eb * eb) * (1.0f / 3.0f) + a.lambda_depth * fabsf(ed));
+      }
     }
   }
   if constexpr (CF::BWD) {
@@ -808,7 +843,8 @@ hipError_t run(ShadeArgs a, hipStream_t s, int* grid_used) {
     occ[a.K] = n;
   }
   int grid = num_cus() * occ[a.K];
-  if (grid > shade_grid_limit()) grid = shade_grid_limit();
+  const int most = CF::BWD ? shade_grid_rows() : shade_grid_limit();
+  if (grid > most) grid = most;
   plan_items(&a.tab, grid, CF::BWD);
   if (grid > a.tab.n_items) grid = a.tab.n_items;
   if (grid < 1) grid = 1;
@@ -844,7 +880,11 @@ hipError_t run_mlp(const float* params, const float* X, int64_t n, float* out, h
 
 }  // namespace
 
+// The partials' last 128 rows (of at least 1,476 floats) hold the live-ray
+// arrays; up to three blocks per CU of 256 stay below them.
 int shade_grid_limit() { return 1024; }
+int shade_grid_rows() { return 896; }
+static_assert(live_bytes(kMaxLiveRays) + 256 <= 128 * 1476 * sizeof(float), "live-ray arrays");
 
 hipError_t launch_shade(const ShadeArgs& a, int mode, hipStream_t s, int* grid_used) {
   *grid_used = 0;

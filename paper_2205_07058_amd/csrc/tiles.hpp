@@ -32,8 +32,8 @@ extern __shared__ __attribute__((aligned(16))) char g_lds[];
 struct ItemDeal {
   int G, lb, nb, n_static;
   int32_t* counter;
-  __device__ __forceinline__ ItemDeal(const SceneTable& tab, int32_t* item_counter)
-      : G(gridDim.x), nb(tab.n_items), counter(item_counter) {
+  __device__ __forceinline__ ItemDeal(int n_items, int32_t* item_counter)
+      : G(gridDim.x), nb(n_items), counter(item_counter) {
     const int b = blockIdx.x;
     lb = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
     const int n_tail = counter != nullptr ? (nb < 2 * G ? nb : 2 * G) : 0;
@@ -50,6 +50,125 @@ struct ItemDeal {
     return it;
   }
 };
+// Work items over the live rays of a call (SceneTable::live_n): item i takes
+// live rays [i rays, (i + 1) rays) in ray order, rays = what gives every
+// block the same number of items of at most kLiveItemRays.  Every ray of an
+// item has hits, so items carry nearly the same number of hits and fill their
+// windows, where items over all rays carry what their rays happen to hit
+// (random rays, a fifth of them live with seven hits each: 1.4 times the mean
+// in the fullest of 255 items, windows two thirds full).
+// Each block counts the live rays itself, from one byte per traversal block
+// (16 KB for 2^20 rays), and finds an item's rays by their rank: the thread's
+// stretch of bytes by bisection over the stretches' prefix sums, the traversal
+// block by its bytes, the ray by its bit.
+struct LiveRays {
+  int items, rays;        // work items, rays of an item
+  int total;              // live rays
+  int pre, stretch;       // live rays before this thread's traversal blocks; blocks per thread
+};
+
+__device__ __forceinline__ uint32_t byte_sum(const uint4& v) {
+  uint32_t s = __builtin_amdgcn_sad_u8(v.x, 0u, 0u);
+  s = __builtin_amdgcn_sad_u8(v.y, 0u, s);
+  s = __builtin_amdgcn_sad_u8(v.z, 0u, s);
+  return __builtin_amdgcn_sad_u8(v.w, 0u, s);
+}
+
+// Called by all threads; ends with a barrier.
+__device__ __forceinline__ LiveRays live_rays(const SceneTable& tab, int* scr) {
+  LiveRays lr;
+  const int n = tab.n_trace, G = gridDim.x;
+  lr.stretch = (n + 4095) / 4096 * 16;
+  const int w0 = static_cast<int>(threadIdx.x) * lr.stretch;
+  uint32_t s = 0;
+  for (int w = w0; w < w0 + lr.stretch && w < n; w += 16) {
+    uint4 v = *reinterpret_cast<const uint4*>(tab.live_n + w);
+    auto keep = [&](int k) {           // bytes of the 4 from w + 4 k that are below n
+      const int left = n - w - 4 * k;
+      return left >= 4 ? ~0u : left <= 0 ? 0u : (1u << (8 * left)) - 1u;
+    };
+    v.x &= keep(0);
+    v.y &= keep(1);
+    v.z &= keep(2);
+    v.w &= keep(3);
+    s += byte_sum(v);
+  }
+  lr.pre = block_excl_scan<kWaves>(static_cast<int>(s), scr, lr.total);
+  const int round = G * kLiveItemRays;
+  const int rounds = lr.total > 0 ? (lr.total + round - 1) / round : 1;
+  lr.rays = lr.total > 0 ? (lr.total + G * rounds - 1) / (G * rounds) : 1;
+  lr.items = (lr.total + lr.rays - 1) / lr.rays;
+  return lr;
+}
+
+// The rays of an item, relative to the scene's first: thread t gets the
+// item's ray t, or -1, and ids[t] holds it for the block after its next
+// barrier.  Called by all threads; `prefix` (1 KB) is free again after the
+// block's next barrier.
+__device__ __forceinline__ int find_rays(const SceneTable& tab, const LiveRays& lr, int item, int* prefix,
+                                         int* ids) {
+  const int tid = threadIdx.x, rank = item * lr.rays + tid;
+  prefix[tid] = lr.pre;
+  __syncthreads();
+  int r = -1;
+  if (tid < lr.rays && rank < lr.total) {
+    int t = 0;                         // last stretch that starts at or before the rank
+#pragma unroll
+    for (int step = kThreads / 2; step > 0; step >>= 1)
+      if (prefix[t + step] <= rank) t += step;
+    int i = rank - prefix[t], w = t * lr.stretch;
+    const int end = w + lr.stretch;
+    uint4 v = *reinterpret_cast<const uint4*>(tab.live_n + w);
+    for (int s = byte_sum(v); i >= s && w + 16 < end; s = byte_sum(v)) {
+      i -= s;
+      w += 16;
+      v = *reinterpret_cast<const uint4*>(tab.live_n + w);
+    }
+    const uint32_t q[4] = {v.x, v.y, v.z, v.w};
+    uint32_t x = q[0];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int s = __builtin_amdgcn_sad_u8(q[k], 0u, 0u);
+      if (w % 16 == 4 * k && i >= s) {
+        i -= s;
+        w += 4;
+        x = q[k + 1];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int s = static_cast<int>(x & 0xFFu);
+      if (w % 4 == k && i >= s) {
+        i -= s;
+        ++w;
+        x >>= 8;
+      }
+    }
+    // bit i (from 0) of the mask's set bits
+    const uint64_t m = tab.live_mask[w];
+    uint32_t b = static_cast<uint32_t>(m);
+    int bit = 0;
+    const int lo = __popc(b);
+    if (i >= lo) {
+      i -= lo;
+      bit = 32;
+      b = static_cast<uint32_t>(m >> 32);
+    }
+#pragma unroll
+    for (int step = 16; step > 0; step >>= 1) {
+      const int c = __popc(b & ((1u << step) - 1u));
+      if (i >= c) {
+        i -= c;
+        bit += step;
+        b >>= step;
+      }
+    }
+    r = 64 * w + bit;
+  }
+  if (tid < kLiveItemRays) ids[tid] = r;
+  return r;
+}
+
 // Hit window [s0, s1): the rays whose hits all fit in [s0, s0 + WIN), from the
 // map of the item's hits (hit -> lane | slot << 8, written once per item): the
 // window ends at the start of the ray that holds hit s0 + WIN (no ray is longer

@@ -95,6 +95,13 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace_internal(
                      });
   }
   cnt_out[r] = count;
+  if (tab.live_n != nullptr) {
+    const uint64_t m = __ballot(count > 0);
+    if (threadIdx.x == 0) {
+      tab.live_n[b] = static_cast<uint8_t>(__popcll(m));
+      tab.live_mask[b] = m;
+    }
+  }
 }
 
 size_t stack_bytes(int depth) {
