@@ -302,7 +302,9 @@ int run_shade(int mode, const svlf_scene* scenes, int32_t n_scenes, const int64_
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
-    if (n_scenes == 1 && live_planned(n)) set_live(&a.tab, n, base + w.live);
+    // (deterministic: items over all rays, so that a call on reused hits, which
+    // has no live-ray arrays, groups the decoder-gradient partials alike)
+    if (n_scenes == 1 && live_planned(n) && !det) set_live(&a.tab, n, base + w.live);
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
                               const_cast<int32_t*>(a.cnt), a.item_counter,
                               a.item_counter != nullptr ? 1 : 0, s);

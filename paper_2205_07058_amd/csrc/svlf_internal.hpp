@@ -55,8 +55,9 @@ struct SceneTable {
 // that reuses hits may take them from a call of another decoder, whose
 // workspace has these arrays elsewhere.)  Measured, all rays -> live rays:
 // 640,000-ray FP32 view 172 -> 155 us, 2,560,000-ray BF16 view 484 -> 457, FP32
-// train step of 262,144 rays 361 -> 262, BF16 of 2^20 1226 -> 1167, 100,003
-// deterministic 384 -> 377.
+// train step of 262,144 rays 361 -> 262, BF16 of 2^20 1226 -> 1167.
+// Deterministic calls keep items over all rays (100,003 rays: 384 us, 377 over
+// live rays), so that they give the same bits on their own and on reused hits.
 constexpr int64_t kMinLiveRays = 1 << 15, kMaxLiveRays = 1 << 22;
 constexpr bool live_planned(int64_t n) { return n >= kMinLiveRays && n <= kMaxLiveRays; }
 constexpr int kLiveItemRays = 128;   // most live rays of a work item

@@ -85,3 +85,34 @@ def test_live_plan(gpu_lib, model, n, pattern):
             assert torch.equal(x, y), i
         else:
             assert (x - y).abs().max() <= 1e-4 * y.abs().max(), i
+
+
+def test_deterministic_same_bits_on_reused_hits(gpu_lib):
+    """A deterministic train step gives the same bits whether it traverses
+    the rays itself or reuses the hits of an earlier call."""
+    import torch
+    svlf = gpu_lib
+    n, K = 40009, 5
+    w = tiny_workload(5, 5, 8, (8, 32, 32, 4), K)
+    sc = w.scene()
+    rng = np.random.default_rng(3)
+    o = rng.normal(size=(n, 3))
+    o = 3.0 * o / np.linalg.norm(o, axis=1, keepdims=True)
+    d = rng.uniform(-0.3, 0.3, (n, 3)) - o
+    d[rng.random(n) < 0.8] *= -1.0
+    t = rng.uniform(0, 1, (n, 4))
+    o, d, rgb_t, dep_t = [torch.from_numpy(np.ascontiguousarray(x, np.float32)).cuda()
+                          for x in (o, d, t[:, :3], 3 * t[:, 3])]
+    scene = svlf.DeviceScene.from_host(sc.leaf_ijk, sc.depth, w.features())
+    params = torch.from_numpy(w.params()).cuda()
+    ws = svlf.Workspace()
+    got = []
+    for flags in (0, svlf.FLAG_REUSE_HITS):
+        gF, gp, loss = torch.zeros_like(scene.features), torch.zeros_like(params), torch.zeros(1, device="cuda")
+        opts = svlf.make_opts(K, "voxel", "fp32", svlf.FLAG_DETERMINISTIC | flags)
+        svlf.train_step([scene], [n], params, w.widths, opts, o, d, rgb_t, dep_t, 0.1, 1.0 / n, [gF], gp,
+                        loss_out=loss, workspace=ws)
+        got.append((gF, gp, loss))
+    assert got[0][0].abs().max() > 0
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
