@@ -168,9 +168,12 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace: [hit slots n*K][counts n][per-block dW partials][per-block loss]
 // [work-item counter].  The live-ray arrays take the last rows of the partials,
-// which no grid reaches (shade_grid_rows()).
+// which no grid reaches (shade_grid_rows()).  Rows of a decoder that no kernel
+// serves may be too short for them (8-32-4 has 420 parameters; such a call still
+// traverses, and with SVLF_FLAG_TRACE_ONLY that is all it does).
 struct WsLayout {
   size_t hits, cnt, partials, live, loss, counter, total;
+  bool fits_live(int64_t n) const { return live + live_bytes(n) <= loss; }
 };
 
 WsLayout ws_layout(int64_t n_rays, int K, int64_t n_params) {
@@ -304,7 +307,7 @@ int run_shade(int mode, const svlf_scene* scenes, int32_t n_scenes, const int64_
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
     // (deterministic: items over all rays, so that a call on reused hits, which
     // has no live-ray arrays, groups the decoder-gradient partials alike)
-    if (n_scenes == 1 && live_planned(n) && !det) set_live(&a.tab, n, base + w.live);
+    if (n_scenes == 1 && live_planned(n) && !det && w.fits_live(n)) set_live(&a.tab, n, base + w.live);
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
                               const_cast<int32_t*>(a.cnt), a.item_counter,
                               a.item_counter != nullptr ? 1 : 0, s);
