@@ -61,9 +61,12 @@ struct SceneTable {
 constexpr int64_t kMinLiveRays = 1 << 15, kMaxLiveRays = 1 << 22;
 constexpr bool live_planned(int64_t n) { return n >= kMinLiveRays && n <= kMaxLiveRays; }
 constexpr int kLiveItemRays = 128;   // most live rays of a work item
-constexpr size_t live_bytes(int64_t n) {   // live_n padded to 16 bytes per thread of a block, then live_mask
-  const int64_t waves = (n + 63) / 64;
-  return !live_planned(n) ? 0 : static_cast<size_t>((waves + 4095) / 4096 * 4096 + waves * 8);
+// Room for them: live_n padded to 16 bytes per thread of a block, then live_mask.
+// Calls past the range keep the largest size, so that a workspace sized for some
+// rays serves every call with fewer.
+constexpr size_t live_bytes(int64_t n) {
+  const int64_t waves = ((n < kMaxLiveRays ? n : kMaxLiveRays) + 63) / 64;
+  return n < kMinLiveRays ? 0 : static_cast<size_t>((waves + 4095) / 4096 * 4096 + waves * 8);
 }
 inline void set_live(SceneTable* tab, int64_t n, void* p) {
   tab->live_n = static_cast<uint8_t*>(p);

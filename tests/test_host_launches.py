@@ -75,3 +75,24 @@ def test_live_arrays_inside_the_workspace(rec, widths, n, flags):
     assert rec.rec_live_traces() == 1 or not served
     if rec.rec_live_traces():
         assert FAKE <= rec.rec_live_begin() and rec.rec_live_end() <= FAKE + size
+
+
+def _lf_model():
+    m = svlf.LfModel()
+    m.c_density, m.c_color, m.hidden, m.n_hidden_density, m.n_hidden_color = svlf.LF_DECODERS
+    m.params = FAKE
+    return m
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("K", [1, 8, 16])
+@pytest.mark.parametrize("call", ["render", "lf_render", "lf"])
+def test_workspace_size_grows_with_the_rays(rec, call, K, precision):
+    """A workspace sized for some rays serves every call with fewer."""
+    opts = svlf.make_opts(K, "voxel", precision)
+    m, query = (_mlp((8, 32, 32, 4)), rec.svlf_workspace_bytes) if call == "render" else (
+        _lf_model(), getattr(rec, f"svlf_{call}_workspace_bytes"))
+    edges = [1, 64, 4096, 1 << 15, 1 << 18, 1 << 20, 1 << 22, (1 << 22) + 1345, (1 << 22) + 9857, 1 << 23]
+    ns = sorted({e + k for e in edges for k in (-64, -1, 0, 1, 63, 64) if e + k > 0})
+    sizes = [query(ct.byref(m), ct.byref(opts), n) for n in ns]
+    assert all(0 < a <= b for a, b in zip(sizes, sizes[1:])), [n for n, a, b in zip(ns, sizes, sizes[1:]) if a > b]
