@@ -385,7 +385,8 @@ int check_lf_model(const svlf_lf_model* m, const svlf_render_opts* opts, int64_t
 // Workspace: [hit slots][counts][per-hit state][dL/d(o_T0, o_T1)][decoder
 // packs][per-block partials of F_T][of F_C][per-block loss][BF16 calls with
 // a backward pass: the density decoder's input rows per hit slot][work-item
-// counters][live-ray arrays]
+// counters][calls with a backward pass: live-ray arrays (the forward kernels take
+// items over all rays)]
 struct LfLayout {
   size_t hits, cnt, st, gT, packs, partT, partC, loss, xs, ctr, live, total;
 };
@@ -417,7 +418,7 @@ LfLayout lf_layout(int64_t n, int K, int precision, int viewdir, bool backward) 
   w.ctr = off;
   off = align256(off + 3 * sizeof(int32_t));
   w.live = off;
-  off = align256(off + live_bytes(n));
+  if (backward) off = align256(off + live_bytes(n));
   w.total = off;
   return w;
 }
@@ -467,7 +468,7 @@ int run_lf_call(int mode, const svlf_scene* scenes, int32_t n_scenes, const int6
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
-    if (n_scenes == 1 && live_planned(n)) set_live(&a.tab, n, base + w.live);
+    if (need_grads && n_scenes == 1 && live_planned(n)) set_live(&a.tab, n, base + w.live);
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
                               const_cast<int32_t*>(a.cnt), a.item_counters, 3, s);
   } else {

@@ -96,3 +96,21 @@ def test_workspace_size_grows_with_the_rays(rec, call, K, precision):
     ns = sorted({e + k for e in edges for k in (-64, -1, 0, 1, 63, 64) if e + k > 0})
     sizes = [query(ct.byref(m), ct.byref(opts), n) for n in ns]
     assert all(0 < a <= b for a, b in zip(sizes, sizes[1:])), [n for n, a, b in zip(ns, sizes, sizes[1:]) if a > b]
+
+
+@pytest.mark.parametrize("n", [40009, 1 << 18])
+def test_lf_render_makes_no_live_arrays(rec, n):
+    """The light field's forward kernels take items over all rays: a render neither asks for room for the
+    live-ray arrays nor has the traversal write them; a backward pass does both."""
+    m, opts, offs = _lf_model(), svlf.make_opts(4, "direct", "fp32"), (ct.c_int64 * 2)(0, n)
+    args = (_scene(), 1, offs, ct.byref(m), ct.byref(opts), FAKE, FAKE)
+    size = rec.svlf_lf_render_workspace_bytes(ct.byref(m), ct.byref(opts), n)
+    rec.rec_reset()
+    assert rec.svlf_lf_render(*args, FAKE, FAKE, FAKE, FAKE, size, None) == svlf.OK
+    assert (rec.rec_traces(), rec.rec_live_traces()) == (1, 0)
+    full = rec.svlf_lf_workspace_bytes(ct.byref(m), ct.byref(opts), n)
+    assert full - size >= (n + 63) // 64 * 9
+    rec.rec_reset()
+    assert rec.svlf_lf_render_backward(*args, FAKE, FAKE, FAKE, (ct.c_void_p * 1)(FAKE), FAKE, FAKE, full, None) == svlf.OK
+    assert (rec.rec_traces(), rec.rec_live_traces()) == (1, 1)
+    assert FAKE <= rec.rec_live_begin() and rec.rec_live_end() <= FAKE + full
