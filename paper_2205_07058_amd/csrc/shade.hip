@@ -39,6 +39,8 @@
 // BF16 view 388 -> 360 us; backward of 20,011 rays at H = 32 FP32 63 -> 33 us.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "svlf_internal.hpp"
 #include "tiles.hpp"
 
@@ -828,21 +830,23 @@ template <class CF>
 hipError_t run(ShadeArgs a, hipStream_t s, int* grid_used) {
   const auto kern = k_shade<CF>;
   const int lds = CF::lds_bytes(a.K);
+  // (the limit is the process's: one value for every K, so that threads cannot
+  // lower it between each other's set and launch)
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, CF::lds_bytes(SVLF_MAX_K));
   if (e != hipSuccess) return e;
   // Resident blocks per CU by registers and LDS (the hit map grows with K): the
   // persistent grid must fit in one round, or the blocks of a second round
   // would run after the rest.
-  static int occ[SVLF_MAX_K + 1] = {};
-  if (occ[a.K] == 0) {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(kern), kThreads, lds) !=
-            hipSuccess || n < 1)
-      n = 1;
-    occ[a.K] = n;
+  static std::atomic<int> occ[SVLF_MAX_K + 1];
+  int per_cu = occ[a.K].load(std::memory_order_relaxed);
+  if (per_cu == 0) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), kThreads, lds) !=
+            hipSuccess || per_cu < 1)
+      per_cu = 1;
+    occ[a.K].store(per_cu, std::memory_order_relaxed);
   }
-  int grid = num_cus() * occ[a.K];
+  int grid = num_cus() * per_cu;
   const int most = CF::BWD ? shade_grid_rows() : shade_grid_limit();
   if (grid > most) grid = most;
   plan_items(&a.tab, grid, CF::BWD);

@@ -114,3 +114,13 @@ def test_lf_render_makes_no_live_arrays(rec, n):
     assert rec.svlf_lf_render_backward(*args, FAKE, FAKE, FAKE, (ct.c_void_p * 1)(FAKE), FAKE, FAKE, full, None) == svlf.OK
     assert (rec.rec_traces(), rec.rec_live_traces()) == (1, 1)
     assert FAKE <= rec.rec_live_begin() and rec.rec_live_end() <= FAKE + full
+
+
+def test_lds_limit_does_not_depend_on_the_call(rec):
+    """A kernel's dynamic-LDS limit is state of the process: threads that launch the same kernel with different K
+    must not set it to different values between each other's set and launch."""
+    rec.rec_reset()
+    for widths in ((8, 32, 32, 4), (16, 64, 64, 64, 4), (32, 64, 64, 64, 4)):
+        for K in (16, 1, 9):
+            assert _render(rec, widths, 4096, K=K)[0] == svlf.OK
+            assert rec.rec_lds_limit_changes() == 0, (widths, K)
