@@ -258,30 +258,33 @@ __device__ __forceinline__ void layer_mma(const f32x16& init, const frag_t (&w)[
 // dw[nt] += (tile ta of A)^T x (tile nt of B) over the window's hits (hits from
 // tw to the next multiple of 16 are zero in one of the two and finite in the
 // other); bs += the sum of A's row (the bias gradient, half of the hits in
-// each lane group).
+// each lane group), added up by step and window first: bs runs over the whole
+// launch.
 template <bool BF, int ROWA, int ROWB, int NT>
 __device__ __forceinline__ void dw_mma(f32x16 (&dw)[NT], float& bs, int base_a, int ta, int base_b, int tw, int lane) {
   lane = here(lane);
+  float win = 0.0f;
 #pragma unroll 1
   for (int k = 0; k < (tw + 15) >> 4; ++k) {
+    float sum = 0.0f;
     if constexpr (BF) {
       const s16x8 a = hits_operand_bf16<ROWA>(base_a, ta, k, lane);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) dw[nt] = mma(a, hits_operand_bf16<ROWB>(base_b, nt, k, lane), dw[nt]);
-      float sum = 0.0f;
 #pragma unroll
       for (int j = 0; j < 8; ++j) sum += bf16_f32(static_cast<uint16_t>(a[j]));
-      bs += sum;
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const float a = hits_operand_fp32<ROWA>(base_a, ta, 8 * k + j, lane);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) dw[nt] = mma(a, hits_operand_fp32<ROWB>(base_b, nt, 8 * k + j, lane), dw[nt]);
-        bs += a;
+        sum += a;
       }
     }
+    win += sum;
   }
+  bs += win;
 }
 
 // The output layer's gradients are kept [output][hit] (row stride GOS bytes) as

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kThreads) void k_fill(float* __restrict__ d, float 
 // rows over 16 sums, added up pairwise, and the four quarter sums are then added
 // in order: a fixed summation order for any launch.  (One running sum per quarter
 // is 64 to 224 additions long at 256 to 896 rows: for 512 equal rows 30 x 2^-24
-// off, 3.5 so; 8.8 against 6.2 us for 1,671 columns, the loads being in flight at
+// off, 3.5 so; 8.8 against 6.2 us for 1,572 columns, the loads being in flight at
 // once.)  Block 0 also sums the loss partials.
 constexpr int kRedCols = 64;
 __global__ __launch_bounds__(kThreads) void k_reduce(const float* __restrict__ part, int rows,

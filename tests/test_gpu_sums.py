@@ -29,10 +29,14 @@ def _bias_entries(widths, at=0):
     return out, at
 
 
-# model, rays, hits of a window, most windows of a block (items stay on their
-# blocks), most rows of partials
+# model, rays, hits of a window, most windows of a block per 256 blocks
+# (deterministic: items stay on their blocks; light field: the last two of 8
+# rounds of items go to whichever block is free, so up to four times a block's
+# share), most rows of partials
 CASES = {
+    "16": ((16, 64, 64, 64, 4), 1 << 19, 128, 16, 512),
     "8": ((8, 32, 32, 4), 8192, 16, 1, 512),
+    "lf": (None, 1 << 18, 64, 4 * 16, 256),
 }
 
 
