@@ -126,6 +126,16 @@ inline void plan_items(SceneTable* tab, int blocks, bool backward) {
   tab->n_items = static_cast<int32_t>(items);
 }
 
+// Work items that are dealt to fixed blocks of a grid; the rest, up to two rounds,
+// are handed out on demand, as blocks become free.  The first round never is: all
+// blocks ask at once, and the one counter serves them one after the other before
+// any has an item (a 65,536-ray C = 8 BF16 render on reused hits: 33 us, 27 so,
+// where the same items on a quarter of the blocks took 28).
+__host__ __device__ constexpr int dealt_items(int n_items, int blocks) {
+  const int first = n_items < blocks ? n_items : blocks, all_but_two = n_items - 2 * blocks;
+  return all_but_two > first ? all_but_two : first;
+}
+
 // Rays of one work item.  The rays of kIlvItems consecutive full
 // kRaysPerBlock-ray items of a scene are interleaved: item j of such a group
 // takes rays j, j + kIlvItems, j + 2 kIlvItems, ... of the group, so that one

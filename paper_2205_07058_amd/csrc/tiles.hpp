@@ -24,8 +24,8 @@ constexpr int kWaves = 4;
 extern __shared__ __attribute__((aligned(16))) char g_lds[];
 
 // Work items of a persistent kernel: dealt round-robin over the grid, except
-// the last two rounds, which `counter` hands out in order to whichever block
-// asks first (null: none).  The logical block index groups the blocks of one
+// the last of them (dealt_items), which `counter` hands out in order to whichever
+// block asks first (null: none).  The logical block index groups the blocks of one
 // XCD (hardware places block b on XCD b % 8), so that each XCD works on
 // neighbouring rays in every round and shares their features in its L2.
 // Uniform over the block; scr[10] carries the counter's value.
@@ -36,8 +36,7 @@ struct ItemDeal {
       : G(gridDim.x), nb(n_items), counter(item_counter) {
     const int b = blockIdx.x;
     lb = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
-    const int n_tail = counter != nullptr ? (nb < 2 * G ? nb : 2 * G) : 0;
-    n_static = nb - n_tail;
+    n_static = counter != nullptr ? dealt_items(nb, G) : nb;
   }
   __device__ int first(int* scr) { return lb < n_static ? lb : tail(scr); }
   __device__ int next(int item, int* scr) { return item + G < n_static ? item + G : tail(scr); }

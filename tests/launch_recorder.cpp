@@ -39,6 +39,7 @@ int rec_live_traces() { return g_rec.live_traces; }
 int rec_lds_limit_changes() { return g_rec.lds_limit_changes; }
 uint64_t rec_live_begin() { return g_rec.live_begin; }
 uint64_t rec_live_end() { return g_rec.live_end; }
+int rec_dealt_items(int n_items, int blocks) { return svlf::dealt_items(n_items, blocks); }
 
 void** __hipRegisterFatBinary(const void*) {
   static void* handle;

@@ -124,3 +124,14 @@ def test_lds_limit_does_not_depend_on_the_call(rec):
         for K in (16, 1, 9):
             assert _render(rec, widths, 4096, K=K)[0] == svlf.OK
             assert rec.rec_lds_limit_changes() == 0, (widths, K)
+
+
+def test_first_round_of_items_is_dealt(rec):
+    """Blocks start on items of their own: the counter that hands out the last two rounds would serve all blocks of
+    the first round one after the other."""
+    for blocks in (1, 7, 256, 896):
+        for n in (0, 1, blocks - 1, blocks, blocks + 1, 2 * blocks, 3 * blocks - 1, 3 * blocks, 3 * blocks + 1,
+                  20 * blocks + 3):
+            dealt = rec.rec_dealt_items(n, blocks)
+            assert min(n, blocks) <= dealt <= n and n - dealt <= 2 * blocks
+            assert n < 3 * blocks or dealt == n - 2 * blocks
