@@ -25,7 +25,9 @@
 //    registers, built through LDS once per launch;
 //  * activations are LDS tiles that are MFMA operands as stored (tiles.hpp),
 //    dL/dz replaces them in place, and weight gradients read the same tiles
-//    with the hits along K (LDS transpose read in BF16);
+//    with the hits along K (LDS transpose read in BF16).  Forward with H = 32 a
+//    lane would read back just what it stored, so they stay in registers (a
+//    2200^2 FP32 view, C = 8: 592 us of shading through LDS, 495 so);
 //  * blocks per CU: forward 4 (H = 32), 3 (BF16), 2 (FP32; with 64-hit windows 3
 //    fit, 137 instead of 130 us for an 800^2 view); backward 2.  The FP32
 //    backward with H = 64 needs twice the registers: one block (two with the
@@ -70,7 +72,8 @@ struct Cfg {
   static_assert(TPW >= 1 && MG * NG == kWaves && NTX <= (NG > 1 ? 2 : 1), "wave grid");
   static_assert(C <= 32 && (H == 64 || NTX == 1), "input layer");
   // parameters
-  static constexpr int NACT = BWD ? NH : 1;              // forward: each layer takes the previous one's place
+  static constexpr bool REG = MG == 1 && !BWD;           // activations stay in registers
+  static constexpr int NACT = BWD ? NH : REG ? 0 : 1;    // forward: each layer takes the previous one's place
   static constexpr int act_of(int l) { return BWD ? l : 0; }
   static constexpr int in_r(int l) { return l == 0 ? CIN : H; }
   static constexpr int out_r(int l) { return l == NH ? OUT : H; }
@@ -240,11 +243,17 @@ struct Weights {
   }
 };
 
+// The last hidden layer's activations of a wave's hits as operand fragments,
+// where they stay in registers (Cfg::REG).
+template <class CF>
+using Frags = frag_t[CF::REG ? CF::NFH : 1];
+
 // Hidden layers of the window's first tp hits (a multiple of 64): wave (mg, ng)
 // computes its features of its hits.  Called by all threads; ends with a
-// barrier.
+// barrier.  REG: a wave owns its hits' whole rows and reads back only what its
+// lanes wrote, so the activations stay in registers, and there is no barrier.
 template <class CF>
-__device__ __forceinline__ void hidden_layers(const Weights<CF>& W, int tp, int mg, int ng, int lane) {
+__device__ __forceinline__ void hidden_layers(const Weights<CF>& W, int tp, int mg, int ng, int lane, Frags<CF>& act) {
   constexpr bool BF = CF::BF;
   constexpr int TPW = CF::TPW;
   const int g = lane >> 5, t0 = TPW * ng;
@@ -252,8 +261,7 @@ __device__ __forceinline__ void hidden_layers(const Weights<CF>& W, int tp, int 
   static_for<CF::NH>([&](auto lc) {
     constexpr int l = decltype(lc)::value;
     constexpr int SRC = CF::L_ACT + CF::act_of(l > 0 ? l - 1 : 0) * CF::ACT, DST = CF::L_ACT + CF::act_of(l) * CF::ACT;
-    // in place: all waves have read before any writes (H = 32: own rows only)
-    constexpr bool IN_PLACE = l > 0 && SRC == DST && CF::MG > 1;
+    constexpr bool IN_PLACE = l > 0 && SRC == DST && CF::MG > 1;   // all waves have read before any writes
     f32x16 acc[TPW];
     if (mine) {
       const int ln = here(lane), hit = 32 * t0 + (ln & 31);
@@ -271,7 +279,8 @@ __device__ __forceinline__ void hidden_layers(const Weights<CF>& W, int tp, int 
         for (int i = 0; i < CF::NFH; ++i)
 #pragma unroll
           for (int t = 0; t < TPW; ++t)
-            acc[t] = mma_frag<BF>(W.wh[l - 1][i], frag_at<CF::ROWH>(SRC, hit + 32 * t, 2 * i + g), acc[t]);
+            acc[t] = mma_frag<BF>(W.wh[l - 1][i], CF::REG ? act[CF::REG ? i : 0] : frag_at<CF::ROWH>(SRC, hit + 32 * t, 2 * i + g),
+                                  acc[t]);
       }
     }
     if constexpr (IN_PLACE) __syncthreads();
@@ -279,24 +288,29 @@ __device__ __forceinline__ void hidden_layers(const Weights<CF>& W, int tp, int 
 #pragma unroll
       for (int t = 0; t < TPW; ++t) {
         relu16(acc[t]);
-        store_tile<BF, CF::ROWH>(DST, mg, 32 * (t0 + t) + (lane & 31), g, acc[t]);
+        if constexpr (CF::REG) {
+#pragma unroll
+          for (int q = 0; q < CF::NFH; ++q) act[q] = pack_chunk<BF>(acc[t], q);
+        } else {
+          store_tile<BF, CF::ROWH>(DST, mg, 32 * (t0 + t) + (lane & 31), g, acc[t]);
+        }
       }
     }
-    __syncthreads();
+    if constexpr (!CF::REG) __syncthreads();
   });
 }
 
 // Output layer of the 32 hits from n0: raw o_0 .. o_3 of hit n0 + lane in
 // registers 0 .. 3 of lanes 0 .. 31.
 template <class CF>
-__device__ __forceinline__ f32x16 output_layer(int n0, int lane) {
+__device__ __forceinline__ f32x16 output_layer(int n0, int lane, const Frags<CF>& act) {
   const int ln = here(lane), g = lane >> 5;
   f32x16 o = lds_bias(CF::L_BIAS + CF::NH * CF::H * 4, g);
 #pragma unroll
   for (int i = 0; i < CF::NFH; ++i) {
     frag_t wf = {0, 0, 0, 0};
     if ((ln & 31) < 4) wf = *reinterpret_cast<const frag_t*>(g_lds + CF::L_W3 + ((ln & 31) * 2 * CF::NFH + 2 * i + g) * 16);
-    o = mma_frag<CF::BF>(wf, frag_at<CF::ROWH>(CF::L_LAST, n0 + (ln & 31), 2 * i + g), o);
+    o = mma_frag<CF::BF>(wf, CF::REG ? act[CF::REG ? i : 0] : frag_at<CF::ROWH>(CF::L_LAST, n0 + (ln & 31), 2 * i + g), o);
   }
   return o;
 }
@@ -487,7 +501,8 @@ __global__ __launch_bounds__(kThreads, CF::BLOCKS) void k_shade(ShadeArgs a) {
       __syncthreads();
       if (CF::DEFER && pend_tw > 0) scatter(rb ^ 1);
 
-      hidden_layers<CF>(W, tp, mg, ng, lane);
+      Frags<CF> act;
+      hidden_layers<CF>(W, tp, mg, ng, lane, act);
       const int t0 = TPW * ng;                     // first tile of this wave's hits
       const bool mine = 32 * t0 < tp;
       (void)mine;
@@ -496,7 +511,7 @@ __global__ __launch_bounds__(kThreads, CF::BLOCKS) void k_shade(ShadeArgs a) {
       const int n0 = 32 * wave;
       const bool has_tile = wave < CF::NT && n0 < tw;
       if (has_tile) {
-        const f32x16 o = output_layer<CF>(n0, lane);
+        const f32x16 o = output_layer<CF>(n0, lane, act);
         if (g == 0 && n0 + row < tw) {
           float* hp = out + 8 * (n0 + row);
           const float tmid = hp[6], dt = hp[7];
@@ -805,9 +820,10 @@ __global__ __launch_bounds__(kThreads) void k_mlp_rows(const float* __restrict__
       *reinterpret_cast<frag_t*>(tile_at<CF::ROWX>(CF::L_X, hh, q)) = pack_row<BF>(x);
     }
     __syncthreads();
-    hidden_layers<CF>(W, CF::WIN, mg, ng, lane);
+    Frags<CF> act;
+    hidden_layers<CF>(W, CF::WIN, mg, ng, lane, act);
     if (wave < CF::NT) {
-      const f32x16 o = output_layer<CF>(32 * wave, lane);
+      const f32x16 o = output_layer<CF>(32 * wave, lane, act);
       const int64_t r = base + 32 * wave + (lane & 31);
       if (g == 0 && r < n) {
 #pragma unroll
