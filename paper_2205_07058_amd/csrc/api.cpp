@@ -304,14 +304,15 @@ int run_shade(int mode, const svlf_scene* scenes, int32_t n_scenes, const int64_
   a.n_params = sh.n_params;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
+  // (deterministic calls keep items over all rays)
+  if (n_scenes == 1 && live_planned(n) && !det && w.fits_live(n)) set_live(&a.tab, n, base + w.live);
+  const int n_zero = a.item_counter != nullptr ? 1 : 0;
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
-    // (deterministic: items over all rays, so that a call on reused hits, which
-    // has no live-ray arrays, groups the decoder-gradient partials alike)
-    if (n_scenes == 1 && live_planned(n) && !det && w.fits_live(n)) set_live(&a.tab, n, base + w.live);
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
-                              const_cast<int32_t*>(a.cnt), a.item_counter,
-                              a.item_counter != nullptr ? 1 : 0, s);
-  } else if (a.item_counter != nullptr) {
+                              const_cast<int32_t*>(a.cnt), a.item_counter, n_zero, s);
+  } else if (a.tab.live_n != nullptr) {
+    e = launch_live(a.tab, a.cnt, a.item_counter, n_zero, s);
+  } else if (n_zero > 0) {
     e = launch_fill(reinterpret_cast<float*>(a.item_counter), 0.0f, 1, s);   // 0.0f has zero bits
   }
   if (e != hipSuccess) return hip_fail(e, who);
@@ -467,10 +468,12 @@ int run_lf_call(int mode, const svlf_scene* scenes, int32_t n_scenes, const int6
   a.params = model->params;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
+  if (need_grads && n_scenes == 1 && live_planned(n)) set_live(&a.tab, n, base + w.live);
   if (!(opts->flags & SVLF_FLAG_REUSE_HITS)) {
-    if (need_grads && n_scenes == 1 && live_planned(n)) set_live(&a.tab, n, base + w.live);
     e = launch_trace_internal(a.tab, ray_o, ray_d, opts->K, const_cast<HitRec*>(a.hits),
                               const_cast<int32_t*>(a.cnt), a.item_counters, 3, s);
+  } else if (a.tab.live_n != nullptr) {
+    e = launch_live(a.tab, a.cnt, a.item_counters, 3, s);
   } else {
     e = launch_fill(reinterpret_cast<float*>(a.item_counters), 0.0f, 3, s);   // 0.0f has zero bits
   }

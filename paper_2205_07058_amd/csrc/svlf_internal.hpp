@@ -40,24 +40,20 @@ struct SceneTable {
   int32_t n_items;        // work items over all scenes (plan_items)
   int32_t n_trace;        // traversal blocks over all scenes
   // Live rays (rays with hits) of every traversal block, written by the
-  // traversal: their number and their bit mask.  Null: work items are planned
+  // traversal (reused hits: launch_live): their number and their bit mask.  Null: work items are planned
   // over all rays (plan_items), otherwise over the live ones (LiveRays).
   uint8_t* live_n;        // [n_trace], readable up to live_bytes()
   uint64_t* live_mask;    // [n_trace]
 };
 
-// Calls of one scene with kMinLiveRays to kMaxLiveRays rays, traversed by the
-// call itself, are planned over live rays.  Fewer rays give every block at most
-// one window of hits either way, and counting the live rays is 2 us of a
-// 4,096-ray render's 24.  With more, a thread's stretch of bytes grows past 256
-// and finding a ray past 16 reads, while 256-ray items are 20 rounds of the
-// grid and balance as well.  (One scene: ranks run over the whole call.  A call
-// that reuses hits may take them from a call of another decoder, whose
-// workspace has these arrays elsewhere.)  Measured, all rays -> live rays:
-// 640,000-ray FP32 view 172 -> 155 us, 2,560,000-ray BF16 view 484 -> 457, FP32
-// train step of 262,144 rays 361 -> 262, BF16 of 2^20 1226 -> 1167.
+// Calls of one scene with kMinLiveRays to kMaxLiveRays rays are planned over live
+// rays (one scene: ranks run over the whole call).  Measured, all rays -> live
+// rays: 640,000-ray FP32 view 172 -> 155 us, 2,560,000-ray BF16 view 484 -> 457,
+// FP32 train step of 262,144 rays 361 -> 262, BF16 of 2^20 1226 -> 1167; renders on
+// reused hits, whose arrays are made from the counts (launch_live): 10^6 rays, C =
+// 8, FP32 86 -> 64, C = 16, BF16 94 -> 68.
 // Deterministic calls keep items over all rays (100,003 rays: 384 us, 377 over
-// live rays), so that they give the same bits on their own and on reused hits.
+// live rays).
 constexpr int64_t kMinLiveRays = 1 << 15, kMaxLiveRays = 1 << 22;
 constexpr bool live_planned(int64_t n) { return n >= kMinLiveRays && n <= kMaxLiveRays; }
 constexpr int kLiveItemRays = 128;   // most live rays of a work item
@@ -170,6 +166,7 @@ hipError_t launch_trace_public(const svlf_octree& oct, const float* o, const flo
 hipError_t launch_trace_internal(const SceneTable& tab, const float* o, const float* d,
                                  int K, HitRec* hits, int32_t* cnt, int32_t* zero, int n_zero,
                                  hipStream_t s);
+hipError_t launch_live(const SceneTable& tab, const int32_t* cnt, int32_t* zero, int n_zero, hipStream_t s);
 
 struct ShadeArgs {
   SceneTable tab;

@@ -104,6 +104,23 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace_internal(
   }
 }
 
+// The live-ray arrays of a call that reuses hits, from their counts: one wave per
+// traversal block.  It also clears the work-item counters, in place of a launch of
+// its own.
+__global__ __launch_bounds__(4 * kTraceThreads) void k_live(SceneTable tab, const int32_t* __restrict__ cnt,
+                                                            int32_t* __restrict__ zero, int n_zero) {
+  const int lane = threadIdx.x % kTraceThreads;
+  const int b = blockIdx.x * 4 + threadIdx.x / kTraceThreads;
+  if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < n_zero) zero[threadIdx.x] = 0;
+  if (b >= tab.n_trace) return;
+  const int64_t r = tab.s[0].ray_begin + static_cast<int64_t>(b) * kTraceThreads + lane;
+  const uint64_t m = __ballot(r < tab.s[0].ray_end && cnt[r] > 0);
+  if (lane == 0) {
+    tab.live_n[b] = static_cast<uint8_t>(__popcll(m));
+    tab.live_mask[b] = m;
+  }
+}
+
 size_t stack_bytes(int depth) {
   const int levels = depth > 1 ? depth - 1 : 1;
   return static_cast<size_t>(levels) * kTraceThreads * sizeof(uint2);
@@ -131,6 +148,12 @@ hipError_t launch_trace_internal(const SceneTable& tab, const float* o, const fl
   hipLaunchKernelGGL(k_trace_internal, dim3(static_cast<unsigned>(tab.n_trace)),
                      dim3(kTraceThreads), stack_bytes(max_depth), s, tab, o, d, K, hits, cnt,
                      zero, n_zero);
+  return hipGetLastError();
+}
+
+hipError_t launch_live(const SceneTable& tab, const int32_t* cnt, int32_t* zero, int n_zero, hipStream_t s) {
+  hipLaunchKernelGGL(k_live, dim3(static_cast<unsigned>((tab.n_trace + 3) / 4)), dim3(4 * kTraceThreads), 0, s, tab,
+                     cnt, zero, n_zero);
   return hipGetLastError();
 }
 

@@ -24,7 +24,7 @@ std::map<const void*, std::string>& names() {
 std::map<const void*, int> g_lds_limit;
 // what the calls since the last rec_reset() did
 struct {
-  int launches, traces, live_traces, lds_limit_changes;
+  int launches, traces, live_traces, live_counts, lds_limit_changes;
   uint64_t live_begin, live_end;      // addresses of the live-ray arrays of the last live trace
 } g_rec;
 
@@ -36,6 +36,7 @@ void rec_reset() { std::memset(&g_rec, 0, sizeof(g_rec)); }
 int rec_launches() { return g_rec.launches; }
 int rec_traces() { return g_rec.traces; }
 int rec_live_traces() { return g_rec.live_traces; }
+int rec_live_counts() { return g_rec.live_counts; }
 int rec_lds_limit_changes() { return g_rec.lds_limit_changes; }
 uint64_t rec_live_begin() { return g_rec.live_begin; }
 uint64_t rec_live_end() { return g_rec.live_end; }
@@ -64,11 +65,14 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 }
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
   ++g_rec.launches;
-  if (names()[f].find("k_trace_internal") != std::string::npos) {
-    ++g_rec.traces;
+  const bool trace = names()[f].find("k_trace_internal") != std::string::npos;
+  const bool count = names()[f].find("k_live") != std::string::npos;
+  g_rec.traces += trace;
+  g_rec.live_counts += count;
+  if (trace || count) {
     const auto& tab = *static_cast<const svlf::SceneTable*>(args[0]);
     if (tab.live_n != nullptr) {
-      ++g_rec.live_traces;
+      g_rec.live_traces += trace;
       g_rec.live_begin = reinterpret_cast<uint64_t>(tab.live_n);
       g_rec.live_end = reinterpret_cast<uint64_t>(tab.live_mask + tab.n_trace);
     }

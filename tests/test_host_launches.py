@@ -135,3 +135,16 @@ def test_first_round_of_items_is_dealt(rec):
             dealt = rec.rec_dealt_items(n, blocks)
             assert min(n, blocks) <= dealt <= n and n - dealt <= 2 * blocks
             assert n < 3 * blocks or dealt == n - 2 * blocks
+
+
+@pytest.mark.parametrize("n,live", [((1 << 15) - 1, 0), (1 << 15, 1), (262145, 1), (1 << 22, 1), ((1 << 22) + 1, 0)])
+def test_reused_hits_get_the_live_plan(rec, n, live):
+    """A call that reuses hits has its items planned like one that traverses: the live-ray arrays are made from the
+    counts, inside the workspace."""
+    rc, size = _render(rec, (8, 32, 32, 4), n, flags=svlf.FLAG_REUSE_HITS)
+    assert rc == svlf.OK and rec.rec_traces() == 0 and rec.rec_live_counts() == live and rec.rec_launches() == 2
+    if live:
+        assert FAKE <= rec.rec_live_begin() and rec.rec_live_end() <= FAKE + size
+    # no room (a decoder that no kernel serves): over all rays
+    assert _render(rec, (8, 32, 4), n, flags=svlf.FLAG_REUSE_HITS)[0] == svlf.E_UNSUPPORTED
+    assert rec.rec_live_counts() == (live and n < 1 << 20)
