@@ -28,8 +28,12 @@
 //    with the hits along K (LDS transpose read in BF16).  Forward with H = 32 a
 //    lane would read back just what it stored, so they stay in registers (a
 //    2200^2 FP32 view, C = 8: 592 us of shading through LDS, 495 so);
-//  * blocks per CU: forward 4 (H = 32), 3 (BF16), 2 (FP32; with 64-hit windows 3
-//    fit, 137 instead of 130 us for an 800^2 view); backward 2.  The FP32
+//  * blocks per CU, by registers (launch_bounds) as far as the LDS, which grows
+//    with K, leaves room: forward 4 (H = 32; BF16 with C = 16: a 2200^2 view 716 us
+//    with three, 665 so, and three from K = 10 on), 3 (BF16 with C = 32: four made
+//    an 800^2 view on reused hits 97 -> 109 us) or 2 (FP32; with 64-hit windows 3
+//    fit, 137 instead of 130 us for an 800^2 view); backward 2, but with C = 32 and
+//    the view direction one from K = 9 on (82,384 of 81,920 bytes).  The FP32
 //    backward with H = 64 needs twice the registers: one block (two with the
 //    weights read per window took 374 instead of 348 us for a 262,144-ray train
 //    step), and a window's atomics are issued after the next window's gather, whose
@@ -59,10 +63,10 @@ struct Cfg {
   static constexpr int CIN = C + 3 * VD;                 // decoder inputs
   static constexpr int CI = BF ? align16(CIN) : align8(CIN);
   static constexpr bool BWD = MODE != kForward;
-  static constexpr bool NARROW = BF || H == 32;          // a wave's weights take <= 76 registers
+  static constexpr bool NARROW = BF || H == 32;          // a wave's weights take <= 80 registers
   static constexpr bool DEFER = BWD && !NARROW;
   static constexpr int WIN = 128;
-  static constexpr int BLOCKS = BWD ? (NARROW ? 2 : 1) : (H == 32 ? 4 : NARROW ? 3 : 2);   // per CU, by registers
+  static constexpr int BLOCKS = BWD ? (NARROW ? 2 : 1) : (H == 32 || (BF && C == 16) ? 4 : NARROW ? 3 : 2);   // per CU, by registers
   static constexpr int NT = WIN / 32;                    // 32-hit tiles
   static constexpr int MG = H / 32, NG = kWaves / MG;    // wave grid
   static constexpr int TPW = NT / NG;                    // tiles of a wave's hits
