@@ -296,7 +296,6 @@ hipError_t launch_occupancy(const float* o, const float* d, const float* t, int6
 hipError_t launch_lf(const LfArgs& a, int mode, hipStream_t s);
 
 hipError_t launch_shade(const ShadeArgs& a, int mode, hipStream_t s, int* grid_used);
-size_t shade_workspace_bytes(int64_t n_params, int n_rays_hint);
 int shade_grid_limit();   // rows of the workspace's per-block partials
 int shade_grid_rows();    // most blocks of a launch that writes them
 

@@ -201,7 +201,6 @@ template <bool BF>
 struct Types {
   using Elem = typename std::conditional<BF, uint16_t, float>::type;
   using El = Elem;
-  using Op = typename std::conditional<BF, s16x8, float>::type;
   static constexpr int EB = BF ? 2 : 4;
 };
 
