@@ -30,14 +30,15 @@
 //    2200^2 FP32 view, C = 8: 592 us of shading through LDS, 495 so);
 //  * blocks per CU, by registers (launch_bounds) as far as the LDS, which grows
 //    with K, leaves room: forward 4 (H = 32; BF16 with C = 16: a 2200^2 view 716 us
-//    with three, 665 so, and three from K = 10 on), 3 (BF16 with C = 32: four made
+//    with three, 665 so, and three from K = 11 on), 3 (BF16 with C = 32: four made
 //    an 800^2 view on reused hits 97 -> 109 us) or 2 (FP32; with 64-hit windows 3
 //    fit, 137 instead of 130 us for an 800^2 view); backward 2, but with C = 32 and
 //    the view direction one from K = 9 on (82,384 of 81,920 bytes).  The FP32
 //    backward with H = 64 needs twice the registers: one block (two with the
 //    weights read per window took 374 instead of 348 us for a 262,144-ray train
 //    step), and a window's atomics are issued after the next window's gather, whose
-//    loads would otherwise queue behind them;
+//    loads would otherwise queue behind them.  At 256 registers the BF16 backward
+//    with H = 64 spills 11 to 37, forward with C = 16 at 128 11;
 //  * a row that consecutive hits of a ray share is added once (CornerCarry).
 // Measured against one 124 KB block per CU with the packs in LDS (2^20 rays, C =
 // 32, BF16): train kernel 1.18 -> 1.03 ms, of which 0.5 ms without atomics

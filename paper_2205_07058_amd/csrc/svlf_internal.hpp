@@ -52,6 +52,13 @@ struct SceneTable {
 // FP32 train step of 262,144 rays 361 -> 262, BF16 of 2^20 1226 -> 1167; renders on
 // reused hits, whose arrays are made from the counts (launch_live): 10^6 rays, C =
 // 8, FP32 86 -> 64, C = 16, BF16 94 -> 68.
+// Below the range a render loses the 2 us that counting takes (4,096 rays 33 -> 34
+// us, 32,000 36 -> 38), while backward kernels of one block per CU would gain
+// (light field, FP32: 8,192 rays 310 -> 229 us, 32,000 632 -> 547; C = 32, FP32, K =
+// 16: 12,000 rays 129 -> 95): one limit serves both families.  Above it the arrays
+// outgrow the smallest decoder's rows (756 KB) and the search for a ray in a
+// thread's stretch 16 reads, though larger views would gain too (2200^2: C = 8,
+// BF16 499 -> 457 us, C = 32 774 -> 710).
 // Deterministic calls keep items over all rays (100,003 rays: 384 us, 377 over
 // live rays).
 constexpr int64_t kMinLiveRays = 1 << 15, kMaxLiveRays = 1 << 22;
@@ -94,10 +101,12 @@ constexpr int kTraceThreads = 64;    // rays (threads) of a traversal block
 // the last rounds are handed out on demand, which balances as well and keeps
 // neighbouring rays together.  The limit is higher in the backward kernels,
 // whose items are long (400,009 rays over three scenes, 3.1 rounds: 470 us
-// with on-demand rounds, 374 us spread; at 8 rounds no difference); forward
-// kernels gain more from neighbours sharing rows in L2 (an 800^2 FP32 view, 4.9
-// rounds: 153 us, spread 172 us; views of up to 3 rounds are 0 to 25% faster
-// spread).
+// with on-demand rounds, 374 us spread; at 8 rounds no difference).  Forward, the
+// light field sets it: its kernels gain from neighbours sharing rows in L2 (800^2
+// view, 5 rounds: BF16 337 us, spread 354; FP32 1,388 and 1,466; 500^2, 2 rounds:
+// BF16 203, spread 186).  Renders of several scenes by the single decoder would
+// gain further up (three scenes, 640,000 rays, 4 and 5 rounds: FP32, C = 32, 254
+// us, 150 spread; BF16, C = 32, 129 and 95).
 constexpr int kBalancedRounds = 3, kBalancedRoundsBwd = 6;
 constexpr int kMinItemRays = 16;
 
